@@ -28,8 +28,12 @@ from paper_1712_10116_amd import workloads as W
 # softening of each particle distribution
 EPS = {"plummer": 0.01, "sphere": 0.005, "disk": 0.02, "zoom": 0.001}
 LEAVES = (16, 24, 32, 48, 64, 96, 128)
-# integrator parameters of the serving ensemble
-RUN = dict(eps=0.01, theta=0.5, p=4, eta=0.0025, max_levels=10)
+# Integrator parameters: those of the serving ensemble at the opening angle of the
+# paper's cold collapse.  At 0.5 every pair of equal cells two cells apart lies
+# exactly on the threshold of the opening test, where the last bit of a position
+# decides it, so that trajectories could only be compared bit for bit; at 0.45 no
+# pair of cells does.
+RUN = dict(eps=0.01, theta=0.45, p=4, eta=0.0025, max_levels=10)
 DT_TOP = 1.0 / 16
 # force particles of one top-level step per particle of the system, measured
 # on the ensemble's systems (an estimate for work(): it depends on the rungs)

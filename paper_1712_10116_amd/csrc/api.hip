@@ -63,7 +63,8 @@ static bool alloc_nodes(fmm_ctx *c, int64_t cap) {
             dalloc(c, &t.bounds, cap * 8) && dalloc(c, &t.m2l_off, cap) &&
             dalloc(c, &t.m2l_cnt, cap) && dalloc(c, &t.p2p_off, cap) &&
             dalloc(c, &t.p2p_cnt, cap) && dalloc(c, &t.open_off, cap) &&
-            dalloc(c, &t.open_cnt, cap) && dalloc(c, &t.nreq, cap);
+            dalloc(c, &t.open_cnt, cap) && dalloc(c, &t.nreq, cap) &&
+            dalloc(c, &t.nshare, cap) && dalloc(c, &t.part_off, cap);
   if (!ok) return false;
   char *m = nullptr, *l = nullptr, *mh = nullptr;
   ok = dalloc(c, &m, (int64_t)(cap * t.kmax * real)) && dalloc(c, &l, (int64_t)(cap * t.kmax * real)) &&
@@ -78,7 +79,7 @@ static void free_nodes(fmm_ctx *c) {
   DevTree &t = c->t;
   void *ptrs[] = {t.nbeg, t.nend, t.nlev, t.nparent, t.nchild0, t.nnchild, t.ngeo, t.bounds,
                   t.m2l_off, t.m2l_cnt, t.p2p_off, t.p2p_cnt, t.open_off, t.open_cnt, t.M, t.L,
-                  t.Mh, t.nreq};
+                  t.Mh, t.nreq, t.nshare, t.part_off};
   for (void *p : ptrs) dfree(c, p);
 }
 
@@ -173,7 +174,13 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
     t.cap_m2l = 96 * cap_nodes;
     t.cap_p2p = 32 * cap_nodes;
     t.cap_open = 16 * cap_nodes;
-    ok = dalloc(c, &t.m2l_src, t.cap_m2l) && dalloc(c, &t.p2p_src, t.cap_p2p) &&
+    // near-field items and partial rows: small systems are cut fine (up to a
+    // share per window), large ones only at long lists
+    t.p2p_src_window = p2p_window_sources(prm->precision == FMM_PREC_MIXED);
+    t.cap_items = 2 * cap_nodes + 65536;
+    t.cap_part = std::min<int64_t>(4 * n, n / 4 + (4 << 20)) + 65536;
+    ok = dalloc(c, &t.items, t.cap_items) && dalloc(c, &t.part, t.cap_part) &&
+         dalloc(c, &t.m2l_src, t.cap_m2l) && dalloc(c, &t.p2p_src, t.cap_p2p) &&
          dalloc(c, &t.open_buf0, t.cap_open) && dalloc(c, &t.open_buf1, t.cap_open);
   }
   ok = ok && dalloc(c, &c->inv_part, FMM_INV_BLOCKS * 12);
@@ -352,6 +359,26 @@ static fmm_status regrow_lists(fmm_ctx *c, int which, int64_t need) {
   return FMM_OK;
 }
 
+// Regrow the near-field items and partial rows to what a plan counted (every
+// workgroup counts its cells, also when they do not fit).
+static fmm_status regrow_items(fmm_ctx *c, int64_t items, int64_t rows) {
+  DevTree &t = c->t;
+  if (items > t.cap_items) {
+    dfree(c, t.items);
+    t.items = nullptr;
+    t.cap_items = items + items / 4;
+    if (!dalloc(c, &t.items, t.cap_items)) return fail(c, FMM_ENOMEM, "P2P item regrow failed");
+  }
+  if (rows > t.cap_part) {
+    if (rows > INT32_MAX) return fail(c, FMM_EOVERFLOW, "P2P partial sums of %lld rows", (long long)rows);
+    dfree(c, t.part);
+    t.part = nullptr;
+    t.cap_part = std::min<int64_t>(rows + rows / 4, INT32_MAX);
+    if (!dalloc(c, &t.part, t.cap_part)) return fail(c, FMM_ENOMEM, "P2P partial-sum regrow failed");
+  }
+  return FMM_OK;
+}
+
 static void set_eval_args(fmm_ctx *c, EvalArgs &e, int64_t n_all, int p, double eps) {
   e.n = (int)n_all;
   e.p = p;
@@ -389,6 +416,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   if (st != FMM_OK) return st;
   BuildArgs a = {};
   a.n = (int)n_all;
+  for (int r = 0; r < n_req; ++r) a.n_max = std::max(a.n_max, (int)reqs[r].n_active);
   a.n_req = n_req;
   a.n_blk = n_blk;
   a.leaf_size = c->prm.leaf_size;
@@ -421,7 +449,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     if (st != FMM_OK) return st;
     if (c->hh.nonfinite) return fail(c, FMM_ENONFINITE, "non-finite input position");
     if (c->hh.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
-    if (!(c->hh.overflow & (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN))) return finish(tree_depth());
+    if (!(c->hh.overflow & (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS)))
+      return finish(tree_depth());
   }
   // 1a. split levels predicted from recent builds: tree and walk queued behind
   // the sort, one readback.  The tree equals the one built below whenever the
@@ -472,8 +501,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     memcpy(&c->hh, c->pin_hdr, sizeof(Header));
     if (c->hh.nonfinite) return fail(c, FMM_ENONFINITE, "non-finite input position");
     const int need = std::min(FMM_MAXLEVEL, c->hh.max_prefix + 1);
-    if (need <= pred &&
-        !(c->hh.overflow & (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH))) {
+    if (need <= pred && !(c->hh.overflow & OVF_ANY)) {
       record_levels(c, need);
       st = finish(tree_depth());
       if (st == FMM_OK && fuse) {
@@ -564,7 +592,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     }
     const Header &h = c->hh;
     if (h.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
-    if (h.overflow & (OVF_M2L | OVF_P2P | OVF_OPEN)) {
+    if (h.overflow & (OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS)) {
       if (h.overflow & OVF_M2L) {
         st = regrow_lists(c, OVF_M2L, h.m2l_cursor);
         if (st != FMM_OK) return st;
@@ -577,6 +605,10 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
         uint32_t mx = 0;
         for (int l = 0; l < FMM_NLEVELS; ++l) mx = std::max(mx, h.open_cursor[l]);
         st = regrow_lists(c, OVF_OPEN, mx);
+        if (st != FMM_OK) return st;
+      }
+      if (h.overflow & OVF_ITEMS) {
+        st = regrow_items(c, h.item_cursor, (int64_t)h.part_cursor);
         if (st != FMM_OK) return st;
       }
       continue;

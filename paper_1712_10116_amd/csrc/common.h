@@ -41,6 +41,10 @@
 // the tree holds cells deeper than the levels the (predicted) walk covers: the
 // cells below them have no lists, so nothing may be evaluated on it
 #define OVF_DEPTH 32
+// the P2P work items, or the partial sums of split leaves, did not fit
+#define OVF_ITEMS 64
+#define OVF_ANY \
+  (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH | OVF_ITEMS)
 
 struct Header {
   int32_t lvl_start[FMM_NLEVELS + 2];  // nodes of level l: [lvl_start[l], lvl_start[l+1])
@@ -52,6 +56,17 @@ struct Header {
   unsigned long long p2p_pairs;        // ordered particle interactions in P2P
   int32_t n_leaves;
   int32_t max_prefix;  // deepest level of a cell holding more than leaf_size particles
+  uint32_t item_cursor;            // near-field work items of the tree
+  unsigned long long part_cursor;  // partial-sum rows of its split leaves
+};
+
+// One wavefront's share of the near field: sinks tb .. tb + 63 of leaf A
+// against the entries [q0, q1) of its P2P list and, when those are one chunk
+// of 64, the windows [w0, w1) of that chunk's source stream.  grp counts the
+// leaf's shares; the sums of share 0 go to near[], those of the others to row
+// part + (sink of the leaf) of the partial sums.
+struct P2PItem {
+  int32_t A, tb, q0, q1, w0, w1, grp, part;
 };
 
 // Box: o[3] (origin), L (side), s = 2^21/L, lo[3], hi[3]
@@ -108,6 +123,12 @@ struct DevTree {
   int32_t *p2p_off, *p2p_cnt, *p2p_src;
   int32_t *open_off, *open_cnt;
   int32_t *open_buf0, *open_buf1;
+  // near-field work items (k_p2p_plan) and the partial sums of split leaves:
+  // shares 1 .. nshare of leaf A at rows part_off[A] + (share - 1) * (its
+  // particles) + sink
+  P2PItem *items;                // [cap_items]
+  int32_t *nshare, *part_off;    // [cap_nodes]
+  double4 *part;                 // [cap_part] ax, ay, az, pot
   // scratch
   int32_t *scan_part;          // [FMM_SCAN_BLOCKS]
   double *bbox_part;           // [bbox blocks][6]
@@ -116,7 +137,8 @@ struct DevTree {
   uint32_t *scan_blk;          // block sums of the generic scan
   Header *hdr;
   Box *box;  // [cap_req]
-  int64_t cap_n, cap_nodes, cap_m2l, cap_p2p, cap_open;
+  int64_t cap_n, cap_nodes, cap_m2l, cap_p2p, cap_open, cap_items, cap_part;
+  int p2p_src_window;  // sources of one staged P2P window (by precision)
   int kmax, khmax;
 };
 
@@ -236,6 +258,7 @@ struct PhaseTimer {
 // ---------------------------------------------------------------------------
 struct BuildArgs {
   int n;          // active particles over all requests
+  int n_max;      // most active particles of one request
   int n_req;      // requests (roots)
   int n_blk;      // bbox blocks over all requests
   int leaf_size;
@@ -293,6 +316,8 @@ hipError_t launch_evaluate(const DevTree &t, const EvalArgs &e, hipStream_t s);
 // mass gather, P2M and M2M of an evaluation on stream s (exact tree sizes)
 hipError_t launch_upward(const DevTree &t, const EvalArgs &e, hipStream_t s);
 bool eval_order_supported(int p);
+// sources of one staged P2P window
+int p2p_window_sources(bool mixed);
 // grad.hip: force gradient of one system's n active particles (SoA 6 x n) on
 // the tree and local expansions of the evaluation just queued on stream s
 hipError_t launch_force_gradient(const DevTree &t, int n_nodes, int n, int p, int kernel,

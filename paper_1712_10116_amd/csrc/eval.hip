@@ -79,8 +79,7 @@ __device__ __forceinline__ bool has_sink(const DevTree &t, int A, int bA, int nA
 // nothing is evaluated on a tree or lists whose build overflowed a
 // workspace (node arrays, list buffers or descent stack).
 __device__ __forceinline__ bool tree_incomplete(const DevTree &t) {
-  return (t.hdr->overflow & (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH)) !=
-         0;
+  return (t.hdr->overflow & OVF_ANY) != 0;
 }
 __device__ __forceinline__ int node_count(const DevTree &t, int n) {
   if (n >= 0) return n;
@@ -475,15 +474,28 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2p(DevTree t, int n, bool dev, d
   T phi, gx, gy, gz;
   l2p_eval<T, P>(Lt, mono, phi, gx, gy, gz);
   const int64_t cap = t.cap_n;
-  q.acc[i] = sgn * (t.near[j] - (double)gx * ih);
-  q.acc[nq + i] = sgn * (t.near[cap + j] - (double)gy * ih);
-  q.acc[2 * nq + i] = sgn * (t.near[2 * cap + j] - (double)gz * ih);
-  q.pot[i] = t.near[3 * cap + j] + (double)phi;
+  double nx = t.near[j], ny = t.near[cap + j], nz = t.near[2 * cap + j], np = t.near[3 * cap + j];
+  const int ne = sgn > 0 ? t.nshare[leaf] : 0;  // the vector-source near field is not cut
+  if (ne > 0) {  // the near field's further shares, in share order
+    const int b = t.nbeg[leaf], na = t.nend[leaf] - b;
+    const double4 *row = t.part + t.part_off[leaf] + (j - b);
+    for (int k = 0; k < ne; ++k) {
+      const double4 v = row[(int64_t)k * na];
+      nx += v.x;
+      ny += v.y;
+      nz += v.z;
+      np += v.w;
+    }
+  }
+  q.acc[i] = sgn * (nx - (double)gx * ih);
+  q.acc[nq + i] = sgn * (ny - (double)gy * ih);
+  q.acc[2 * nq + i] = sgn * (nz - (double)gz * ih);
+  q.pot[i] = np + (double)phi;
 }
 
 // ---------------------------------------------------------------------------
-// P2P: one wavefront per target leaf, lanes = (sink, phase) pairs in a layout
-// chosen per leaf (below).
+// P2P: one wavefront per work item, lanes = (sink, phase) pairs in a layout
+// chosen per group of sinks (below).
 // ---------------------------------------------------------------------------
 template <typename R, int KERNEL>
 struct PairKernel {
@@ -513,8 +525,11 @@ struct PairKernel {
   }
 };
 
-// One wavefront per target leaf A.  The particles of every leaf in A's P2P
-// list (A itself included) form one stream, staged into LDS in windows of up
+// One wavefront per work item: up to 64 sinks of a target leaf A against a
+// share of A's P2P list (see k_p2p_plan), a workgroup each, so that a short
+// item does not hold its slot until a long neighbour ends (four to a workgroup:
+// 2^20 solve 1.62 -> 1.69 ms).  The particles of every leaf in the list chunk
+// (A itself included) form one stream, staged into LDS in windows of up
 // to SRC particles -- FP32 offsets from A's centre in the mixed form, absolute
 // FP64 positions in the FP64 form.  Consecutive lanes load consecutive slots,
 // each finding its particle from the list entry that holds the slot (a binary
@@ -533,7 +548,8 @@ struct PairKernel {
 // away, so every lane runs the same number of unrolled blocks with no bounds
 // test.  FP32 partial sums are added into FP64 accumulators after every block
 // of UNROLL sources.
-#define P2P_WAVES 4
+#define P2P_WAVES 1
+#define P2P_XCD_CHUNK 128  // items per XCD chunk
 #define P2P_UNROLL 8
 #define P2P_MAXPH 16  // at most 16 phases, so a window pads to a multiple of 128
 
@@ -733,7 +749,7 @@ __device__ __forceinline__ int p2p_lanes_log2(int ns) {
 // zero (dx = 0) -- and its potential term, reproduced bit for bit, is taken
 // off once per sink.
 template <bool MIXED, int KERNEL, bool SELF>
-__global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t, int n_nodes, double eps) {
+__global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t, double eps) {
   typedef typename P2PTypes<MIXED>::R R;
   typedef typename P2PTypes<MIXED>::R4 R4;
   constexpr int SRC = P2PTypes<MIXED>::SRC;
@@ -748,20 +764,24 @@ __global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t
   R(*sk)[64] = sink_all[w];
   // the target leaf and all that is read from it are the same in every lane:
   // kept in scalar registers
-  const int wave = __builtin_amdgcn_readfirstlane(xcd_block<32>(blockIdx.x, gridDim.x) * P2P_WAVES + w);
+  const int wave = __builtin_amdgcn_readfirstlane(
+      xcd_block<P2P_XCD_CHUNK / P2P_WAVES>(blockIdx.x, gridDim.x) * P2P_WAVES + w);
   const int nwaves = gridDim.x * P2P_WAVES;
   const R eps2 = (R)(eps * eps);
   const R inv_eps = eps > 0 ? (R)(1.0 / eps) : R(0);
   const R inv_eps3 = eps > 0 ? (R)(1.0 / (eps * eps * eps)) : R(0);
   const int64_t cap = t.cap_n;
-  n_nodes = node_count(t, n_nodes);
-  for (int A = wave; A < n_nodes; A += nwaves) {
-    if (t.nnchild[A] != 0 || skipped(t, A)) continue;
+  const int n_items = tree_incomplete(t) ? 0 : (int)t.hdr->item_cursor;
+  for (int it = wave; it < n_items; it += nwaves) {
+    const P2PItem im = t.items[it];
+    const int A = im.A;
+    if (skipped(t, A)) continue;
     const int bA = t.nbeg[A], nA = t.nend[A] - bA;
     if (!has_sink(t, A, bA, nA)) continue;
     const double4 gA = t.ngeo[A];
-    const int off = t.p2p_off[A], cnt = t.p2p_cnt[A];
-    for (int tb = 0; tb < nA; tb += 64) {
+    const int off = t.p2p_off[A], cnt = im.q1;
+    const int tb = im.tb;
+    {
       const int ns = min(64, nA - tb);
       const int lg = p2p_lanes_log2(ns);
       const int LP = 1 << lg;                  // sinks per pass
@@ -785,7 +805,7 @@ __global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t
         sk[2][lane] = t.sz[gi];
       }
       double ax = 0, ay = 0, az = 0, pp = 0;
-      for (int qb = 0; qb < cnt; qb += 64) {
+      for (int qb = im.q0; qb < cnt; qb += 64) {
         const int q = qb + lane;
         const bool vq = q < cnt;
         const int B = vq ? t.p2p_src[off + q] : A;
@@ -800,7 +820,8 @@ __global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t
             __builtin_amdgcn_readfirstlane(selfm ? __shfl(pos, self_lane, 64) : -(1 << 30));
         lf[lane] = make_int3(pos, nb, bB);  // kept in LDS across the windows
         __builtin_amdgcn_wave_barrier();
-        for (int w0 = 0; w0 < total; w0 += SRC) {
+        const int wend = im.w1 < total / SRC + 1 ? im.w1 * SRC : total;
+        for (int w0 = im.w0 * SRC; w0 < wend && w0 < total; w0 += SRC) {
           const int W = min(SRC, total - w0);
           const int Wr = (W + blk - 1) / blk * blk;
           // consecutive lanes stage consecutive slots, two per lane at a
@@ -876,17 +897,21 @@ __global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t
         az = group_sum(az, nph);
         pp = group_sum(pp, nph);
       }
-      if (!SELF) {  // the self pair's potential term, as the loop computed it
+      if (!SELF && im.grp == 0) {  // the self pair's potential term, as the loop computed it
         R mg0, t0;
         PairKernel<R, KERNEL>::eval(R(0), MIXED ? (R)t.sm32[gi] : (R)t.sm[gi], eps2, inv_eps,
                                     inv_eps3, mg0, t0);
         pp += (double)t0;
       }
       if (hv) {
-        t.near[gi] = ax;
-        t.near[cap + gi] = ay;
-        t.near[2 * cap + gi] = az;
-        t.near[3 * cap + gi] = pp;
+        if (im.grp == 0) {
+          t.near[gi] = ax;
+          t.near[cap + gi] = ay;
+          t.near[2 * cap + gi] = az;
+          t.near[3 * cap + gi] = pp;
+        } else {
+          t.part[im.part + (gi - bA)] = make_double4(ax, ay, az, pp);
+        }
       }
     }
   }
@@ -950,14 +975,15 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   hipEventRecord(e.fork, s);
   hipStreamWaitEvent(e.side, e.fork, 0);
   const int tp = tm ? tm->begin(PH_P2P, e.side) : -1;
+  // the number of items is read on the device: about one to two per leaf of a
+  // large system, up to one per staged window of a small one
+  const int p2p_blocks = ((e.n <= 131072 ? 8 : 2) * ga + P2P_WAVES - 1) / P2P_WAVES;
   if (e.eps > 0)
-    hipLaunchKernelGGL((k_p2p<(sizeof(T) == 4), KERNEL, false>),
-                       dim3((ga + P2P_WAVES - 1) / P2P_WAVES), dim3(P2P_WAVES * 64), 0, e.side,
-                       t, narg, e.eps);
+    hipLaunchKernelGGL((k_p2p<(sizeof(T) == 4), KERNEL, false>), dim3(p2p_blocks),
+                       dim3(P2P_WAVES * 64), 0, e.side, t, e.eps);
   else
-    hipLaunchKernelGGL((k_p2p<(sizeof(T) == 4), KERNEL, true>),
-                       dim3((ga + P2P_WAVES - 1) / P2P_WAVES), dim3(P2P_WAVES * 64), 0, e.side,
-                       t, narg, e.eps);
+    hipLaunchKernelGGL((k_p2p<(sizeof(T) == 4), KERNEL, true>), dim3(p2p_blocks),
+                       dim3(P2P_WAVES * 64), 0, e.side, t, e.eps);
   if (tm) tm->end(tp, e.side);
   hipEventRecord(e.join, e.side);
   if (e.upward_done)
@@ -1006,6 +1032,8 @@ static bool dispatch_order(const DevTree &t, const EvalArgs &e, hipStream_t s) {
 }
 
 bool eval_order_supported(int p) { return p >= 1 && p <= 6; }
+
+int p2p_window_sources(bool mixed) { return mixed ? P2PTypes<true>::SRC : P2PTypes<false>::SRC; }
 
 template <typename T, int KERNEL>
 static bool dispatch_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {

@@ -398,10 +398,243 @@ __global__ __launch_bounds__(TRAV_WAVES * 64) void k_walk_level_dev(DevTree t, i
     walk_parent(t, l, P, th2, eps, lds[w]);
 }
 
+__global__ void k_reset_lists(Header *h) {
+  int i = threadIdx.x;
+  if (i == 0) {
+    h->m2l_cursor = 0;
+    h->p2p_cursor = 0;
+    h->p2p_pairs = 0;
+    h->overflow &= OVF_NODES | OVF_DEPTH;
+    h->item_cursor = 0;
+    h->part_cursor = 0;
+  }
+  if (i < FMM_NLEVELS) h->open_cursor[i] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// Near-field work items.  With one wavefront per leaf the near field waited
+// for its longest list: a sparse outer leaf of a concentrated system lists a
+// large part of all leaves (12,526-particle Plummer sphere, leaf 64: one leaf
+// of 785 kept P2P running for 540 us, now 34).  A leaf's list is therefore cut
+// into shares, each summed by a wavefront of its own and added up in share
+// order when L2P reads them; the groups of 64 sinks of a leaf are separate
+// items too (they had been taken in turn by one wavefront).
+//
+// The cut depends on the leaf, its list and the size of its own system only,
+// so a system's sums do not depend on what it is batched with, nor on the
+// sinks asked for.  Shares consist of whole windows of the source stream, so
+// the FP32 partial sums of the mixed form are those of the uncut list.
+//
+// Windows per share (0: whole chunks, P2P_SHARE_CHUNKS of them): small systems
+// have too few leaves to fill the chip, so every window is a share; large ones
+// have leaves enough and are cut only where a list is long (disk galaxy 2^22:
+// solve 14.4 -> 13.1 ms).  Systems of at most 1024 particles have no list
+// longer than a few windows and the multipole passes beside P2P take longer:
+// not cut, which needs no look at the sources.
+// ---------------------------------------------------------------------------
+#define P2P_SHARE_CHUNKS 4
+#define P2P_SHARE_MAX_LEAF 4096  // larger leaves (coincident particles) are cut by sinks only
+#define P2P_SHARE_FINE_N 524288  // largest system cut by windows
+__device__ __forceinline__ int p2p_share_windows(int n) {
+  if (n <= SMALL_AUTO_N || n > P2P_SHARE_FINE_N) return 0;
+  return n <= 32768 ? 1 : n <= 131072 ? 2 : 4;
+}
+
+// shares of a leaf of nA particles whose list of cnt entries is cut by whole chunks
+__device__ __forceinline__ int whole_chunk_shares(int nA, int cnt) {
+  return nA > P2P_SHARE_MAX_LEAF
+             ? 1
+             : max(1, (cnt + 64 * P2P_SHARE_CHUNKS - 1) / (64 * P2P_SHARE_CHUNKS));
+}
+
+__device__ __forceinline__ void emit_whole_chunks(const DevTree &t, int A, int nA, int cnt,
+                                                  int groups, int64_t i0, int64_t r0) {
+  const int T = (nA + 63) >> 6;
+  const int per = groups > 1 ? 64 * P2P_SHARE_CHUNKS : max(cnt, 1);
+  for (int k = 0; k < groups; ++k)
+    for (int q = 0; q < T; ++q)
+      t.items[i0 + (int64_t)k * T + q] =
+          P2PItem{A, q * 64, k * per, min(cnt, (k + 1) * per), 0, 1 << 30, k,
+                  k ? (int32_t)(r0 + (int64_t)(k - 1) * nA) : -1};
+}
+
+#define PLAN_WAVES 16
+#define PLAN_CHUNKS 256  // window counts of list chunks a wavefront keeps
+
+// Source windows of the four chunks of 64 list entries from qb on, summed over
+// the wavefront (0 past the list's end); their loads are independent.
+__device__ __forceinline__ void chunk_windows(const DevTree &t, int off, int cnt, int qb,
+                                              int (&nw)[4]) {
+  const int lane = threadIdx.x & 63;
+  int B[4], nb[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int q = qb + 64 * k + lane;
+    B[k] = q < cnt ? t.p2p_src[off + q] : -1;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) nb[k] = B[k] >= 0 ? t.nend[B[k]] - t.nbeg[B[k]] : 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    nw[k] = (wave_sum(nb[k]) + t.p2p_src_window - 1) / t.p2p_src_window;
+}
+
+// Each wavefront plans npw consecutive cells, 64 at a time: a lane per cell,
+// and for systems cut by windows the whole wavefront on one leaf after the
+// other (it adds up the source counts of the leaf's chunks).  A workgroup
+// allocates its items and rows with one atomic each.
+__global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw_min) {
+  __shared__ int s_items[PLAN_WAVES];
+  __shared__ unsigned long long s_rows[PLAN_WAVES];
+  __shared__ unsigned s_item0;
+  __shared__ unsigned long long s_row0;
+  __shared__ uint16_t s_nw[PLAN_WAVES][PLAN_CHUNKS];
+  Header *h = t.hdr;
+  if (h->overflow & (OVF_ANY & ~OVF_ITEMS)) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int nn = min(h->lvl_start[FMM_NLEVELS], (int)t.cap_nodes);
+  const int nwaves = gridDim.x * PLAN_WAVES;
+  const int npw = max((nn + nwaves - 1) / nwaves, npw_min);
+  const int64_t first = (int64_t)(blockIdx.x * PLAN_WAVES + w) * npw;
+  for (int b = 0; b < npw; b += 64) {
+    const int64_t id = first + b + lane;
+    const bool leaf = b + lane < npw && id < nn && t.nnchild[id] == 0;
+    const int A = leaf ? (int)id : 0;
+    int nA = 0, cnt = 0, off = 0, g = 0, groups = 0;
+    if (leaf) {
+      nA = t.nend[A] - t.nbeg[A];
+      cnt = t.p2p_cnt[A];
+      off = t.p2p_off[A];
+      g = p2p_share_windows(t.reqs[t.nreq[A]].n);
+      groups = whole_chunk_shares(nA, cnt);
+    }
+    const unsigned long long fine = __ballot(leaf && g > 0 && nA <= P2P_SHARE_MAX_LEAF && cnt > 0);
+    int used = 0;  // chunks counted so far in this batch (kept up to PLAN_CHUNKS)
+    for (unsigned long long m = fine; m; m &= m - 1) {
+      const int l = (int)__ffsll((long long)m) - 1;
+      const int c = __shfl(cnt, l, 64), o = __shfl(off, l, 64), gl = __shfl(g, l, 64);
+      int sum = 0;
+      for (int qb = 0; qb < c; qb += 256) {
+        int nw[4];
+        chunk_windows(t, o, c, qb, nw);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (qb + 64 * k < c) {
+            if (lane == 0 && used < PLAN_CHUNKS) s_nw[w][used] = (uint16_t)nw[k];
+            ++used;
+          }
+          sum += (nw[k] + gl - 1) / gl;
+        }
+      }
+      if (lane == l) groups = max(1, sum);
+    }
+    const int T = (nA + 63) >> 6;
+    const int items = leaf ? groups * T : 0;
+    const int rows = leaf ? (groups - 1) * nA : 0;
+    int itot, rtot;
+    const int ipos = wave_excl_scan_int(items, &itot);
+    const int rpos = wave_excl_scan_int(rows, &rtot);
+    if (lane == 0) {
+      s_items[w] = itot;
+      s_rows[w] = (unsigned long long)rtot;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      unsigned it = 0;
+      unsigned long long r = 0;
+      for (int k = 0; k < PLAN_WAVES; ++k) {
+        it += (unsigned)s_items[k];
+        r += s_rows[k];
+      }
+      s_item0 = it ? atomicAdd(&h->item_cursor, it) : 0u;
+      s_row0 = r ? atomicAdd(&h->part_cursor, r) : 0ull;
+      if ((int64_t)s_item0 + it > t.cap_items || (int64_t)(s_row0 + r) > t.cap_part) {
+        atomicOr(&h->overflow, OVF_ITEMS);
+        s_item0 = 0xffffffffu;
+      }
+    }
+    __syncthreads();
+    int64_t i0 = s_item0, r0 = (int64_t)s_row0;
+    const bool fits = s_item0 != 0xffffffffu;
+    for (int k = 0; k < w; ++k) {
+      i0 += s_items[k];
+      r0 += (int64_t)s_rows[k];
+    }
+    __syncthreads();  // the totals are rewritten by the next batch
+    if (!fits) continue;  // uniform over the workgroup
+    i0 += ipos;
+    r0 += rpos;
+    if (leaf) {
+      t.nshare[A] = groups - 1;
+      t.part_off[A] = (int32_t)r0;
+      if (!(fine >> lane & 1)) emit_whole_chunks(t, A, nA, cnt, groups, i0, r0);
+    }
+    int at = 0;  // the batch's chunks in the order counted
+    for (unsigned long long m = fine; m; m &= m - 1) {
+      const int l = (int)__ffsll((long long)m) - 1;
+      const int c = __shfl(cnt, l, 64), o = __shfl(off, l, 64), gl = __shfl(g, l, 64);
+      const int Al = __shfl(A, l, 64), nl = __shfl(nA, l, 64), Tl = __shfl(T, l, 64);
+      const int64_t il = (int64_t)__shfl((unsigned long long)i0, l, 64);
+      const int64_t rl = (int64_t)__shfl((unsigned long long)r0, l, 64);
+      int done = 0;  // shares of the chunks before
+      for (int qb = 0; qb < c; qb += 64, ++at) {
+        int nw;
+        if (at < PLAN_CHUNKS) {
+          nw = s_nw[w][at];
+        } else {
+          int n4[4];
+          chunk_windows(t, o, min(c, qb + 64), qb, n4);
+          nw = n4[0];
+        }
+        const int ng = (nw + gl - 1) / gl;
+        for (int k = lane; k < ng * Tl; k += 64) {
+          const int gk = done + k / Tl, q = k % Tl;
+          t.items[il + (int64_t)gk * Tl + q] =
+              P2PItem{Al, q * 64, qb, min(c, qb + 64), (k / Tl) * gl, (k / Tl + 1) * gl, gk,
+                      gk ? (int32_t)(rl + (int64_t)(gk - 1) * nl) : -1};
+        }
+        done += ng;
+      }
+      if (done == 0)  // no sources
+        for (int q = lane; q < Tl; q += 64)
+          t.items[il + q] = P2PItem{Al, q * 64, 0, 0, 0, 0, 0, -1};
+    }
+  }
+}
+
+// The items of a tree of at most SMALL_AUTO_N particles, whose systems are all
+// cut by whole chunks, by the workgroup that walked it (they always fit: at
+// most 1024 leaves of at most four shares, against 65,536 items and rows).
+__device__ void plan_small(const DevTree &t) {
+  __shared__ int s_items, s_rows;
+  if (threadIdx.x == 0) s_items = s_rows = 0;
+  __syncthreads();
+  Header *h = t.hdr;
+  if (!(h->overflow & OVF_ANY)) {
+    const int nn = min(h->lvl_start[FMM_NLEVELS], (int)t.cap_nodes);
+    for (int A = threadIdx.x; A < nn; A += SMALL_THREADS) {
+      if (t.nnchild[A] != 0) continue;
+      const int nA = t.nend[A] - t.nbeg[A], cnt = t.p2p_cnt[A];
+      const int groups = whole_chunk_shares(nA, cnt);
+      const int i0 = atomicAdd(&s_items, groups * ((nA + 63) >> 6));
+      const int r0 = atomicAdd(&s_rows, (groups - 1) * nA);
+      t.nshare[A] = groups - 1;
+      t.part_off[A] = r0;
+      emit_whole_chunks(t, A, nA, cnt, groups, i0, r0);
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    h->item_cursor = (unsigned)s_items;
+    h->part_cursor = (unsigned long long)s_rows;
+  }
+}
+
 // All levels of the walk in one workgroup (small trees): the waves share the
 // parents of a level, and a barrier separates levels (a level reads the open
 // lists the previous one wrote).  Level sizes come from the tree header.
-__global__ __launch_bounds__(SMALL_THREADS) void k_walk_small(DevTree t, double th2, double eps) {
+__global__ __launch_bounds__(SMALL_THREADS) void k_walk_small(DevTree t, double th2, double eps,
+                                                              bool plan) {
   __shared__ WaveLds lds[SMALL_WAVES];
   const int w = threadIdx.x >> 6;
   const Header *h = t.hdr;
@@ -412,17 +645,17 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_walk_small(DevTree t, double 
     for (int P = ps + w; P < pe; P += SMALL_WAVES) walk_parent(t, l, P, th2, eps, lds[w]);
     __syncthreads();
   }
+  if (plan) plan_small(t);
 }
 
-__global__ void k_reset_lists(Header *h) {
-  int i = threadIdx.x;
-  if (i == 0) {
-    h->m2l_cursor = 0;
-    h->p2p_cursor = 0;
-    h->p2p_pairs = 0;
-    h->overflow &= OVF_NODES | OVF_DEPTH;
-  }
-  if (i < FMM_NLEVELS) h->open_cursor[i] = 0;
+static void launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s) {
+  // a wavefront per cell where the systems are cut by windows (8 n / leaf_size
+  // bounds the cells a context holds), a lane per cell where they are not: a
+  // workgroup's items then follow 1024 cells in order, and so the XCDs' shares
+  const int64_t cells = std::min<int64_t>(t.cap_nodes, (int64_t)a.n + 1024);
+  const int npw = a.n_max > P2P_SHARE_FINE_N ? 64 : 1;
+  const int blocks = (int)std::min<int64_t>(1024, (cells + npw * PLAN_WAVES - 1) / (npw * PLAN_WAVES));
+  hipLaunchKernelGGL(k_p2p_plan, dim3(std::max(blocks, 1)), dim3(PLAN_WAVES * 64), 0, s, t, npw);
 }
 
 hipError_t launch_reset_lists(const DevTree &t, hipStream_t s) {
@@ -434,8 +667,10 @@ hipError_t launch_traverse_small(const DevTree &t, const BuildArgs &a, hipStream
   launch_reset_lists(t, s);
   if (a.n <= 0) return hipGetLastError();
   if (a.tm) a.tm->start(PH_WALK, s);
-  hipLaunchKernelGGL(k_walk_small, dim3(1), dim3(SMALL_THREADS), 0, s, t, a.theta * a.theta,
-                     a.eps);
+  const bool plan = a.n <= SMALL_AUTO_N;
+  hipLaunchKernelGGL(k_walk_small, dim3(1), dim3(SMALL_THREADS), 0, s, t, a.theta * a.theta, a.eps,
+                     plan);
+  if (!plan) launch_p2p_plan(t, a, s);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }
@@ -453,6 +688,7 @@ hipError_t launch_traverse(const DevTree &t, const BuildArgs &a, hipStream_t s) 
     hipLaunchKernelGGL(k_walk_level, dim3((nw + TRAV_WAVES - 1) / TRAV_WAVES),
                        dim3(TRAV_WAVES * 64), 0, s, t, l, ps, pe, th2, a.eps);
   }
+  launch_p2p_plan(t, a, s);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }
@@ -468,6 +704,7 @@ hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels,
   for (int l = 0; l <= levels && l <= FMM_MAXLEVEL; ++l)
     hipLaunchKernelGGL(k_walk_level_dev, dim3(blocks), dim3(TRAV_WAVES * 64), 0, s, t, l, th2,
                        a.eps);
+  launch_p2p_plan(t, a, s);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }

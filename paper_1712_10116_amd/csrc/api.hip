@@ -64,7 +64,7 @@ static bool alloc_nodes(fmm_ctx *c, int64_t cap) {
             dalloc(c, &t.m2l_cnt, cap) && dalloc(c, &t.p2p_off, cap) &&
             dalloc(c, &t.p2p_cnt, cap) && dalloc(c, &t.open_off, cap) &&
             dalloc(c, &t.open_cnt, cap) && dalloc(c, &t.nreq, cap) &&
-            dalloc(c, &t.nshare, cap) && dalloc(c, &t.part_off, cap);
+            dalloc(c, &t.ninfo, cap) && dalloc(c, &t.nshare, cap) && dalloc(c, &t.part_off, cap);
   if (!ok) return false;
   char *m = nullptr, *l = nullptr, *mh = nullptr;
   ok = dalloc(c, &m, (int64_t)(cap * t.kmax * real)) && dalloc(c, &l, (int64_t)(cap * t.kmax * real)) &&
@@ -79,7 +79,7 @@ static void free_nodes(fmm_ctx *c) {
   DevTree &t = c->t;
   void *ptrs[] = {t.nbeg, t.nend, t.nlev, t.nparent, t.nchild0, t.nnchild, t.ngeo, t.bounds,
                   t.m2l_off, t.m2l_cnt, t.p2p_off, t.p2p_cnt, t.open_off, t.open_cnt, t.M, t.L,
-                  t.Mh, t.nreq, t.nshare, t.part_off};
+                  t.Mh, t.nreq, t.ninfo, t.nshare, t.part_off};
   for (void *p : ptrs) dfree(c, p);
 }
 
@@ -444,13 +444,12 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   // readback; anything that needs more room falls through to the general path
   if (n_all <= c->small_max) {
     HIPCHK(c, launch_build_small(c->t, a, c->stream));
-    HIPCHK(c, launch_traverse_small(c->t, a, c->stream));
+    HIPCHK(c, launch_traverse_paths(c->t, a, WALK_PATH_SMALL_GRID, c->stream));
     st = read_header(c);
     if (st != FMM_OK) return st;
     if (c->hh.nonfinite) return fail(c, FMM_ENONFINITE, "non-finite input position");
     if (c->hh.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
-    if (!(c->hh.overflow & (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS)))
-      return finish(tree_depth());
+    if (!(c->hh.overflow & OVF_ANY)) return finish(tree_depth());
   }
   // 1a. split levels predicted from recent builds: tree and walk queued behind
   // the sort, one readback.  The tree equals the one built below whenever the
@@ -482,7 +481,12 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, launch_upward(c->t, u, c->side));
       HIPCHK(c, hipEventRecord(c->up_done, c->side));
     }
-    HIPCHK(c, launch_traverse_dev(c->t, a, pred, c->stream));
+    // split cells of the last tree
+    const int groups = prev_nodes - c->hh.n_leaves;
+    if (prev_nodes > 0 && groups <= WALK_PATH_GROUPS)
+      HIPCHK(c, launch_traverse_paths(c->t, a, prev_nodes + prev_nodes / 4, c->stream));
+    else
+      HIPCHK(c, launch_traverse_dev(c->t, a, pred, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->pin_hdr, c->t.hdr, sizeof(Header), hipMemcpyDeviceToHost,
                              c->stream));
     HIPCHK(c, hipEventRecord(c->hdr_ev, c->stream));
@@ -564,8 +568,12 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   // node count and level bounds from the header and do nothing if a list
   // buffer overflowed; then the lists are regrown, the walk is redone and
   // *evaluated stays false (the caller evaluates again).
+  bool paths = lvl[FMM_NLEVELS] - c->hh.n_leaves <= WALK_PATH_GROUPS;
   for (int attempt = 0; attempt < 10; ++attempt) {
-    HIPCHK(c, launch_traverse(c->t, a, c->stream));
+    if (paths)
+      HIPCHK(c, launch_traverse_paths(c->t, a, lvl[FMM_NLEVELS], c->stream));
+    else
+      HIPCHK(c, launch_traverse(c->t, a, c->stream));
     bool queued = false;
     if (up && evaluated && attempt == 0) {
       // the header copy goes behind the walk, the evaluation behind it; the
@@ -592,7 +600,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     }
     const Header &h = c->hh;
     if (h.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
-    if (h.overflow & (OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS)) {
+    if (h.overflow & (OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS | OVF_PATH)) {
+      if (h.overflow & OVF_PATH) paths = false;
       if (h.overflow & OVF_M2L) {
         st = regrow_lists(c, OVF_M2L, h.m2l_cursor);
         if (st != FMM_OK) return st;

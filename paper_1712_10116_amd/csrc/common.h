@@ -43,8 +43,10 @@
 #define OVF_DEPTH 32
 // the P2P work items, or the partial sums of split leaves, did not fit
 #define OVF_ITEMS 64
-#define OVF_ANY \
-  (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH | OVF_ITEMS)
+// an open list outgrew the walk's path form (the host walks by levels)
+#define OVF_PATH 128
+#define OVF_ANY                                                                            \
+  (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH | OVF_ITEMS | OVF_PATH)
 
 struct Header {
   int32_t lvl_start[FMM_NLEVELS + 2];  // nodes of level l: [lvl_start[l], lvl_start[l+1])
@@ -115,6 +117,8 @@ struct DevTree {
   // nodes
   int32_t *nbeg, *nend, *nlev, *nparent, *nchild0, *nnchild;
   double4 *ngeo;
+  int4 *ninfo;  // first child (-1: leaf), child count, begin, end: what the walk
+                // reads of a candidate beside its geometry, in one load
   int32_t *bounds;  // [cap_nodes][8]
   void *M, *L;      // [cap_nodes][Kmax] of float or double
   void *Mh;         // [cap_nodes][KHmax]: moments folded onto z-degree <= 1 (harmonic far field)
@@ -283,8 +287,14 @@ hipError_t launch_build_tree_direct(const DevTree &t, const BuildArgs &a, int wa
 hipError_t launch_traverse(const DevTree &t, const BuildArgs &a, hipStream_t s);
 // levels 0..levels, level bounds read on the device (tree sizes not yet known)
 hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels, hipStream_t s);
-// all walk levels in one workgroup, level sizes read on the device
-hipError_t launch_traverse_small(const DevTree &t, const BuildArgs &a, hipStream_t s);
+// Trees of at most this many split cells are walked in the path form: at 1,590
+// it took 175 us against some 280 by levels, at 2,769 (2^20 sphere) a
+// workgroup per group takes longer than the wavefront form's 168.
+#define WALK_PATH_GROUPS 1600
+#define WALK_PATH_SMALL_GRID 512  // workgroups for a tree of unknown, small size
+// the whole walk in one launch (trees of few split cells), sizes read on the
+// device; flags OVF_PATH when an open list is too long for it
+hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, hipStream_t s);
 hipError_t launch_reset_lists(const DevTree &t, hipStream_t s);
 // eval.hip
 struct EvalArgs {

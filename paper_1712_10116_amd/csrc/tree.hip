@@ -742,7 +742,7 @@ __global__ __launch_bounds__(TD_THREADS) void k_tree_levels(DevTree t, int n, in
 // level, each block's exclusive offset among the level's cells, tot the
 // level totals.  A split cell's child count is written first as the end of
 // its children (by the particle that ends the cell) and turned into a count
-// by k_tree_nchild.
+// by k_node_info.
 __global__ __launch_bounds__(TD_THREADS) void k_tree_nodes(DevTree t, int n, int nblk,
                                                            const uint32_t *hist,
                                                            const uint32_t *tot, int walk_levels) {
@@ -838,12 +838,18 @@ __global__ __launch_bounds__(TD_THREADS) void k_tree_nodes(DevTree t, int n, int
   }
 }
 
-// split cells: child count = end of the children - first child
-__global__ __launch_bounds__(FMM_BLOCK) void k_tree_nchild(DevTree t) {
+// Walk record of every cell; turn_counts: nnchild of a split cell still holds
+// the end of its children (k_tree_nodes) and becomes a count first.
+__global__ __launch_bounds__(FMM_BLOCK) void k_node_info(DevTree t, bool turn_counts) {
   const int total = min(t.hdr->lvl_start[FMM_NLEVELS + 1], (int)t.cap_nodes);
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < total; k += gridDim.x * blockDim.x) {
     const int c0 = t.nchild0[k];
-    if (c0 >= 0) t.nnchild[k] -= c0;
+    int nc = t.nnchild[k];
+    if (turn_counts && c0 >= 0) {
+      nc -= c0;
+      t.nnchild[k] = nc;
+    }
+    t.ninfo[k] = make_int4(c0, nc, t.nbeg[k], t.nend[k]);
   }
 }
 
@@ -1056,6 +1062,8 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_build_small(DevTree t, int n,
   int total;
   block_excl_scan_small(leaves, wsum, &total);
   if (tid == 0 && total) atomicAdd((int *)&h->n_leaves, total);
+  for (int k2 = tid; k2 < min(run, (int)t.cap_nodes); k2 += T)
+    t.ninfo[k2] = make_int4(t.nchild0[k2], t.nnchild[k2], t.nbeg[k2], t.nend[k2]);
 }
 
 hipError_t launch_build_small(const DevTree &t, const BuildArgs &a, hipStream_t s) {
@@ -1142,8 +1150,8 @@ hipError_t launch_build_tree_direct(const DevTree &t, const BuildArgs &a, int wa
                        nblk, t.sort_dtot);
     hipLaunchKernelGGL(k_tree_nodes, dim3(nblk), dim3(TD_THREADS), 0, s, t, n, nblk, t.sort_hist,
                        t.sort_dtot, walk_levels);
-    hipLaunchKernelGGL(k_tree_nchild, dim3(std::min(1024, std::max(1, n / 256))), dim3(FMM_BLOCK),
-                       0, s, t);
+    hipLaunchKernelGGL(k_node_info, dim3(std::min(1024, std::max(1, n / 256))), dim3(FMM_BLOCK), 0,
+                       s, t, true);
   }
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
@@ -1160,6 +1168,8 @@ hipError_t launch_build_tree(const DevTree &t, const BuildArgs &a, int max_level
       hipLaunchKernelGGL(k_tree_emit, dim3(FMM_SCAN_BLOCKS), dim3(FMM_BLOCK), 0, s, t, l,
                          a.leaf_size);
     }
+    hipLaunchKernelGGL(k_node_info, dim3(std::min(1024, std::max(1, n / 256))), dim3(FMM_BLOCK), 0,
+                       s, t, false);
   }
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();

@@ -274,9 +274,8 @@ fmm_status fmm_forces_batched(fmm_ctx *ctx, int n_req, const fmm_request *reqs, 
 fmm_status fmm_tree_info(fmm_ctx *ctx, int64_t info[9]);
 
 /* Builds of few active particles (all systems of a batch together) run as
- * two single-workgroup launches with one readback: enable = 1 (the default)
- * up to 1024 particles, beyond which the multi-workgroup path is faster;
- * enable = 2 up to 8192, the most those launches hold; enable = 0 never.
+ * a single-workgroup launch and a walk with one readback up to 1024 particles,
+ * the most that launch holds: enable = 1 (the default) or 2; enable = 0 never.
  * Trees, lists and results are the same either way (for comparison and
  * tests).  Other values: FMM_EINVAL. */
 fmm_status fmm_set_small_path(fmm_ctx *ctx, int enable);

@@ -101,7 +101,7 @@ static bool alloc_reqs(fmm_ctx *c, int cap) {
   const size_t bytes = req_region_bytes(cap);
   char *region = nullptr;
   if (!dalloc(c, &region, (int64_t)bytes) || !dalloc(c, &t.box, cap) ||
-      !dalloc(c, &t.bbox_part, (int64_t)cap * FMM_BBOX_BLOCKS * 6))
+      !dalloc(c, &t.bbox_part, (int64_t)cap * FMM_BBOX_BLOCKS * FMM_BBOX_COLS))
     return false;
   t.reqs = (DevReq *)region;
   t.req_off = (int32_t *)(region + sizeof(DevReq) * (size_t)cap);
@@ -129,7 +129,7 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
   if (!c) return FMM_ENOMEM;
   c->prm = *prm;
   c->max_n = max_n;
-  c->small_max = SMALL_AUTO_N;
+  c->small_max = SMALL_N;
   c->predict_levels = false;
   c->lvl_hist_n = 0;
   c->stream = (hipStream_t)stream;
@@ -156,12 +156,10 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
   t.cap_n = max_n;
   int64_t n = max_n;
   int64_t cap_nodes = 8 * n / prm->leaf_size + 1024;
-  // radix histograms: one column per tile, and for sorts of at most
-  // SORT_RAW_TILES tiles one slice per pass
+  // radix histograms: one column per tile; also the cells per level and block
+  // of the tree build
   const int64_t sort_tiles = (n + SORT_TILE - 1) / SORT_TILE;
-  const int64_t sort_hist_n =
-      256 * std::max<int64_t>(sort_tiles, SORT_MAX_PASSES * std::min<int64_t>(sort_tiles, SORT_RAW_TILES)) +
-      256;
+  const int64_t sort_hist_n = std::max<int64_t>(256 * sort_tiles, FMM_MAXLEVEL * ((n + 1023) / 1024)) + 256;
   bool ok = dalloc(c, &t.key, n) && dalloc(c, &t.key2, n) && dalloc(c, &t.slot, n) &&
             dalloc(c, &t.slot2, n) && dalloc(c, &t.sx, n) && dalloc(c, &t.sy, n) &&
             dalloc(c, &t.sz, n) && dalloc(c, &t.sm, n) && dalloc(c, &t.sm32, n) &&
@@ -229,7 +227,7 @@ extern "C" const char *fmm_last_error(const fmm_ctx *c) { return c ? c->err : "n
 
 extern "C" fmm_status fmm_set_small_path(fmm_ctx *c, int enable) {
   if (!c || enable < 0 || enable > 2) return FMM_EINVAL;
-  c->small_max = enable == 0 ? -1 : enable == 1 ? SMALL_AUTO_N : SMALL_N;
+  c->small_max = enable == 0 ? -1 : SMALL_N;
   return FMM_OK;
 }
 
@@ -442,7 +440,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   };
   // 0. small batches: build and walk in two single-workgroup launches and one
   // readback; anything that needs more room falls through to the general path
-  if (n_all <= c->small_max) {
+  if (n_all <= c->small_max && build_tree_direct_ok(a.leaf_size)) {
     HIPCHK(c, launch_build_small(c->t, a, c->stream));
     HIPCHK(c, launch_traverse_paths(c->t, a, WALK_PATH_SMALL_GRID, c->stream));
     st = read_header(c);

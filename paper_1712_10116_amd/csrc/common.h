@@ -21,15 +21,10 @@
 #define FMM_BLOCK 256
 #define FMM_SCAN_BLOCKS 256
 #define FMM_BBOX_BLOCKS 256  // box-reduction blocks per request, at most
+#define FMM_BBOX_COLS 7      // lower, upper corner, non-finite flag of a block
 #define SORT_TILE 4096       // keys per radix-sort tile (one histogram column)
-#define SORT_RAW_TILES 16    // sorts of at most this many tiles run without digit-scan launches
-#define SORT_MAX_PASSES 12   // 8 key digits + at most 4 request digits
-// single-workgroup ("small") build, walk and level passes
-#define SMALL_WAVES 8
-#define SMALL_THREADS (SMALL_WAVES * 64)
-#define SMALL_N (SMALL_THREADS * 16)  // active particles of a batch, at most
-#define SMALL_AUTO_N 1024             // the small path's default reach (beyond it the
-                                      // multi-workgroup path is faster)
+// single-workgroup ("small") build and level passes
+#define SMALL_N 1024                  // active particles of a batch built in one workgroup
 #define SMALL_NODES 2048              // cells of a tree whose M2M / L2L levels run in one workgroup
 
 // error bits latched in Header::overflow

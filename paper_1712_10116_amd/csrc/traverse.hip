@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(WALK_WAVES * 64, 4) void k_walk_level(DevTree t, in
 #define P2P_SHARE_MAX_LEAF 4096  // larger leaves (coincident particles) are cut by sinks only
 #define P2P_SHARE_FINE_N 524288  // largest system cut by windows
 __device__ __forceinline__ int p2p_share_windows(int n) {
-  if (n <= SMALL_AUTO_N || n > P2P_SHARE_FINE_N) return 0;
+  if (n <= SMALL_N || n > P2P_SHARE_FINE_N) return 0;
   return n <= 32768 ? 1 : n <= 131072 ? 2 : 4;
 }
 

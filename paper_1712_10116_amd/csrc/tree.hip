@@ -6,8 +6,10 @@
 //      scale s = 2^21/L;
 //   2. 63-bit Morton keys from q_d = clamp(floor((x_d - o_d) s), 0, 2^21-1),
 //      x bits at 3b+2, y at 3b+1, z at 3b;
-//   3. stable LSD radix sort of (key, active slot), 8 passes of 8 bits; ranks
-//      inside a wavefront come from 8 ballots per 64 keys;
+//   3. stable sort of (key, active slot): tiles sorted in LDS and merged by
+//      rank, or for systems of more than MSORT_MAX_N particles an LSD radix
+//      sort, 8 passes of 8 bits, ranks inside a wavefront from 8 ballots per 64
+//      keys;
 //   4. top-down split (the paper's recursive build, Sec. 2.3, done level by
 //      level): a cell of level l < 21 holding more than leaf_size particles
 //      gets one child per non-empty octant of its key range; children of a
@@ -25,20 +27,15 @@
 #define SORT_WAVES 16                          // wavefronts per radix tile
 #define SORT_ITEMS (SORT_TILE / (SORT_WAVES * 64))
 #define SORT_THREADS (SORT_WAVES * 64)
-#define SMALL_ITEMS 16
+#define BBOX_COLS FMM_BBOX_COLS
 
 // ---------------------------------------------------------------------------
 // request of every slot (binary search in the request offsets)
 // ---------------------------------------------------------------------------
 
-// request of every active slot; also clears the header counters that the
-// following kernels accumulate into (non-finite flag, leaf count)
+// request of every active slot, for the request passes of the radix sort
 __global__ __launch_bounds__(FMM_BLOCK) void k_slot_req(DevTree t, int n) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s == 0) {
-    t.hdr->nonfinite = 0;
-    t.hdr->n_leaves = 0;
-  }
   if (s < n) t.slot_req[s] = upper_index(t.req_off, t.n_req, s);
 }
 
@@ -67,7 +64,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_bbox_partial(DevTree t) {
     red[d][threadIdx.x] = lo[d];
     red[3 + d][threadIdx.x] = hi[d];
   }
-  if (__syncthreads_or(bad) && threadIdx.x == 0) atomicOr(&t.hdr->nonfinite, 1);
+  bad = __syncthreads_or(bad);
   for (int o = FMM_BLOCK / 2; o > 0; o >>= 1) {
     if (threadIdx.x < o) {
 #pragma unroll
@@ -78,7 +75,9 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_bbox_partial(DevTree t) {
     }
     __syncthreads();
   }
-  if (threadIdx.x < 6) t.bbox_part[blockIdx.x * 6 + threadIdx.x] = red[threadIdx.x][0];
+  if (threadIdx.x < 7)
+    t.bbox_part[blockIdx.x * BBOX_COLS + threadIdx.x] =
+        threadIdx.x < 6 ? red[threadIdx.x][0] : (bad ? 1.0 : 0.0);
 }
 
 // c = (lo+hi)/2, L = max extent (1 if 0), o = c - L/2, s = 2^21/L
@@ -99,29 +98,6 @@ __device__ __forceinline__ void finish_box(Box &bx, double lo[3], double hi[3], 
   }
   bx.L = L;
   bx.s = 2097152.0 / L;
-}
-
-// one wavefront per request
-__global__ __launch_bounds__(FMM_BLOCK) void k_bbox_final(DevTree t) {
-  const int r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (r >= t.n_req) return;
-  const int b0 = t.blk_off[r], b1 = t.blk_off[r + 1];
-  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int b = b0 + lane; b < b1; b += 64)
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = fmin(lo[d], t.bbox_part[b * 6 + d]);
-      hi[d] = fmax(hi[d], t.bbox_part[b * 6 + 3 + d]);
-    }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      lo[d] = fmin(lo[d], __shfl_xor(lo[d], off, 64));
-      hi[d] = fmax(hi[d], __shfl_xor(hi[d], off, 64));
-    }
-  if (lane != 0) return;
-  finish_box(t.box[r], lo, hi, t.reqs[r].n == 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -155,8 +131,8 @@ __device__ __forceinline__ uint64_t quantise(double x, double o, double s) {
   return (uint64_t)q;
 }
 
-__device__ __forceinline__ void make_key(const DevTree &t, int s, uint64_t *key, int32_t *slot) {
-  const int r = t.slot_req[s];
+// key and packed position of active slot s, of request r
+__device__ __forceinline__ uint64_t make_key(const DevTree &t, int s, int r, double4 &pos) {
   const DevReq q = t.reqs[r];
   const int i = s - q.off;
   int64_t g = q.active ? q.active[i] : i;
@@ -165,16 +141,20 @@ __device__ __forceinline__ void make_key(const DevTree &t, int s, uint64_t *key,
   uint64_t qx = quantise(x, bx.o[0], bx.s);
   uint64_t qy = quantise(y, bx.o[1], bx.s);
   uint64_t qz = quantise(z, bx.o[2], bx.s);
-  key[s] = (spread3(qx) << 2) | (spread3(qy) << 1) | spread3(qz);
-  slot[s] = s;
-  t.pak[s] = make_double4(x, y, z, 0.0);
+  pos = make_double4(x, y, z, 0.0);
+  t.pak[s] = pos;
+  return (spread3(qx) << 2) | (spread3(qy) << 1) | spread3(qz);
 }
 
 // keys and slots into key2 / slot2 when the sort that follows makes an odd
 // number of passes (so that its result lands in key / slot)
 __global__ __launch_bounds__(FMM_BLOCK) void k_keys(DevTree t, int n, int odd) {
   int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < n) make_key(t, s, odd ? t.key2 : t.key, odd ? t.slot2 : t.slot);
+  if (s >= n) return;
+  const int r = t.n_req > 1 ? t.slot_req[s] : 0;
+  double4 pos;
+  (odd ? t.key2 : t.key)[s] = make_key(t, s, r, pos);
+  (odd ? t.slot2 : t.slot)[s] = s;
 }
 
 // ---------------------------------------------------------------------------
@@ -190,14 +170,11 @@ __device__ __forceinline__ uint32_t sort_digit(const uint64_t *key, const int32_
                 : (uint32_t)(key[i] >> shift) & 255u;
 }
 
-// clear_slices > 0: also clears this tile's column of the clear_slices
-// histograms that follow hist (one per later raw pass, 256 * nblk apart)
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(const uint64_t *__restrict__ key,
                                                             const int32_t *__restrict__ slot,
                                                             const int32_t *__restrict__ slot_req,
                                                             int n, int shift, int by_req,
-                                                            uint32_t *__restrict__ hist,
-                                                            int nblk, int clear_slices) {
+                                                            uint32_t *__restrict__ hist, int nblk) {
   __shared__ uint32_t h[256];
   if (threadIdx.x < 256) h[threadIdx.x] = 0;
   __syncthreads();
@@ -208,11 +185,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(const uint64_t *__re
     if (i < n) atomicAdd(&h[sort_digit(key, slot, slot_req, i, shift, by_req)], 1u);
   }
   __syncthreads();
-  if (threadIdx.x < 256) {
-    hist[threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
-    for (int p = 1; p <= clear_slices; ++p)
-      hist[(size_t)p * 256 * nblk + threadIdx.x * nblk + blockIdx.x] = 0u;
-  }
+  if (threadIdx.x < 256) hist[threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
 }
 
 // Per-digit exclusive scan over the blocks: hist[d][0..nblk) in place, digit
@@ -262,24 +235,16 @@ __device__ __forceinline__ uint32_t scan256(uint32_t v, uint32_t *wsum) {
 // the pass is stable), the tile reordered by digit in LDS, then written out
 // in tile order so that consecutive threads store consecutive addresses of a
 // digit's run.
-// raw = 1 (at most SORT_RAW_TILES tiles): hist holds the tiles' raw digit
-// counts and each tile sums what it needs itself (no digit-scan launch);
-// raw = 0: hist holds each digit's exclusive prefix over the tiles and dtot
-// the digit totals.
-// hist_next (raw passes but the last, else NULL): the next pass's raw counts,
-// zero on entry, are accumulated here (digit next_shift / next_by_req of each
-// element, by the tile of its destination), so that pass needs no histogram
-// launch of its own; counts do not depend on the order they are added in.
+// hist holds each digit's exclusive prefix over the tiles and dtot the digit
+// totals.
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
     const uint64_t *__restrict__ kin, const int32_t *__restrict__ sin, uint64_t *__restrict__ kout,
     int32_t *__restrict__ sout, const int32_t *__restrict__ slot_req, int n, int shift, int by_req,
-    const uint32_t *__restrict__ hist, int nblk, const uint32_t *__restrict__ dtot, int raw,
-    uint32_t *__restrict__ hist_next, int next_shift, int next_by_req) {
+    const uint32_t *__restrict__ hist, int nblk, const uint32_t *__restrict__ dtot) {
   // keys | slots | digits of the reordered tile; the per-wave digit counters
   // of the ranking step live in the front of the same space before that
   __shared__ __align__(16) unsigned char smem[SORT_TILE * 13];
   __shared__ uint32_t lstart[256], gbase[256], wsum[SORT_WAVES];
-  __shared__ uint32_t lnext[256 * SORT_RAW_TILES];  // next pass's counts, [digit][tile]
   uint64_t *skey = (uint64_t *)smem;
   int32_t *sslot = (int32_t *)(smem + 8 * SORT_TILE);
   uint8_t *sdig = smem + 12 * SORT_TILE;
@@ -290,16 +255,8 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
   // counts of the earlier tiles
   uint32_t dtotal = 0, tprefix = 0;
   if (tid < 256) {
-    if (raw) {
-      for (int b = 0; b < nblk; ++b) {
-        const uint32_t c = hist[tid * nblk + b];
-        dtotal += c;
-        tprefix += b < (int)blockIdx.x ? c : 0u;
-      }
-    } else {
-      dtotal = dtot[tid];
-      tprefix = hist[tid * nblk + blockIdx.x];
-    }
+    dtotal = dtot[tid];
+    tprefix = hist[tid * nblk + blockIdx.x];
   }
   const uint32_t dbase = scan256(dtotal, wsum);
   const int tile = blockIdx.x * SORT_TILE;
@@ -365,10 +322,6 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
   }
   __syncthreads();
   const int tn = min(SORT_TILE, n - tile);
-  const bool count_next = hist_next != nullptr && nblk <= SORT_RAW_TILES;
-  if (count_next)
-    for (int d = tid; d < 256 * nblk; d += SORT_THREADS) lnext[d] = 0;
-  __syncthreads();
 #pragma unroll
   for (int it = 0; it < SORT_ITEMS; ++it) {
     const int j = it * SORT_THREADS + tid;
@@ -376,17 +329,188 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
       const uint32_t dst = gbase[sdig[j]] + (uint32_t)j;
       kout[dst] = skey[j];
       sout[dst] = sslot[j];
-      if (count_next) {
-        const uint32_t d = next_by_req ? ((uint32_t)slot_req[sslot[j]] >> next_shift) & 255u
-                                       : (uint32_t)(skey[j] >> next_shift) & 255u;
-        atomicAdd(&lnext[d * nblk + dst / SORT_TILE], 1u);
-      }
     }
   }
-  if (count_next) {
-    __syncthreads();
-    for (int d = tid; d < 256 * nblk; d += SORT_THREADS)
-      if (lnext[d]) atomicAdd(&hist_next[d], lnext[d]);
+}
+
+// ---------------------------------------------------------------------------
+// Merge sort, for batches whose largest system has at most MSORT_MAX_N
+// particles: tiles of 1024 slots sorted in LDS (the kernel that makes the
+// keys), then 16 runs at a time merged by rank.  An element's place in the
+// merged run is its place in its own run plus, for each other run, the number
+// of keys before it there, a binary search; the searches of 8 runs go on side
+// by side, so a merge costs some 20 dependent reads whatever its size.  The 8
+// radix passes cost 9 us each in launches and latency below 65,536 particles,
+// and 17 with their histogram and digit-scan launches above.  Sorts, in all:
+// 12,526 particles 34 us (radix 73 + 6 in 10 launches), 100,003 53 (140
+// in 25), 300,007 128 (149); at 2^20 the searches read more than the passes
+// (radix 171 us).
+//
+// Several systems: their slots are contiguous, and so are their sorted
+// positions, in every run: position q belongs to the same system before and
+// after, and an element is ranked among its own system's part of a run only.
+// A system's runs are counted from the tile its first slot is in.  Equal keys
+// keep slot order: runs before its own count keys up to and including an
+// element's, runs after it keys below.
+// ---------------------------------------------------------------------------
+#define MSORT_TILE 1024
+#define MSORT_FAN 16
+#define MSORT_MAX_N 524288
+
+// Sorted LDS runs of RUN elements merged four at a time: the element at
+// position p of kin (its system's slots lie in [s0, s1) of the tile) moves to
+// its place in kout.
+template <int RUN>
+__device__ __forceinline__ void lds_merge4(const uint64_t *kin, const uint16_t *iin, uint64_t *kout,
+                                           uint16_t *iout, int p, bool valid, int s0, int s1) {
+  if (!valid) return;
+  const uint64_t k = kin[p];
+  const int g0 = p & ~(4 * RUN - 1), m = (p / RUN) & 3;
+  int at = max(s0, g0) + p - max(s0, g0 + m * RUN);
+  int lo[3], hi[3];
+#pragma unroll
+  for (int u = 0; u < 3; ++u) {
+    const int j = u + (u >= m ? 1 : 0);
+    lo[u] = max(s0, g0 + j * RUN);
+    hi[u] = max(lo[u], min(s1, g0 + j * RUN + RUN));
+    at -= lo[u];
+  }
+  // RUN + 1 possible places: this many halvings always end the search
+#pragma unroll
+  for (int st = RUN; st > 0; st >>= 1)
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int mid = (lo[u] + hi[u]) >> 1;
+      const uint64_t x = kin[min(mid, MSORT_TILE - 1)];
+      const bool right = lo[u] < hi[u] && (x < k || (u < m && x == k));
+      const bool left = lo[u] < hi[u] && !right;
+      lo[u] = right ? mid + 1 : lo[u];
+      hi[u] = left ? mid : hi[u];
+    }
+#pragma unroll
+  for (int u = 0; u < 3; ++u) at += lo[u];
+  kout[at] = k;
+  iout[at] = iin[p];
+}
+
+struct TileLds {
+  uint64_t ka[MSORT_TILE], kb[MSORT_TILE];
+  uint16_t ia[MSORT_TILE], ib[MSORT_TILE];
+  double x[MSORT_TILE], y[MSORT_TILE], z[MSORT_TILE];
+};
+
+// Keys of the slots of one tile, sorted to kout / sout; last: also the sorted
+// positions.  A workgroup of MSORT_TILE threads.
+__device__ __forceinline__ void sort_tile(const DevTree &t, int n, int tile, uint64_t *kout,
+                                          int32_t *sout, bool last, TileLds &L) {
+  const int p = threadIdx.x, q = tile * MSORT_TILE + p;
+  const bool valid = q < n;
+  int s0 = 0, s1 = 0;  // the system's slots, within the tile
+  uint64_t key = 0;
+  if (valid) {
+    const int r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, q) : 0;
+    s0 = max(t.req_off[r] - tile * MSORT_TILE, 0);
+    s1 = min(t.req_off[r + 1] - tile * MSORT_TILE, MSORT_TILE);
+    double4 pos;
+    key = make_key(t, q, r, pos);
+    L.x[p] = pos.x;
+    L.y[p] = pos.y;
+    L.z[p] = pos.z;
+  }
+  L.ka[p] = key;
+  __builtin_amdgcn_wave_barrier();
+  // runs of 64: rank by counting
+  const int w0 = p & ~63;
+  {
+    const int a = max(s0, w0), b = min(s1, w0 + 64);
+    int at = a;
+#pragma unroll 16
+    for (int j = 0; j < 64; ++j) {
+      const uint64_t x = L.ka[w0 + j];
+      at += (w0 + j >= a && w0 + j < b && (x < key || (x == key && w0 + j < p))) ? 1 : 0;
+    }
+    if (valid) {
+      L.kb[at] = key;
+      L.ib[at] = (uint16_t)p;
+    }
+  }
+  __syncthreads();
+  lds_merge4<64>(L.kb, L.ib, L.ka, L.ia, p, valid, s0, s1);
+  __syncthreads();
+  lds_merge4<256>(L.ka, L.ia, L.kb, L.ib, p, valid, s0, s1);
+  __syncthreads();
+  if (valid) {
+    const int i = L.ib[p];
+    kout[q] = L.kb[p];
+    sout[q] = tile * MSORT_TILE + i;
+    if (last) {
+      t.sx[q] = L.x[i];
+      t.sy[q] = L.y[i];
+      t.sz[q] = L.z[i];
+    }
+  }
+}
+
+__global__ __launch_bounds__(MSORT_TILE) void k_sort_tiles(DevTree t, int n, uint64_t *kout,
+                                                           int32_t *sout, bool last) {
+  __shared__ TileLds lds;
+  sort_tile(t, n, blockIdx.x, kout, sout, last, lds);
+}
+
+// Runs of R sorted elements (of every system, from the tile its first slot is
+// in) merged MSORT_FAN at a time; last: also the sorted positions.
+__global__ __launch_bounds__(FMM_BLOCK) void k_sort_merge(DevTree t, int n, int R,
+                                                          const uint64_t *__restrict__ kin,
+                                                          const int32_t *__restrict__ sin,
+                                                          uint64_t *__restrict__ kout,
+                                                          int32_t *__restrict__ sout, bool last) {
+  const int q = blockIdx.x * blockDim.x + threadIdx.x;
+  if (q >= n) return;
+  const int r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, q) : 0;
+  const int off0 = t.req_off[r], off1 = t.req_off[r + 1];
+  const uint64_t k = kin[q];
+  const int slot = sin[q];
+  double4 pos;
+  if (last) pos = t.pak[slot];
+  const int o = off0 & ~(MSORT_TILE - 1);
+  const int run = (q - o) / R, m = run & (MSORT_FAN - 1);
+  const int64_t g0 = o + (int64_t)(run - m) * R;  // first slot of the runs merged here
+  unsigned at = (unsigned)max((int64_t)off0, g0) + q -
+                (unsigned)max((int64_t)off0, g0 + (int64_t)m * R);
+  for (int h = 0; h < MSORT_FAN; h += 8) {
+    if (h > 0 && g0 + (int64_t)h * R >= off1) break;
+    int lo[8], hi[8], len = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int64_t a = g0 + (int64_t)(h + u) * R;
+      lo[u] = (int)min((int64_t)off1, max((int64_t)off0, a));
+      hi[u] = h + u == m ? lo[u] : (int)max((int64_t)lo[u], min((int64_t)off1, a + R));
+      at -= (unsigned)lo[u];
+      len = max(len, hi[u] - lo[u]);
+    }
+    for (; len > 0; len >>= 1) {  // len + 1 places: bit length of len halvings
+      uint64_t x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = kin[min((lo[u] + hi[u]) >> 1, n - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int mid = (lo[u] + hi[u]) >> 1;
+        const bool right = x[u] < k || (h + u < m && x[u] == k);
+        if (lo[u] < hi[u]) {
+          lo[u] = right ? mid + 1 : lo[u];
+          hi[u] = right ? hi[u] : mid;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) at += (unsigned)lo[u];
+  }
+  kout[at] = k;
+  sout[at] = slot;
+  if (last) {
+    t.sx[at] = pos.x;
+    t.sy[at] = pos.y;
+    t.sz[at] = pos.z;
   }
 }
 
@@ -460,6 +584,7 @@ __device__ __forceinline__ void header_init(const DevTree &t) {
   for (int l = 1; l < FMM_NLEVELS + 2; ++l) h->lvl_start[l] = R;
   h->overflow = R > t.cap_nodes ? OVF_NODES : 0;
   h->max_prefix = 0;
+  h->n_leaves = 0;
 }
 
 __device__ __forceinline__ void root_init(const DevTree &t, int r, int leaf_size) {
@@ -475,10 +600,60 @@ __device__ __forceinline__ void root_init(const DevTree &t, int r, int leaf_size
   if (t.req_off[r + 1] - t.req_off[r] <= leaf_size) atomicAdd((int *)&t.hdr->n_leaves, 1);
 }
 
-__global__ __launch_bounds__(FMM_BLOCK) void k_tree_init(DevTree t, int leaf_size) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r == 0) header_init(t);
-  if (r < t.n_req) root_init(t, r, leaf_size);
+// Box of request r from its blocks' partial boxes, by one wavefront; returns
+// whether a position was not finite.
+__device__ __forceinline__ bool box_of_request(const DevTree &t, int r) {
+  const int lane = threadIdx.x & 63;
+  const int b0 = t.blk_off[r], b1 = t.blk_off[r + 1];
+  double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+  bool bad = false;
+  for (int b = b0 + lane; b < b1; b += 64) {
+    const double *part = t.bbox_part + (int64_t)b * BBOX_COLS;
+    for (int d = 0; d < 3; ++d) {
+      lo[d] = fmin(lo[d], part[d]);
+      hi[d] = fmax(hi[d], part[3 + d]);
+    }
+    bad |= part[6] != 0.0;
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      lo[d] = fmin(lo[d], __shfl_xor(lo[d], off, 64));
+      hi[d] = fmax(hi[d], __shfl_xor(hi[d], off, 64));
+    }
+  if (lane == 0) finish_box(t.box[r], lo, hi, t.reqs[r].n == 0);
+  return __ballot(bad) != 0ull;
+}
+
+// Boxes, header and roots of a batch of few requests, by one workgroup (a
+// wavefront per request); batches of more take k_header_init and k_boxes.
+#define INIT_WAVES 16
+__global__ __launch_bounds__(INIT_WAVES * 64) void k_init(DevTree t, int leaf_size) {
+  bool bad = false;
+  for (int r = threadIdx.x >> 6; r < t.n_req; r += INIT_WAVES) bad |= box_of_request(t, r);
+  const int any = __syncthreads_or(bad);
+  if (threadIdx.x == 0) {
+    header_init(t);
+    t.hdr->nonfinite = any ? 1 : 0;
+  }
+  __syncthreads();
+  for (int r = threadIdx.x; r < t.n_req; r += INIT_WAVES * 64) root_init(t, r, leaf_size);
+}
+
+__global__ void k_header_init(DevTree t) {
+  header_init(t);
+  t.hdr->nonfinite = 0;
+}
+
+__global__ __launch_bounds__(FMM_BLOCK) void k_boxes(DevTree t, int leaf_size) {
+  const int r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+  if (r >= t.n_req) return;
+  const bool bad = box_of_request(t, r);
+  if ((threadIdx.x & 63) == 0) {
+    if (bad) atomicOr(&t.hdr->nonfinite, 1);
+    root_init(t, r, leaf_size);
+  }
 }
 
 __device__ __forceinline__ int lower_bound_digit(const uint64_t *__restrict__ key, int b, int e,
@@ -682,14 +857,6 @@ __device__ __forceinline__ int common_levels(uint64_t a, uint64_t b) {
   return x == 0 ? FMM_MAXLEVEL : (__clzll(x) - 1) / 3;
 }
 
-// c(i) into slot2 (free after the sort): -1 when i + L is past the system
-__global__ __launch_bounds__(FMM_BLOCK) void k_tree_pairs(DevTree t, int n, int L) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, i) : 0;
-  t.slot2[i] = i + L < t.req_off[r + 1] ? common_levels(t.key[i], t.key[i + L]) : -1;
-}
-
 // per-particle level data, packed: d | lo << 8 | lo2 << 16 (lo: first level
 // >= 1 at which i starts a cell; lo2: first level at which i ends a run)
 __device__ __forceinline__ void td_unpack(uint64_t v, int &d, int &lo, int &lo2) {
@@ -698,26 +865,51 @@ __device__ __forceinline__ void td_unpack(uint64_t v, int &d, int &lo, int &lo2)
   lo2 = (int)((v >> 16) & 255u);
 }
 
-// d, lo, lo2 of every particle into key2, and per level l >= 1 the number of
-// cells of level l that start in each block of TD_THREADS particles into
-// hist[(l - 1) * nblk + block]
-__global__ __launch_bounds__(TD_THREADS) void k_tree_levels(DevTree t, int n, int L, int nblk,
-                                                            uint32_t *hist) {
-  __shared__ int cw[TD_THREADS + TD_MAXLEAF];  // c over [b0 - L, b0 + TD_THREADS)
-  __shared__ int wcnt[TD_WAVES][FMM_MAXLEVEL];
-  const int b0 = blockIdx.x * TD_THREADS;
-  for (int k = threadIdx.x; k < TD_THREADS + L; k += TD_THREADS) {
+struct LevelLds {
+  int cw[TD_THREADS + TD_MAXLEAF];  // c over [b0 - L, b0 + TD_THREADS), then window maxima
+  int wcnt[TD_WAVES][FMM_MAXLEVEL];
+  int wmax[TD_WAVES];
+};
+
+// Block blk of TD_THREADS sorted particles: d, lo, lo2 of each into key2, per
+// level l >= 1 the number of cells of level l that start in the block into
+// hist[(l - 1) * nblk + blk], and the split depth into the header.  The
+// maximum over a window of L + 1 values comes from two overlapping windows of
+// the largest power of two within it, formed by doubling in LDS.
+__device__ __forceinline__ void tree_levels(const DevTree &t, int n, int L, int blk, int nblk,
+                                            uint32_t *hist, LevelLds &S) {
+  const int b0 = blk * TD_THREADS, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  for (int k = tid; k < TD_THREADS + L; k += TD_THREADS) {
     const int g = b0 - L + k;
-    cw[k] = (g >= 0 && g < n) ? t.slot2[g] : -1;
+    int c = -1;
+    if (g >= 0 && g < n) {
+      const int r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, g) : 0;
+      if (g + L < t.req_off[r + 1]) c = common_levels(t.key[g], t.key[g + L]);
+    }
+    S.cw[k] = c;
   }
   __syncthreads();
-  const int i = b0 + threadIdx.x;
+  int best = S.cw[L + tid];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) best = max(best, __shfl_xor(best, off, 64));
+  if (lane == 0) S.wmax[w] = best;
+  int span = 1;
+  for (; 2 * span <= L + 1; span *= 2) {
+    const int k1 = tid + TD_THREADS;
+    const int v0 = max(S.cw[tid], S.cw[min(tid + span, TD_THREADS + L - 1)]);
+    const int v1 = k1 < TD_THREADS + L ? max(S.cw[k1], S.cw[min(k1 + span, TD_THREADS + L - 1)]) : 0;
+    __syncthreads();
+    S.cw[tid] = v0;
+    if (k1 < TD_THREADS + L) S.cw[k1] = v1;
+    __syncthreads();
+  }
+  const int i = b0 + tid;
   int lo = 1, hi = 0;
   if (i < n) {
     const int r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, i) : 0;
     const int rs = t.req_off[r], re = t.req_off[r + 1];
-    int m = -1;
-    for (int k = max(i - L, rs); k <= i; ++k) m = max(m, cw[k - b0 + L]);
+    // windows that start before the system do not fit in their own and hold -1
+    const int m = max(S.cw[tid], S.cw[tid + L + 1 - span]);
     const int d = m < 0 ? 0 : min(FMM_MAXLEVEL, m + 1);
     const int cpi = i == rs ? 0 : common_levels(t.key[i - 1], t.key[i]);
     const int lo2 = i + 1 == re ? 0 : common_levels(t.key[i], t.key[i + 1]) + 1;
@@ -725,184 +917,204 @@ __global__ __launch_bounds__(TD_THREADS) void k_tree_levels(DevTree t, int n, in
     hi = d;
     t.key2[i] = (uint64_t)d | ((uint64_t)lo << 8) | ((uint64_t)lo2 << 16);
   }
-  const int w = threadIdx.x >> 6;
   for (int l = 1; l <= FMM_MAXLEVEL; ++l) {
     const unsigned long long b = __ballot(lo <= l && l <= hi);
-    if ((threadIdx.x & 63) == 0) wcnt[w][l - 1] = __popcll(b);
+    if (lane == 0) S.wcnt[w][l - 1] = __popcll(b);
   }
   __syncthreads();
-  if (threadIdx.x < FMM_MAXLEVEL) {
+  if (tid < FMM_MAXLEVEL) {
     int s = 0;
-    for (int ww = 0; ww < TD_WAVES; ++ww) s += wcnt[ww][threadIdx.x];
-    hist[(size_t)threadIdx.x * nblk + blockIdx.x] = (uint32_t)s;
+    for (int ww = 0; ww < TD_WAVES; ++ww) s += S.wcnt[ww][tid];
+    hist[(size_t)tid * nblk + blk] = (uint32_t)s;
+  }
+  if (tid == 64) {
+    for (int ww = 0; ww < TD_WAVES; ++ww) best = max(best, S.wmax[ww]);
+    if (best > 0) atomicMax(&t.hdr->max_prefix, best);
   }
 }
 
-// The nodes of levels >= 1 and the children of the roots.  hist holds, per
-// level, each block's exclusive offset among the level's cells, tot the
-// level totals.  A split cell's child count is written first as the end of
-// its children (by the particle that ends the cell) and turned into a count
-// by k_node_info.
-__global__ __launch_bounds__(TD_THREADS) void k_tree_nodes(DevTree t, int n, int nblk,
-                                                           const uint32_t *hist,
-                                                           const uint32_t *tot, int walk_levels) {
-  __shared__ int wpre[TD_WAVES][FMM_MAXLEVEL];
-  __shared__ int lvs_s[FMM_NLEVELS + 2];
-  __shared__ int leaves_w[TD_WAVES];
-  if (threadIdx.x == 0) {
-    lvs_s[0] = 0;
-    lvs_s[1] = t.n_req;
-    for (int l = 1; l <= FMM_NLEVELS; ++l)
-      lvs_s[l + 1] = lvs_s[l] + (l <= FMM_MAXLEVEL ? (int)tot[l - 1] : 0);
+__global__ __launch_bounds__(TD_THREADS) void k_tree_levels(DevTree t, int n, int L, int nblk,
+                                                            uint32_t *hist) {
+  __shared__ LevelLds lds;
+  tree_levels(t, n, L, blockIdx.x, nblk, hist, lds);
+}
+
+struct NodeLds {
+  int wpre[TD_WAVES][FMM_MAXLEVEL];
+  int boff[FMM_MAXLEVEL], btot[FMM_MAXLEVEL];
+  int lvs[FMM_NLEVELS + 2];
+  int leaves[TD_WAVES];
+};
+
+// The nodes of levels >= 1 that block blk's particles start, and the children
+// of the roots.  tot = NULL (at most 64 blocks): hist holds the blocks' cells
+// per level and the block adds up those before it; otherwise hist holds, per
+// level, each block's exclusive offset among the level's cells, tot the level
+// totals.  A split cell's child count is written first as the end of its
+// children (by the particle that ends the cell) and turned into a count by
+// k_node_info.
+__device__ __forceinline__ void tree_nodes(const DevTree &t, int n, int blk, int nblk,
+                                           const uint32_t *hist, const uint32_t *tot,
+                                           int walk_levels, NodeLds &S) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if (tot) {
+    if (tid < FMM_MAXLEVEL) {
+      S.boff[tid] = (int)hist[(size_t)tid * nblk + blk];
+      S.btot[tid] = (int)tot[tid];
+    }
+  } else {
+    for (int l = w; l < FMM_MAXLEVEL; l += TD_WAVES) {
+      const int v = lane < nblk ? (int)hist[(size_t)l * nblk + lane] : 0;
+      const int all = wave_sum(v), before = wave_sum(lane < blk ? v : 0);
+      if (lane == 0) {
+        S.boff[l] = before;
+        S.btot[l] = all;
+      }
+    }
   }
-  const int b0 = blockIdx.x * TD_THREADS;
-  const int i = b0 + threadIdx.x;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int i = blk * TD_THREADS + tid;
   int d = 0, lo = 1, lo2 = FMM_MAXLEVEL + 1, r = 0;
+  uint64_t key = 0;
   if (i < n) {
     td_unpack(t.key2[i], d, lo, lo2);
     r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, i) : 0;
+    key = t.key[i];
   }
   const int hi = i < n ? d : 0;
   const unsigned long long below = lanes_below_mask();
   int rank[FMM_MAXLEVEL + 2];  // exclusive rank among the level's cell starts, levels 1..
+#pragma unroll
   for (int l = 1; l <= FMM_MAXLEVEL; ++l) {
     const unsigned long long b = __ballot(lo <= l && l <= hi);
     rank[l] = __popcll(b & below);
-    if (lane == 0) wpre[w][l - 1] = __popcll(b);
+    if (lane == 0) S.wpre[w][l - 1] = __popcll(b);
   }
   rank[0] = rank[FMM_MAXLEVEL + 1] = 0;
   __syncthreads();
-  if (threadIdx.x < FMM_MAXLEVEL) {  // exclusive prefix over the waves, in place
-    int run = 0;
+  if (tid < FMM_MAXLEVEL) {  // exclusive prefix over the waves and the blocks before, in place
+    int run = S.boff[tid];
     for (int ww = 0; ww < TD_WAVES; ++ww) {
-      const int c = wpre[ww][threadIdx.x];
-      wpre[ww][threadIdx.x] = run;
+      const int c = S.wpre[ww][tid];
+      S.wpre[ww][tid] = run;
       run += c;
     }
   }
+  if (tid == 64) {
+    int at = t.n_req;
+    S.lvs[0] = 0;
+    S.lvs[1] = at;
+    for (int l = 1; l <= FMM_NLEVELS; ++l) {
+      at += l <= FMM_MAXLEVEL ? S.btot[l - 1] : 0;
+      S.lvs[l + 1] = at;
+    }
+  }
   __syncthreads();
-  for (int l = 1; l <= FMM_MAXLEVEL; ++l)
-    rank[l] += wpre[w][l - 1] + (int)hist[(size_t)(l - 1) * nblk + blockIdx.x];
   const int64_t cap = t.cap_nodes;
   int leaves = 0;
   if (i < n) {
     const Box box = t.box[r];
-    // cells that start at i
-    for (int l = lo; l <= hi; ++l) {
-      const int64_t k = (int64_t)lvs_s[l] + rank[l];
+#pragma unroll
+    for (int l = 1; l <= FMM_MAXLEVEL; ++l) rank[l] += S.wpre[w][l - 1];
+    // the root's children start at the system's first particle, its run ends at the last
+    if (lo == 1 && i == t.req_off[r] && d > 0 && r < cap) t.nchild0[r] = S.lvs[1] + rank[1];
+    if (lo2 == 0 && d > 0 && r < cap) t.nnchild[r] = S.lvs[1] + rank[1] + (lo <= 1 ? 1 : 0);
+#pragma unroll
+    for (int l = 1; l <= FMM_MAXLEVEL; ++l) {
+      const bool starts = lo <= l && l <= hi, ends = lo2 <= l && l <= hi;
+      if (!starts && !ends) continue;
       const bool split = l < d;
-      leaves += !split;
-      if (k >= cap) continue;
-      const bool ps = lo <= l - 1;  // i also starts its parent
-      t.nbeg[k] = i;
-      t.nlev[k] = l;
-      t.nparent[k] = l == 1 ? r : lvs_s[l - 1] + rank[l - 1] + (ps ? 1 : 0) - 1;
-      t.nchild0[k] = split ? lvs_s[l + 1] + rank[l + 1] : -1;
-      if (!split) t.nnchild[k] = 0;
-      t.nreq[k] = r;
-      t.ngeo[k] = cell_geometry(box, t.key[i] >> (3 * (FMM_MAXLEVEL - l)), l);
-    }
-    // the root's children start at the system's first particle
-    if (lo == 1 && i == t.req_off[r] && d > 0 && r < cap) t.nchild0[r] = lvs_s[1] + rank[1];
-    // runs that end at i
-    for (int l = lo2; l <= hi; ++l) {
-      const bool split = l < d;
-      const int incl_next = split ? rank[l + 1] + (lo <= l + 1 ? 1 : 0) : 0;
-      if (l == 0) {
-        if (split && r < cap) t.nnchild[r] = lvs_s[1] + incl_next;
-        continue;
+      if (starts) {  // a cell starts at i
+        const int64_t k = (int64_t)S.lvs[l] + rank[l];
+        leaves += !split;
+        if (k < cap) {
+          const bool ps = lo <= l - 1;  // i also starts its parent
+          t.nbeg[k] = i;
+          t.nlev[k] = l;
+          t.nparent[k] = l == 1 ? r : S.lvs[l - 1] + rank[l - 1] + (ps ? 1 : 0) - 1;
+          t.nchild0[k] = split ? S.lvs[l + 1] + rank[l + 1] : -1;
+          if (!split) t.nnchild[k] = 0;
+          t.nreq[k] = r;
+          t.ngeo[k] = cell_geometry(box, key >> (3 * (FMM_MAXLEVEL - l)), l);
+        }
       }
-      const int64_t k = (int64_t)lvs_s[l] + rank[l] + (lo <= l ? 1 : 0) - 1;
-      if (k >= cap) continue;
-      t.nend[k] = i + 1;
-      if (split) t.nnchild[k] = lvs_s[l + 1] + incl_next;
+      if (ends) {  // a run ends at i
+        const int64_t k = (int64_t)S.lvs[l] + rank[l] + (lo <= l ? 1 : 0) - 1;
+        if (k < cap) {
+          t.nend[k] = i + 1;
+          if (split) t.nnchild[k] = S.lvs[l + 1] + rank[l + 1] + (lo <= l + 1 ? 1 : 0);
+        }
+      }
     }
   }
   leaves = wave_sum(leaves);
-  if (lane == 0) leaves_w[w] = leaves;
+  if (lane == 0) S.leaves[w] = leaves;
   __syncthreads();
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     int s = 0;
-    for (int ww = 0; ww < TD_WAVES; ++ww) s += leaves_w[ww];
+    for (int ww = 0; ww < TD_WAVES; ++ww) s += S.leaves[ww];
     if (s) atomicAdd((int *)&t.hdr->n_leaves, s);
-    if (blockIdx.x == 0) {
+    if (blk == 0) {
       Header *h = t.hdr;
-      for (int l = 0; l < FMM_NLEVELS + 2; ++l) h->lvl_start[l] = lvs_s[l];
-      if (lvs_s[FMM_NLEVELS + 1] > cap) h->overflow |= OVF_NODES;
+      for (int l = 0; l < FMM_NLEVELS + 2; ++l) h->lvl_start[l] = S.lvs[l];
+      if (S.lvs[FMM_NLEVELS + 1] > cap) h->overflow |= OVF_NODES;
       int deepest = 0;
       for (int l = 1; l <= FMM_MAXLEVEL; ++l)
-        if (lvs_s[l + 1] > lvs_s[l]) deepest = l;
+        if (S.lvs[l + 1] > S.lvs[l]) deepest = l;
       if (deepest > walk_levels) h->overflow |= OVF_DEPTH;
     }
   }
 }
 
-// Walk record of every cell; turn_counts: nnchild of a split cell still holds
-// the end of its children (k_tree_nodes) and becomes a count first.
+__global__ __launch_bounds__(TD_THREADS) void k_tree_nodes(DevTree t, int n, int nblk,
+                                                           const uint32_t *hist,
+                                                           const uint32_t *tot, int walk_levels) {
+  __shared__ NodeLds lds;
+  tree_nodes(t, n, blockIdx.x, nblk, hist, tot, walk_levels, lds);
+}
+
+// Walk record of cell k; turn_counts: nnchild of a split cell still holds
+// the end of its children (tree_nodes) and becomes a count first.
+__device__ __forceinline__ void node_info(const DevTree &t, int k, bool turn_counts) {
+  const int c0 = t.nchild0[k];
+  int nc = t.nnchild[k];
+  if (turn_counts && c0 >= 0) {
+    nc -= c0;
+    t.nnchild[k] = nc;
+  }
+  t.ninfo[k] = make_int4(c0, nc, t.nbeg[k], t.nend[k]);
+}
+
 __global__ __launch_bounds__(FMM_BLOCK) void k_node_info(DevTree t, bool turn_counts) {
   const int total = min(t.hdr->lvl_start[FMM_NLEVELS + 1], (int)t.cap_nodes);
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < total; k += gridDim.x * blockDim.x) {
-    const int c0 = t.nchild0[k];
-    int nc = t.nnchild[k];
-    if (turn_counts && c0 >= 0) {
-      nc -= c0;
-      t.nnchild[k] = nc;
-    }
-    t.ninfo[k] = make_int4(c0, nc, t.nbeg[k], t.nend[k]);
-  }
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < total; k += gridDim.x * blockDim.x)
+    node_info(t, k, turn_counts);
 }
 
 // ---------------------------------------------------------------------------
 // Small batches (at most SMALL_N active particles in all): the whole build up
-// to the walk -- slots, boxes, roots, keys, every sort pass, sorted gather,
-// split depth and every split level -- in one workgroup, one launch, with no
-// host round trip.  Each step is the same per-element code as the multi-block
-// path, so the tree is the same bit for bit.
+// to the walk -- boxes, roots, keys, sort, sorted positions and every split
+// level -- in one workgroup, one launch, with no host round trip: the steps of
+// the multi-workgroup build on one tile and one block, so the tree is the same
+// bit for bit.  1,000 particles: 155 -> 33 us (the split level by level
+// and a radix sort of 8 wavefronts before).
 // ---------------------------------------------------------------------------
-// block-wide exclusive scan of one int per thread (wave shuffles, then the
-// wave totals through LDS); *total gets the sum
-__device__ __forceinline__ int block_excl_scan_small(int v, int *wsum, int *total) {
-  const int w = threadIdx.x >> 6;
-  int wt;
-  const int x = wave_excl_scan_int(v, &wt);
-  if ((threadIdx.x & 63) == 0) wsum[w] = wt;
-  __syncthreads();
-  int off = 0, tot = 0;
-  for (int k = 0; k < SMALL_WAVES; ++k) {
-    off += k < w ? wsum[k] : 0;
-    tot += wsum[k];
-  }
-  __syncthreads();
-  *total = tot;
-  return off + x;
-}
+static_assert(SMALL_N == MSORT_TILE && SMALL_N == TD_THREADS, "one tile, one block");
 
-__global__ __launch_bounds__(SMALL_THREADS) void k_build_small(DevTree t, int n, int leaf_size,
-                                                               int req_passes) {
-  __shared__ uint32_t cnt[SMALL_WAVES][256];
-  __shared__ uint32_t dbase[256];
-  __shared__ uint64_t skey[SMALL_THREADS];
-  __shared__ int sord[SMALL_THREADS];
-  __shared__ int wsum[SMALL_WAVES];
+__global__ __launch_bounds__(SMALL_N) void k_build_small(DevTree t, int n, int leaf_size) {
+  __shared__ union {
+    TileLds tile;
+    LevelLds level;
+    NodeLds node;
+  } lds;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int T = SMALL_THREADS;
-  Header *h = t.hdr;
-  if (tid == 0) {
-    h->nonfinite = 0;
-    h->n_leaves = 0;
-    header_init(t);
-  }
-  for (int q = tid; q < n; q += T) t.slot_req[q] = upper_index(t.req_off, t.n_req, q);
-  // root box of every request: one wavefront per request
-  int bad = 0;
-  for (int r = w; r < t.n_req; r += SMALL_WAVES) {
+  bool bad = false;
+  for (int r = w; r < t.n_req; r += SMALL_N / 64) {  // root boxes: a wavefront per request
     const DevReq q = t.reqs[r];
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (int i = lane; i < q.n; i += 64) {
-      int64_t g = q.active ? q.active[i] : i;
+      const int64_t g = q.active ? q.active[i] : i;
       for (int d = 0; d < 3; ++d) {
-        double x = q.pos[d * q.n_total + g];
+        const double x = q.pos[d * q.n_total + g];
         bad |= !isfinite(x);
         lo[d] = fmin(lo[d], x);
         hi[d] = fmax(hi[d], x);
@@ -915,221 +1127,102 @@ __global__ __launch_bounds__(SMALL_THREADS) void k_build_small(DevTree t, int n,
       }
     if (lane == 0) finish_box(t.box[r], lo, hi, q.n == 0);
   }
-  if (__syncthreads_or(bad) && tid == 0) h->nonfinite = 1;
-  for (int r = tid; r < t.n_req; r += T) root_init(t, r, leaf_size);
-  for (int q = tid; q < n; q += T) make_key(t, q, t.key, t.slot);
-  __syncthreads();
-  if (n <= T) {
-    // at most one particle per thread: the rank of (request, key, slot) among
-    // all of them is its place in the stable sorted order
-    uint64_t k = 0;
-    int r = 0;
-    if (tid < n) {
-      k = t.key[tid];
-      r = t.slot_req[tid];
-      skey[tid] = k;
-      sord[tid] = r;
-    }
-    __syncthreads();
-    if (tid < n) {
-      int rank = 0;
-      for (int j = 0; j < n; ++j) {
-        const int rj = sord[j];
-        const uint64_t kj = skey[j];
-        rank += (rj < r) || (rj == r && (kj < k || (kj == k && j < tid)));
-      }
-      t.key[rank] = k;
-      t.slot[rank] = tid;  // slots are still in input order
-    }
-    __syncthreads();
-  } else {
-    // stable LSD radix sort, 8-bit digits: 8 key passes, then request passes
-    uint64_t *kin = t.key, *kout = t.key2;
-    int32_t *sin = t.slot, *sout = t.slot2;
-    const unsigned long long below = lanes_below_mask();
-    const int base = w * 64 * SMALL_ITEMS;
-    const int items = min(SMALL_ITEMS, max(0, (n - base + 63) / 64));  // uniform per wave
-    for (int pass = 0; pass < 8 + req_passes; ++pass) {
-      const int by_req = pass >= 8;
-      const int shift = by_req ? (pass - 8) * 8 : pass * 8;
-      for (int d = tid; d < SMALL_WAVES * 256; d += T) (&cnt[0][0])[d] = 0;
-      __syncthreads();
-      uint64_t k[SMALL_ITEMS];
-      int32_t sv[SMALL_ITEMS];
-      uint32_t rank[SMALL_ITEMS], dg[SMALL_ITEMS];
-#pragma unroll
-      for (int it = 0; it < SMALL_ITEMS; ++it) {
-        if (it >= items) continue;  // wave-uniform
-        int i = base + it * 64 + lane;
-        bool valid = i < n;
-        k[it] = valid ? kin[i] : 0;
-        sv[it] = valid ? sin[i] : 0;
-        uint32_t d = by_req ? ((uint32_t)t.slot_req[sv[it]] >> shift) & 255u
-                            : (uint32_t)(k[it] >> shift) & 255u;
-        dg[it] = d;
-        unsigned long long m = __ballot(valid);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-          unsigned long long bal = __ballot((d >> b) & 1u);
-          m &= ((d >> b) & 1u) ? bal : ~bal;
-        }
-        uint32_t prior = cnt[w][d];
-        rank[it] = prior + (uint32_t)__popcll(m & below);
-        __builtin_amdgcn_wave_barrier();
-        if (valid && (m & below) == 0) cnt[w][d] = prior + (uint32_t)__popcll(m);
-        __builtin_amdgcn_wave_barrier();
-      }
-      __syncthreads();
-      if (w == 0) {  // digit bases: lane l scans digits 4l .. 4l+3
-        uint32_t tt[4], sum = 0;
-        for (int q = 0; q < 4; ++q) {
-          tt[q] = 0;
-          for (int ww = 0; ww < SMALL_WAVES; ++ww) tt[q] += cnt[ww][4 * lane + q];
-          sum += tt[q];
-        }
-        int tot;
-        uint32_t run = (uint32_t)wave_excl_scan_int((int)sum, &tot);
-        for (int q = 0; q < 4; ++q) {
-          dbase[4 * lane + q] = run;
-          run += tt[q];
-        }
-      }
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t run = dbase[tid];
-        for (int ww = 0; ww < SMALL_WAVES; ++ww) {
-          const uint32_t c = cnt[ww][tid];
-          cnt[ww][tid] = run;
-          run += c;
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int it = 0; it < SMALL_ITEMS; ++it) {
-        int i = base + it * 64 + lane;
-        if (it < items && i < n) {
-          uint32_t dst = cnt[w][dg[it]] + rank[it];
-          kout[dst] = k[it];
-          sout[dst] = sv[it];
-        }
-      }
-      __syncthreads();
-      uint64_t *tk = kin; kin = kout; kout = tk;
-      int32_t *ts = sin; sin = sout; sout = ts;
-    }
+  const int any = __syncthreads_or(bad);
+  if (tid == 0) {
+    header_init(t);
+    t.hdr->nonfinite = any ? 1 : 0;
   }
-  // sorted positions; split depth (keys leaf_size apart, same request)
-  int best = 0;
-  for (int i = tid; i < n; i += T) {
-    gather_at(t, i);
-    if (i + leaf_size < n) {
-      const int r = t.n_req > 1 ? upper_index(t.req_off, t.n_req, i) : 0;
-      if (t.n_req == 1 || i + leaf_size < t.req_off[r + 1]) {
-        uint64_t x = t.key[i] ^ t.key[i + leaf_size];
-        best = max(best, x == 0 ? FMM_MAXLEVEL : (__clzll(x) - 1) / 3);
-      }
-    }
-  }
-  for (int off = 32; off > 0; off >>= 1) best = max(best, __shfl_xor(best, off, 64));
-  if (lane == 0) wsum[w] = best;
   __syncthreads();
-  for (int k2 = 0; k2 < SMALL_WAVES; ++k2) best = max(best, wsum[k2]);
-  if (tid == 0) h->max_prefix = best;
-  const int max_level = min(FMM_MAXLEVEL, best + 1);
+  for (int r = tid; r < t.n_req; r += SMALL_N) root_init(t, r, leaf_size);
+  sort_tile(t, n, 0, t.key, t.slot, true, lds.tile);
   __syncthreads();
-  // level-by-level split
-  int leaves = 0;
-  int ls = 0, run = t.n_req;  // level l occupies [ls, run) when its split starts
-  for (int l = 0; l < max_level; ++l) {
-    const int le = min(run, (int)t.cap_nodes);
-    int next = run;
-    for (int b0 = ls; b0 < le; b0 += T) {
-      const int i = b0 + tid;
-      const int nc = i < le ? count_node(t, i, l, leaf_size) : 0;
-      int total;
-      const int first = next + block_excl_scan_small(nc, wsum, &total);
-      if (i < le) leaves += emit_node(t, i, l, nc, first, leaf_size);
-      next += total;
-    }
-    if (tid == 0) {
-      for (int k2 = l + 2; k2 < FMM_NLEVELS + 2; ++k2) h->lvl_start[k2] = next;
-      if (next > t.cap_nodes) h->overflow |= OVF_NODES;
-    }
-    ls = run;
-    run = next;
-    __syncthreads();
+  if (leaf_size >= n) {  // no cell is split: every window would reach past its system
+    if (tid < t.n_req) node_info(t, tid, true);
+    for (int r = tid + SMALL_N; r < t.n_req; r += SMALL_N) node_info(t, r, true);
+    return;
   }
-  int total;
-  block_excl_scan_small(leaves, wsum, &total);
-  if (tid == 0 && total) atomicAdd((int *)&h->n_leaves, total);
-  for (int k2 = tid; k2 < min(run, (int)t.cap_nodes); k2 += T)
-    t.ninfo[k2] = make_int4(t.nchild0[k2], t.nnchild[k2], t.nbeg[k2], t.nend[k2]);
+  tree_levels(t, n, leaf_size, 0, 1, t.sort_hist, lds.level);
+  __syncthreads();
+  tree_nodes(t, n, 0, 1, t.sort_hist, nullptr, FMM_MAXLEVEL, lds.node);
+  __syncthreads();
+  const int total = min(lds.node.lvs[FMM_NLEVELS + 1], (int)t.cap_nodes);
+  for (int k = tid; k < total; k += SMALL_N) node_info(t, k, true);
 }
 
 hipError_t launch_build_small(const DevTree &t, const BuildArgs &a, hipStream_t s) {
   if (a.tm) a.tm->start(PH_TREE, s);
-  const int req_passes = a.n_req > 1 ? (a.n_req > 65536 ? 4 : 2) : 0;
-  hipLaunchKernelGGL(k_build_small, dim3(1), dim3(SMALL_THREADS), 0, s, t, a.n, a.leaf_size,
-                     req_passes);
+  hipLaunchKernelGGL(k_build_small, dim3(1), dim3(SMALL_N), 0, s, t, a.n, a.leaf_size);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }
 
+// Boxes, header, roots, keys, sort by (system, key, slot) and sorted positions.
 hipError_t launch_sort(const DevTree &t, const BuildArgs &a, hipStream_t s) {
   const int n = a.n;
   const int nb = (n + FMM_BLOCK - 1) / FMM_BLOCK;
   if (a.tm) a.tm->start(PH_SORT, s);
-  hipLaunchKernelGGL(k_slot_req, dim3(std::max(nb, 1)), dim3(FMM_BLOCK), 0, s, t, n);
   hipLaunchKernelGGL(k_bbox_partial, dim3(a.n_blk), dim3(FMM_BLOCK), 0, s, t);
-  hipLaunchKernelGGL(k_bbox_final, dim3((a.n_req + 3) / 4), dim3(FMM_BLOCK), 0, s, t);
-  hipLaunchKernelGGL(k_tree_init, dim3((a.n_req + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
-                     s, t, a.leaf_size);
-  if (n > 0) {
+  if (a.n_req <= INIT_WAVES) {
+    hipLaunchKernelGGL(k_init, dim3(1), dim3(INIT_WAVES * 64), 0, s, t, a.leaf_size);
+  } else {
+    hipLaunchKernelGGL(k_header_init, dim3(1), dim3(1), 0, s, t);
+    hipLaunchKernelGGL(k_boxes, dim3((a.n_req + 3) / 4), dim3(FMM_BLOCK), 0, s, t, a.leaf_size);
+  }
+  if (n > 0 && a.n_max <= MSORT_MAX_N) {
+    // merges until a run holds the largest system; one system starts at slot
+    // 0, others anywhere in a tile
+    const int64_t reach = a.n_req == 1 ? n : (int64_t)a.n_max + MSORT_TILE - 1;
+    int merges = 0;
+    for (int64_t R = MSORT_TILE; R < reach; R *= MSORT_FAN) ++merges;
+    // the result always lands in key / slot
+    uint64_t *k0 = merges & 1 ? t.key2 : t.key, *k1 = merges & 1 ? t.key : t.key2;
+    int32_t *s0 = merges & 1 ? t.slot2 : t.slot, *s1 = merges & 1 ? t.slot : t.slot2;
+    hipLaunchKernelGGL(k_sort_tiles, dim3((n + MSORT_TILE - 1) / MSORT_TILE), dim3(MSORT_TILE), 0,
+                       s, t, n, k0, s0, merges == 0);
+    int R = MSORT_TILE;
+    for (int m = 0; m < merges; ++m, R *= MSORT_FAN) {
+      hipLaunchKernelGGL(k_sort_merge, dim3(nb), dim3(FMM_BLOCK), 0, s, t, n, R, k0, s0, k1, s1,
+                         m + 1 == merges);
+      std::swap(k0, k1);
+      std::swap(s0, s1);
+    }
+  } else if (n > 0) {
     const int nblk = (n + SORT_TILE - 1) / SORT_TILE;
     // 8 passes over the 63-bit key, then (several requests) one pass per byte
     // of the largest request id; with an odd number of passes the keys start
     // in key2 / slot2, so that the result always lands in key / slot
     int req_passes = 0;
-    if (a.n_req > 1) req_passes = a.n_req > 65536 ? 4 : (a.n_req > 256 ? 2 : 1);
+    if (a.n_req > 1) {
+      req_passes = a.n_req > 65536 ? 4 : (a.n_req > 256 ? 2 : 1);
+      hipLaunchKernelGGL(k_slot_req, dim3(nb), dim3(FMM_BLOCK), 0, s, t, n);
+    }
     const int passes = 8 + req_passes;
     const int odd = passes & 1;
     hipLaunchKernelGGL(k_keys, dim3(nb), dim3(FMM_BLOCK), 0, s, t, n, odd);
     uint64_t *kin = odd ? t.key2 : t.key, *kout = odd ? t.key : t.key2;
     int32_t *sin = odd ? t.slot2 : t.slot, *sout = odd ? t.slot : t.slot2;
-    const int raw = nblk <= SORT_RAW_TILES;
-    // raw passes: one histogram slice per pass, the first counted by
-    // k_sort_hist (which clears the others), each later one by the scatter
-    // before it
-    const int slice = 256 * nblk;
     for (int pass = 0; pass < passes; ++pass) {
       const int by_req = pass >= 8;
       const int shift = by_req ? (pass - 8) * 8 : pass * 8;
-      const int nx = pass + 1;
-      const int next_by_req = nx >= 8;
-      const int next_shift = next_by_req ? (nx - 8) * 8 : nx * 8;
-      uint32_t *hist = raw ? t.sort_hist + (size_t)pass * slice : t.sort_hist;
-      uint32_t *hist_next = raw && nx < passes ? t.sort_hist + (size_t)nx * slice : nullptr;
-      if (!raw || pass == 0)
-        hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(SORT_THREADS), 0, s, kin, sin, t.slot_req,
-                           n, shift, by_req, hist, nblk, raw ? passes - 1 : 0);
-      if (!raw)
-        hipLaunchKernelGGL(k_sort_digit_scan, dim3(256), dim3(FMM_BLOCK), 0, s, t.sort_hist, nblk,
-                           t.sort_dtot);
+      hipLaunchKernelGGL(k_sort_hist, dim3(nblk), dim3(SORT_THREADS), 0, s, kin, sin, t.slot_req, n,
+                         shift, by_req, t.sort_hist, nblk);
+      hipLaunchKernelGGL(k_sort_digit_scan, dim3(256), dim3(FMM_BLOCK), 0, s, t.sort_hist, nblk,
+                         t.sort_dtot);
       hipLaunchKernelGGL(k_sort_scatter, dim3(nblk), dim3(SORT_THREADS), 0, s, kin, sin, kout, sout,
-                         t.slot_req, n, shift, by_req, hist, nblk, t.sort_dtot, raw, hist_next,
-                         next_shift, next_by_req);
-      uint64_t *tk = kin; kin = kout; kout = tk;
-      int32_t *ts = sin; sin = sout; sout = ts;
+                         t.slot_req, n, shift, by_req, t.sort_hist, nblk, t.sort_dtot);
+      std::swap(kin, kout);
+      std::swap(sin, sout);
     }
     hipLaunchKernelGGL(k_gather_sorted, dim3(nb), dim3(FMM_BLOCK), 0, s, t, n);
+  }
+  if (n > 0 && !build_tree_direct_ok(a.leaf_size))
     hipLaunchKernelGGL(k_split_depth, dim3(std::min(nb, 512)), dim3(FMM_BLOCK), 0, s, t, n,
                        a.leaf_size);
-  }
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }
 
-// Every level at once (see k_tree_levels); false when leaf_size is beyond the
+// Every level at once (see tree_levels); false when leaf_size is beyond the
 // window that fits in LDS (then launch_build_tree builds level by level).
 bool build_tree_direct_ok(int leaf_size) { return leaf_size >= 1 && leaf_size <= TD_MAXLEAF; }
 
@@ -1140,16 +1233,15 @@ hipError_t launch_build_tree_direct(const DevTree &t, const BuildArgs &a, int wa
   const int n = a.n;
   if (a.tm) a.tm->start(PH_TREE, s);
   if (n > 0) {
-    const int L = a.leaf_size;
     const int nblk = (n + TD_THREADS - 1) / TD_THREADS;
-    hipLaunchKernelGGL(k_tree_pairs, dim3((n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0, s,
-                       t, n, L);
-    hipLaunchKernelGGL(k_tree_levels, dim3(nblk), dim3(TD_THREADS), 0, s, t, n, L, nblk,
+    const bool scan = nblk > 64;  // more blocks than a wavefront adds up itself
+    hipLaunchKernelGGL(k_tree_levels, dim3(nblk), dim3(TD_THREADS), 0, s, t, n, a.leaf_size, nblk,
                        t.sort_hist);
-    hipLaunchKernelGGL(k_sort_digit_scan, dim3(FMM_MAXLEVEL), dim3(FMM_BLOCK), 0, s, t.sort_hist,
-                       nblk, t.sort_dtot);
+    if (scan)
+      hipLaunchKernelGGL(k_sort_digit_scan, dim3(FMM_MAXLEVEL), dim3(FMM_BLOCK), 0, s, t.sort_hist,
+                         nblk, t.sort_dtot);
     hipLaunchKernelGGL(k_tree_nodes, dim3(nblk), dim3(TD_THREADS), 0, s, t, n, nblk, t.sort_hist,
-                       t.sort_dtot, walk_levels);
+                       scan ? t.sort_dtot : nullptr, walk_levels);
     hipLaunchKernelGGL(k_node_info, dim3(std::min(1024, std::max(1, n / 256))), dim3(FMM_BLOCK), 0,
                        s, t, true);
   }

@@ -377,9 +377,9 @@ class Solver:
         return self.evaluate_batched(systems, p=p)
 
     def set_small_path(self, enable):
-        """Single-workgroup build and walk for small batches: True (default)
-        up to 1024 particles, 2 up to 8192 (the most those launches hold),
-        False never; same trees, lists and results either way."""
+        """Single-workgroup build for small batches: True (default) or 2 up to
+        1024 particles (the most that launch holds), False never; same trees,
+        lists and results either way."""
         mode = 2 if enable == 2 else int(bool(enable))
         self._raise(lib().fmm_set_small_path(self._h, mode))
 

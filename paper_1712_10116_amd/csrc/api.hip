@@ -724,12 +724,19 @@ extern "C" fmm_status fmm_forces_grad(fmm_ctx *c, const double *pos, const doubl
                                       double *grad) {
   if (!c) return FMM_EINVAL;
   if (n_active > 0 && !grad) return fail(c, FMM_EINVAL, "grad is NULL");
-  if (!c->gstage && !dalloc(c, &c->gstage, 6 * c->max_n))
-    return fail(c, FMM_ENOMEM, "force-gradient staging");
   fmm_status st = fmm_forces(c, pos, mass, n_total, active, n_active, eps, theta, p, acc, pot);
   if (st != FMM_OK || n_active == 0) return st;
+  if (c->gpart_rows < c->t.cap_part) {  // the partial rows grow with those of the forces
+    dfree(c, c->gstage);
+    c->gstage = nullptr;
+    c->gpart_rows = 0;
+    if (!dalloc(c, &c->gstage, 6 * (c->max_n + c->t.cap_part)))
+      return fail(c, FMM_ENOMEM, "force-gradient staging");
+    c->gpart_rows = c->t.cap_part;
+  }
   HIPCHK(c, launch_force_gradient(c->t, c->n_nodes, (int)n_active, p, c->prm.kernel,
-                                  c->prm.precision == FMM_PREC_MIXED, eps, c->gstage, grad,
+                                  c->prm.precision == FMM_PREC_MIXED, eps, c->gstage, c->gstage + 6 * c->max_n,
+                                  grad,
                                   c->stream));
   return FMM_OK;
 }

@@ -321,13 +321,20 @@ hipError_t launch_evaluate(const DevTree &t, const EvalArgs &e, hipStream_t s);
 // mass gather, P2M and M2M of an evaluation on stream s (exact tree sizes)
 hipError_t launch_upward(const DevTree &t, const EvalArgs &e, hipStream_t s);
 bool eval_order_supported(int p);
+// Wavefronts for the near-field items of a tree of n particles and some
+// n_nodes cells; their number is read on the device: about one to two per leaf
+// of a large system, up to one per staged window of a small one.
+static inline int p2p_grid_items(int n, int n_nodes) {
+  const int64_t w = (n <= 131072 ? 8 : 2) * (int64_t)n_nodes;
+  return (int)(w < 1 ? 1 : w);
+}
 // sources of one staged P2P window
 int p2p_window_sources(bool mixed);
 // grad.hip: force gradient of one system's n active particles (SoA 6 x n) on
 // the tree and local expansions of the evaluation just queued on stream s
 hipError_t launch_force_gradient(const DevTree &t, int n_nodes, int n, int p, int kernel,
-                                 bool mixed, double eps, double *stage, double *grad,
-                                 hipStream_t s);
+                                 bool mixed, double eps, double *stage, double *gpart,
+                                 double *grad, hipStream_t s);
 // vector-source pass (eval.hip): sources m_j v_j on the last build's tree (one
 // system), vec SoA 3 x e.n in active order, dv scratch 3 x cap_n doubles;
 // the request's acc receives +gradient of their potential, pot the potential
@@ -335,8 +342,8 @@ hipError_t launch_dipole(const DevTree &t, const EvalArgs &e, const double *vec,
                          hipStream_t s);
 // its near field (grad.hip): minus sum_j m_j H(x_i - x_j) v_j over the P2P
 // partners into near[0..2], sum_j m_j v_j . grad psi(x_i - x_j) into near[3]
-hipError_t launch_p2p_dipole(const DevTree &t, int n_nodes, int kernel, bool mixed, double eps,
-                             const double *dv, hipStream_t s);
+hipError_t launch_p2p_dipole(const DevTree &t, int n_nodes, int n, int kernel, bool mixed,
+                             double eps, const double *dv, hipStream_t s);
 // hhs.hip
 hipError_t launch_gather_mask_mass(const double *mass, const int32_t *sys, int n_sys,
                                    const int32_t *flag_fast, int mask_fast, double *out,

@@ -475,7 +475,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2p(DevTree t, int n, bool dev, d
   l2p_eval<T, P>(Lt, mono, phi, gx, gy, gz);
   const int64_t cap = t.cap_n;
   double nx = t.near[j], ny = t.near[cap + j], nz = t.near[2 * cap + j], np = t.near[3 * cap + j];
-  const int ne = sgn > 0 ? t.nshare[leaf] : 0;  // the vector-source near field is not cut
+  const int ne = t.nshare[leaf];
   if (ne > 0) {  // the near field's further shares, in share order
     const int b = t.nbeg[leaf], na = t.nend[leaf] - b;
     const double4 *row = t.part + t.part_off[leaf] + (j - b);
@@ -975,9 +975,7 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   hipEventRecord(e.fork, s);
   hipStreamWaitEvent(e.side, e.fork, 0);
   const int tp = tm ? tm->begin(PH_P2P, e.side) : -1;
-  // the number of items is read on the device: about one to two per leaf of a
-  // large system, up to one per staged window of a small one
-  const int p2p_blocks = ((e.n <= 131072 ? 8 : 2) * ga + P2P_WAVES - 1) / P2P_WAVES;
+  const int p2p_blocks = (p2p_grid_items(e.n, ga) + P2P_WAVES - 1) / P2P_WAVES;
   if (e.eps > 0)
     hipLaunchKernelGGL((k_p2p<(sizeof(T) == 4), KERNEL, false>), dim3(p2p_blocks),
                        dim3(P2P_WAVES * 64), 0, e.side, t, e.eps);
@@ -1113,7 +1111,7 @@ static void run_dipole(const DevTree &t, const EvalArgs &e, const double *vec, d
         hipLaunchKernelGGL((k_l2l<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1);
     }
   }
-  launch_p2p_dipole(t, nn, e.kernel, sizeof(T) == 4, e.eps, dv, s);
+  launch_p2p_dipole(t, nn, e.n, e.kernel, sizeof(T) == 4, e.eps, dv, s);
   hipLaunchKernelGGL((k_l2p<T, P>), dim3((e.n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, e.n, false, -1.0);
 }

@@ -45,33 +45,51 @@ struct alignas(4 * sizeof(R)) SrcR {
   R x, y, z, m;
 };
 
-// near part: one wavefront per sink leaf, lanes over its sinks (and, for
-// leaves of at most 32, over 2-16 phases of the sources), each source leaf
-// staged through LDS 64 particles at a time as offsets from the sink leaf's
-// centre in R (FP32 in the mixed form: cell-local offsets, as in the forces'
-// P2P); pair terms in R, summed in R over one source leaf and then into FP64.
-// Per pair: m h d (3 products) and six FMAs of it with d for the h d d^T
+// The entries of its leaf's P2P list that a near-field work item covers here.
+// The items are those of P2P (groups of 64 sinks, shares of the list), but the
+// sums below run leaf by leaf, so share grp of ng takes the grp-th part of the
+// list's entries.
+struct ItemRange {
+  int A, tb, q0, q1, grp, part;
+};
+__device__ __forceinline__ ItemRange item_range(const DevTree &t, int it) {
+  const P2PItem im = t.items[it];
+  const int64_t cnt = t.p2p_cnt[im.A];
+  const int ng = t.nshare[im.A] + 1;
+  return {im.A, im.tb, (int)(cnt * im.grp / ng), (int)(cnt * (im.grp + 1) / ng), im.grp, im.part};
+}
+
+// near part: one wavefront (and workgroup) per work item, lanes over its sinks
+// (and, for 32 sinks or fewer, over 2-16 phases of the sources), each source
+// leaf staged through LDS 64 particles at a time as offsets from the sink
+// leaf's centre in R (FP32 in the mixed form: cell-local offsets, as in the
+// forces' P2P); pair terms in R, summed in R over one source leaf and then into
+// FP64.  Per pair: m h d (3 products) and six FMAs of it with d for the h d d^T
 // part; the g I part is one sum of m g per source leaf.  The self pair (d = 0)
 // is masked by a select, so an infinite g or h there never reaches a sum.
-// Written in sorted order to stage (6 rows of stride cap_n); k_l2p_grad adds
-// the far part and writes each particle's tensor once in active order.
+// Written in sorted order to stage (6 rows of stride cap_n), shares past the
+// first to gpart (6 values a row); k_l2p_grad adds them and the far part and
+// writes each particle's tensor once in active order.  One wavefront per leaf
+// had left the kernel waiting for the longest lists (65,536-particle Plummer
+// sphere, leaf 64, FP64, this kernel and the vector-source one together: 2.6 ->
+// 0.75 ms).
 template <typename R, int KERNEL>
-__global__ __launch_bounds__(FMM_BLOCK) void k_p2p_grad(DevTree t, int n_nodes, double eps,
-                                                        double *__restrict__ stage) {
-  const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(64) void k_p2p_grad(DevTree t, double eps,
+                                                 double *__restrict__ stage,
+                                                 double *__restrict__ gpart) {
+  const int lane = threadIdx.x;
   // neighbouring leaves, which share most of their sources, on one XCD
-  const int wave =
-      __builtin_amdgcn_readfirstlane((xcd_block<32>(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6);
-  const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const int first = __builtin_amdgcn_readfirstlane(xcd_block<128>(blockIdx.x, gridDim.x));
   const R reps = (R)eps, ie = eps > 0 ? (R)(1.0 / eps) : R(0);
-  __shared__ SrcR<R> src_lds[FMM_BLOCK / 64][64];
-  SrcR<R> *st = src_lds[threadIdx.x >> 6];
-  for (int A = wave; A < n_nodes; A += nwaves) {
-    if (t.nnchild[A] != 0) continue;
+  __shared__ SrcR<R> st[64];
+  const int n_items = (int)t.hdr->item_cursor;
+  for (int it = first; it < n_items; it += gridDim.x) {
+    const ItemRange im = item_range(t, it);
+    const int A = im.A, tb = im.tb;
     const int bA = t.nbeg[A], nA = t.nend[A] - bA;
-    const int loff = t.p2p_off[A], cnt = t.p2p_cnt[A];
+    const int loff = t.p2p_off[A];
     const double4 gA = t.ngeo[A];
-    for (int tb = 0; tb < nA; tb += 64) {
+    {
       // lanes = (sink, phase): nph phases share each sink and take every
       // nph-th source, so a leaf of fewer than 64 sinks still fills the wave
       const int ns = min(64, nA - tb);
@@ -82,7 +100,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_p2p_grad(DevTree t, int n_nodes, 
       // the sink's offset, formed exactly as a staged source's
       const R xi = (R)(t.sx[i] - gA.x), yi = (R)(t.sy[i] - gA.y), zi = (R)(t.sz[i] - gA.z);
       double G[6] = {0, 0, 0, 0, 0, 0};
-      for (int q = 0; q < cnt; ++q) {
+      for (int q = im.q0; q < im.q1; ++q) {
         const int B = t.p2p_src[loff + q];
         const int eB = t.nend[B];
         R Gs[6] = {0, 0, 0, 0, 0, 0};
@@ -130,8 +148,10 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_p2p_grad(DevTree t, int n_nodes, 
         for (int c = 0; c < 6; ++c) G[c] += __shfl_xor(G[c], o, 64);
       if (valid && ph == 0) {
         const int64_t cap = t.cap_n;
+        double *out = im.grp == 0 ? stage + i : gpart + 6 * (int64_t)(im.part + (i - bA));
+        const int64_t stride = im.grp == 0 ? cap : 1;
 #pragma unroll
-        for (int c = 0; c < 6; ++c) stage[c * cap + i] = G[c];
+        for (int c = 0; c < 6; ++c) out[c * stride] = G[c];
       }
     }
   }
@@ -144,6 +164,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_p2p_grad(DevTree t, int n_nodes, 
 template <typename T, int P>
 __global__ __launch_bounds__(FMM_BLOCK) void k_l2p_grad(DevTree t, int n,
                                                         const double *__restrict__ stage,
+                                                        const double *__restrict__ gpart,
                                                         double *__restrict__ grad, int64_t nq,
                                                         int32_t off) {
   constexpr MI<P> mi{};
@@ -173,28 +194,40 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2p_grad(DevTree t, int n,
   }
   const int64_t k = t.slot[j] - off, cap = t.cap_n;
   const double s2 = ih * ih;
+  double G[6];
 #pragma unroll
-  for (int c = 0; c < 6; ++c) grad[c * nq + k] = stage[c * cap + j] - (double)H[c] * s2;
+  for (int c = 0; c < 6; ++c) G[c] = stage[c * cap + j];
+  const int ne = t.nshare[leaf];
+  if (ne > 0) {  // the near part's further shares, in share order
+    const int b = t.nbeg[leaf], na = t.nend[leaf] - b;
+    const double *row = gpart + 6 * (int64_t)(t.part_off[leaf] + (j - b));
+    for (int e = 0; e < ne; ++e)
+#pragma unroll
+      for (int c = 0; c < 6; ++c) G[c] += row[6 * (int64_t)e * na + c];
+  }
+#pragma unroll
+  for (int c = 0; c < 6; ++c) grad[c * nq + k] = G[c] - (double)H[c] * s2;
 }
 
 template <typename T, int P>
-void launch_l2p_grad(const DevTree &t, int n, const double *stage, double *grad, hipStream_t s) {
+void launch_l2p_grad(const DevTree &t, int n, const double *stage, const double *gpart,
+                     double *grad, hipStream_t s) {
   hipLaunchKernelGGL((k_l2p_grad<T, P>), dim3((n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK),
-                     0, s, t, n, stage, grad, (int64_t)n, 0);
+                     0, s, t, n, stage, gpart, grad, (int64_t)n, 0);
 }
 
 template <typename T, int KERNEL>
 bool dispatch_grad(const DevTree &t, int n_nodes, int n, int p, double eps, double *stage,
-                   double *grad, hipStream_t s) {
-  hipLaunchKernelGGL((k_p2p_grad<T, KERNEL>), dim3((n_nodes + 3) / 4), dim3(FMM_BLOCK), 0, s, t,
-                     n_nodes, eps, stage);
+                   double *gpart, double *grad, hipStream_t s) {
+  hipLaunchKernelGGL((k_p2p_grad<T, KERNEL>), dim3(p2p_grid_items(n, n_nodes)), dim3(64), 0, s, t,
+                     eps, stage, gpart);
   switch (p) {
-    case 1: launch_l2p_grad<T, 1>(t, n, stage, grad, s); return true;
-    case 2: launch_l2p_grad<T, 2>(t, n, stage, grad, s); return true;
-    case 3: launch_l2p_grad<T, 3>(t, n, stage, grad, s); return true;
-    case 4: launch_l2p_grad<T, 4>(t, n, stage, grad, s); return true;
-    case 5: launch_l2p_grad<T, 5>(t, n, stage, grad, s); return true;
-    case 6: launch_l2p_grad<T, 6>(t, n, stage, grad, s); return true;
+    case 1: launch_l2p_grad<T, 1>(t, n, stage, gpart, grad, s); return true;
+    case 2: launch_l2p_grad<T, 2>(t, n, stage, gpart, grad, s); return true;
+    case 3: launch_l2p_grad<T, 3>(t, n, stage, gpart, grad, s); return true;
+    case 4: launch_l2p_grad<T, 4>(t, n, stage, gpart, grad, s); return true;
+    case 5: launch_l2p_grad<T, 5>(t, n, stage, gpart, grad, s); return true;
+    case 6: launch_l2p_grad<T, 6>(t, n, stage, gpart, grad, s); return true;
     default: return false;
   }
 }
@@ -204,30 +237,28 @@ bool dispatch_grad(const DevTree &t, int n_nodes, int n, int p, double eps, doub
 // H = g I + h d d^T the pair Hessian, and of m_j v_j . grad psi(x_i - x_j)
 // = -m_j g (v_j . d), d = x_j - x_i.  Written to near[] in sorted order with
 // the sign of an acceleration (minus the field) so that L2P adds the far
-// field's gradient the same way.  Layout as k_p2p_grad: one wavefront per
-// sink leaf, (sink, phase) lanes, each source leaf staged through LDS 64
-// particles at a time (offsets from the sink leaf's centre, mass and vector
-// in R), pair terms in R, summed in R over one source leaf and then into FP64.
+// field's gradient the same way (shares past the first to the partial rows, as
+// P2P's).  Layout as k_p2p_grad: one wavefront per work item, (sink, phase)
+// lanes, each source leaf staged through LDS 64 particles at a time (offsets
+// from the sink leaf's centre, mass and vector in R), pair terms in R, summed
+// in R over one source leaf and then into FP64.
 template <typename R, int KERNEL>
-__global__ __launch_bounds__(FMM_BLOCK) void k_p2p_dip(DevTree t, int n_nodes, double eps,
-                                                       const double *__restrict__ dv) {
-  const int lane = threadIdx.x & 63;
+__global__ __launch_bounds__(64) void k_p2p_dip(DevTree t, double eps,
+                                                const double *__restrict__ dv) {
+  const int lane = threadIdx.x;
   // neighbouring leaves, which share most of their sources, on one XCD
-  const int wave =
-      __builtin_amdgcn_readfirstlane((xcd_block<32>(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6);
-  const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const int first = __builtin_amdgcn_readfirstlane(xcd_block<128>(blockIdx.x, gridDim.x));
   const R reps = (R)eps, ie = eps > 0 ? (R)(1.0 / eps) : R(0);
   const int64_t cap = t.cap_n;
-  __shared__ SrcR<R> stage_x[FMM_BLOCK / 64][64];
-  __shared__ SrcR<R> stage_v[FMM_BLOCK / 64][64];
-  SrcR<R> *sx = stage_x[threadIdx.x >> 6];
-  SrcR<R> *sv = stage_v[threadIdx.x >> 6];
-  for (int A = wave; A < n_nodes; A += nwaves) {
-    if (t.nnchild[A] != 0) continue;
+  __shared__ SrcR<R> sx[64], sv[64];
+  const int n_items = (int)t.hdr->item_cursor;
+  for (int it = first; it < n_items; it += gridDim.x) {
+    const ItemRange im = item_range(t, it);
+    const int A = im.A, tb = im.tb;
     const int bA = t.nbeg[A], nA = t.nend[A] - bA;
-    const int loff = t.p2p_off[A], cnt = t.p2p_cnt[A];
+    const int loff = t.p2p_off[A];
     const double4 gA = t.ngeo[A];
-    for (int tb = 0; tb < nA; tb += 64) {
+    {
       const int ns = min(64, nA - tb);
       const int nph = ns <= 4 ? 16 : ns <= 8 ? 8 : ns <= 16 ? 4 : ns <= 32 ? 2 : 1;
       const int ti = lane / nph, ph = lane % nph;
@@ -235,7 +266,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_p2p_dip(DevTree t, int n_nodes, d
       const int i = bA + tb + (valid ? ti : 0);
       const R xi = (R)(t.sx[i] - gA.x), yi = (R)(t.sy[i] - gA.y), zi = (R)(t.sz[i] - gA.z);
       double U[4] = {0, 0, 0, 0};
-      for (int q = 0; q < cnt; ++q) {
+      for (int q = im.q0; q < im.q1; ++q) {
         const int B = t.p2p_src[loff + q];
         const int eB = t.nend[B];
         R Us[4] = {0, 0, 0, 0};
@@ -278,10 +309,14 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_p2p_dip(DevTree t, int n_nodes, d
 #pragma unroll
         for (int c = 0; c < 4; ++c) U[c] += __shfl_xor(U[c], o, 64);
       if (valid && ph == 0) {
-        t.near[i] = -U[0];
-        t.near[cap + i] = -U[1];
-        t.near[2 * cap + i] = -U[2];
-        t.near[3 * cap + i] = U[3];
+        if (im.grp == 0) {
+          t.near[i] = -U[0];
+          t.near[cap + i] = -U[1];
+          t.near[2 * cap + i] = -U[2];
+          t.near[3 * cap + i] = U[3];
+        } else {
+          t.part[im.part + (i - bA)] = make_double4(-U[0], -U[1], -U[2], U[3]);
+        }
       }
     }
   }
@@ -289,35 +324,35 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_p2p_dip(DevTree t, int n_nodes, d
 
 }  // namespace
 
-hipError_t launch_p2p_dipole(const DevTree &t, int n_nodes, int kernel, bool mixed, double eps,
-                             const double *dv, hipStream_t s) {
-  const dim3 grid((n_nodes + 3) / 4), blk(FMM_BLOCK);
+hipError_t launch_p2p_dipole(const DevTree &t, int n_nodes, int n, int kernel, bool mixed,
+                             double eps, const double *dv, hipStream_t s) {
+  const dim3 grid(p2p_grid_items(n, n_nodes)), blk(64);
   if (mixed) {
     if (kernel == 1)
-      hipLaunchKernelGGL((k_p2p_dip<float, 1>), grid, blk, 0, s, t, n_nodes, eps, dv);
+      hipLaunchKernelGGL((k_p2p_dip<float, 1>), grid, blk, 0, s, t, eps, dv);
     else
-      hipLaunchKernelGGL((k_p2p_dip<float, 0>), grid, blk, 0, s, t, n_nodes, eps, dv);
+      hipLaunchKernelGGL((k_p2p_dip<float, 0>), grid, blk, 0, s, t, eps, dv);
   } else {
     if (kernel == 1)
-      hipLaunchKernelGGL((k_p2p_dip<double, 1>), grid, blk, 0, s, t, n_nodes, eps, dv);
+      hipLaunchKernelGGL((k_p2p_dip<double, 1>), grid, blk, 0, s, t, eps, dv);
     else
-      hipLaunchKernelGGL((k_p2p_dip<double, 0>), grid, blk, 0, s, t, n_nodes, eps, dv);
+      hipLaunchKernelGGL((k_p2p_dip<double, 0>), grid, blk, 0, s, t, eps, dv);
   }
   return hipGetLastError();
 }
 
 // One system's tree (request 0 at slot offset 0), n active particles.
 hipError_t launch_force_gradient(const DevTree &t, int n_nodes, int n, int p, int kernel,
-                                 bool mixed, double eps, double *stage, double *grad,
-                                 hipStream_t s) {
+                                 bool mixed, double eps, double *stage, double *gpart,
+                                 double *grad, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   bool ok;
   if (mixed)
-    ok = kernel == 1 ? dispatch_grad<float, 1>(t, n_nodes, n, p, eps, stage, grad, s)
-                     : dispatch_grad<float, 0>(t, n_nodes, n, p, eps, stage, grad, s);
+    ok = kernel == 1 ? dispatch_grad<float, 1>(t, n_nodes, n, p, eps, stage, gpart, grad, s)
+                     : dispatch_grad<float, 0>(t, n_nodes, n, p, eps, stage, gpart, grad, s);
   else
-    ok = kernel == 1 ? dispatch_grad<double, 1>(t, n_nodes, n, p, eps, stage, grad, s)
-                     : dispatch_grad<double, 0>(t, n_nodes, n, p, eps, stage, grad, s);
+    ok = kernel == 1 ? dispatch_grad<double, 1>(t, n_nodes, n, p, eps, stage, gpart, grad, s)
+                     : dispatch_grad<double, 0>(t, n_nodes, n, p, eps, stage, gpart, grad, s);
   if (!ok) return hipErrorInvalidValue;
   return hipGetLastError();
 }

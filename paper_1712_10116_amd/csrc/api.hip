@@ -438,16 +438,61 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       if (c->hh.lvl_start[l + 1] > c->hh.lvl_start[l]) depth = l;
     return depth;
   };
-  // 0. small batches: build and walk in two single-workgroup launches and one
-  // readback; anything that needs more room falls through to the general path
-  if (n_all <= c->small_max && build_tree_direct_ok(a.leaf_size)) {
-    HIPCHK(c, launch_build_small(c->t, a, c->stream));
-    HIPCHK(c, launch_traverse_paths(c->t, a, WALK_PATH_SMALL_GRID, c->stream));
-    st = read_header(c);
-    if (st != FMM_OK) return st;
+  // 0. small trees: everything is queued without reading a size back (the walk's
+  // path form, M2M and L2L in one workgroup, sizes read on the device), with
+  // one header readback at the end; anything that needs more room falls
+  // through to the general path.  Batches of up to SMALL_N particles are built
+  // by one workgroup.  A system has about 2 (uniform) to 5 (concentrated) cells
+  // per leaf_size particles; the host's wait for the level sizes cost about
+  // 25 us of a 12,526-particle solve.
+  const bool direct = build_tree_direct_ok(a.leaf_size);
+  const bool one_wg = n_all <= c->small_max && direct;
+  if (one_wg || (direct && c->small_max >= 0 && n_all <= SMALL_TREE_LEAVES * (int64_t)a.leaf_size)) {
+    if (one_wg) {
+      HIPCHK(c, launch_build_small(c->t, a, c->stream));
+    } else {
+      HIPCHK(c, launch_sort(c->t, a, c->stream));
+      HIPCHK(c, launch_build_tree_direct(c->t, a, FMM_MAXLEVEL, c->stream));
+    }
+    const int cells = (int)std::min<int64_t>(c->t.cap_nodes, 5 * (n_all / a.leaf_size) + 64);
+    const bool fuse = p_fused > 0 && n_all > 0;
+    EvalArgs e = {};
+    if (fuse) {
+      set_eval_args(c, e, n_all, p_fused, eps);
+      e.n_nodes = cells;
+      e.dev = true;
+      e.small_tree = true;
+      HIPCHK(c, hipEventRecord(c->fork, c->stream));
+      HIPCHK(c, hipStreamWaitEvent(c->side, c->fork, 0));
+      HIPCHK(c, launch_upward(c->t, e, c->side));
+      HIPCHK(c, hipEventRecord(c->up_done, c->side));
+    }
+    HIPCHK(c, launch_traverse_paths(c->t, a, cells, c->stream));
+    if (fuse) {
+      e.upward_done = true;
+      e.up_done = c->up_done;
+      e.plan = &a;
+      e.pin_hdr = c->pin_hdr;
+      e.hdr_ev = c->hdr_ev;
+      HIPCHK(c, launch_evaluate(c->t, e, c->stream));
+      HIPCHK(c, hipEventSynchronize(c->hdr_ev));
+      memcpy(&c->hh, c->pin_hdr, sizeof(Header));
+    } else {
+      HIPCHK(c, launch_p2p_plan(c->t, a, c->stream));
+      st = read_header(c);
+      if (st != FMM_OK) return st;
+    }
     if (c->hh.nonfinite) return fail(c, FMM_ENONFINITE, "non-finite input position");
     if (c->hh.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
-    if (!(c->hh.overflow & OVF_ANY)) return finish(tree_depth());
+    if (!(c->hh.overflow & OVF_ANY)) {
+      record_levels(c, std::min(FMM_MAXLEVEL, c->hh.max_prefix + 1));
+      st = finish(tree_depth());
+      if (st == FMM_OK && fuse) {
+        count_evaluation(c, n_req, reqs);
+        *evaluated = true;
+      }
+      return st;
+    }
   }
   // 1a. split levels predicted from recent builds: tree and walk queued behind
   // the sort, one readback.  The tree equals the one built below whenever the
@@ -485,12 +530,17 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, launch_traverse_paths(c->t, a, prev_nodes + prev_nodes / 4, c->stream));
     else
       HIPCHK(c, launch_traverse_dev(c->t, a, pred, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->pin_hdr, c->t.hdr, sizeof(Header), hipMemcpyDeviceToHost,
-                             c->stream));
-    HIPCHK(c, hipEventRecord(c->hdr_ev, c->stream));
-    if (fuse) {
+    if (!fuse) {
+      HIPCHK(c, launch_p2p_plan(c->t, a, c->stream));
+      HIPCHK(c, hipMemcpyAsync(c->pin_hdr, c->t.hdr, sizeof(Header), hipMemcpyDeviceToHost,
+                               c->stream));
+      HIPCHK(c, hipEventRecord(c->hdr_ev, c->stream));
+    } else {
       EvalArgs e = {};
       set_eval_args(c, e, n_all, p_fused, eps);
+      e.plan = &a;
+      e.pin_hdr = c->pin_hdr;
+      e.hdr_ev = c->hdr_ev;
       e.n_nodes = std::max(prev_nodes, 1);
       e.lvl_start_host = prev;
       e.depth = pred;
@@ -516,7 +566,6 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   // 1. tree; one readback of the level sizes (exact launches for the walk).
   // With the direct build the split depth need not be read first.
   int max_level = 0;
-  const bool direct = build_tree_direct_ok(a.leaf_size);
   for (int attempt = 0;; ++attempt) {
     if (attempt == 4) return fail(c, FMM_EOVERFLOW, "node workspace still too small");
     HIPCHK(c, launch_sort(c->t, a, c->stream));
@@ -574,13 +623,13 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, launch_traverse(c->t, a, c->stream));
     bool queued = false;
     if (up && evaluated && attempt == 0) {
-      // the header copy goes behind the walk, the evaluation behind it; the
-      // host waits for the copy only
-      HIPCHK(c, hipMemcpyAsync(c->pin_hdr, c->t.hdr, sizeof(Header), hipMemcpyDeviceToHost,
-                               c->stream));
-      HIPCHK(c, hipEventRecord(c->hdr_ev, c->stream));
+      // the header copy goes behind the walk and the near-field plan, on the
+      // side stream; the host waits for the copy only
       EvalArgs e = {};
       set_eval_args(c, e, n_all, p_fused, eps);
+      e.plan = &a;
+      e.pin_hdr = c->pin_hdr;
+      e.hdr_ev = c->hdr_ev;
       e.n_nodes = lvl[FMM_NLEVELS];
       e.lvl_start_host = lvl;
       e.depth = depth;
@@ -593,6 +642,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, hipEventSynchronize(c->hdr_ev));
       memcpy(&c->hh, c->pin_hdr, sizeof(Header));
     } else {
+      HIPCHK(c, launch_p2p_plan(c->t, a, c->stream));
       st = read_header(c);
       if (st != FMM_OK) return st;
     }

@@ -25,6 +25,8 @@
 #define SORT_TILE 4096       // keys per radix-sort tile (one histogram column)
 // single-workgroup ("small") build and level passes
 #define SMALL_N 1024                  // active particles of a batch built in one workgroup
+#define SMALL_TREE_LEAVES 400         // batches of at most this many times leaf_size particles
+                                      // are queued without reading the tree's size back
 #define SMALL_NODES 2048              // cells of a tree whose M2M / L2L levels run in one workgroup
 
 // error bits latched in Header::overflow
@@ -188,15 +190,19 @@ __device__ __forceinline__ int xcd_block(int b, int G) {
   return ((k / C) * FMM_XCDS + x) * C + k % C;
 }
 
+// Exclusive prefix sum over the wavefront (all 64 lanes active): within each row
+// of 16 lanes by row shifts, then lane 15 of rows 0 and 2 into the next row and
+// lane 31 into the upper half.  DPP moves: no LDS round trips (six lane
+// permutes had made this the longest step of a walk round beside its loads).
 __device__ __forceinline__ int wave_excl_scan_int(int v, int *total) {
-  // inclusive Hillis-Steele over 64 lanes
   int x = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    int y = __shfl_up(x, off, 64);
-    if (__lane_id() >= off) x += y;
-  }
-  *total = __shfl(x, 63, 64);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  *total = __builtin_amdgcn_readlane(x, 63);
   return x - v;
 }
 
@@ -291,6 +297,8 @@ hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels,
 // device; flags OVF_PATH when an open list is too long for it
 hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, hipStream_t s);
 hipError_t launch_reset_lists(const DevTree &t, hipStream_t s);
+// near-field work items of the walk's lists: needed by P2P and L2P only
+hipError_t launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s);
 // eval.hip
 struct EvalArgs {
   hipStream_t side;         // P2P runs here, concurrently with the multipole passes
@@ -316,6 +324,15 @@ struct EvalArgs {
   // stream, beside the walk); the main stream waits for up_done before M2L
   bool upward_done;
   hipEvent_t up_done;
+  // a tree of unknown but small size: M2M and L2L in one workgroup each, the
+  // levels read on the device
+  bool small_tree;
+  // queued behind the walk: the side stream plans the near field of this build
+  // before P2P and copies the header to pin_hdr (hdr_ev), so that neither
+  // delays the multipole passes
+  const BuildArgs *plan;
+  Header *pin_hdr;
+  hipEvent_t hdr_ev;
 };
 hipError_t launch_evaluate(const DevTree &t, const EvalArgs &e, hipStream_t s);
 // mass gather, P2M and M2M of an evaluation on stream s (exact tree sizes)

@@ -424,11 +424,19 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2l(DevTree t, int s, int e) {
 
 // Small trees: all M2M levels (deepest first) or all L2L levels (root first)
 // in one workgroup, a barrier between levels.
+__device__ __forceinline__ int tree_depth(const Header *h) {
+  int l = 0;
+  while (l < FMM_MAXLEVEL && h->lvl_start[l + 2] > h->lvl_start[l + 1]) ++l;
+  return l;
+}
+
+// depth < 0: read from the header
 template <typename T, int P>
 __global__ __launch_bounds__(FMM_BLOCK) void k_m2m_small(DevTree t, int depth, bool harm,
                                                          bool dev) {
   const Header *h = t.hdr;
   if (dev && tree_incomplete(t)) return;
+  if (depth < 0) depth = tree_depth(h);
   for (int l = depth - 1; l >= 0; --l) {
     for (int i = h->lvl_start[l] + (threadIdx.x >> 3); i < h->lvl_start[l + 1];
          i += blockDim.x >> 3)
@@ -441,6 +449,7 @@ template <typename T, int P>
 __global__ __launch_bounds__(FMM_BLOCK) void k_l2l_small(DevTree t, int depth, bool dev) {
   const Header *h = t.hdr;
   if (dev && tree_incomplete(t)) return;
+  if (depth < 0) depth = tree_depth(h);
   for (int l = 1; l <= depth; ++l) {
     for (int c = h->lvl_start[l] + threadIdx.x; c < h->lvl_start[l + 1]; c += blockDim.x)
       l2l_cell<T, P>(t, c);
@@ -479,12 +488,18 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2p(DevTree t, int n, bool dev, d
   if (ne > 0) {  // the near field's further shares, in share order
     const int b = t.nbeg[leaf], na = t.nend[leaf] - b;
     const double4 *row = t.part + t.part_off[leaf] + (j - b);
-    for (int k = 0; k < ne; ++k) {
-      const double4 v = row[(int64_t)k * na];
-      nx += v.x;
-      ny += v.y;
-      nz += v.z;
-      np += v.w;
+    for (int k = 0; k < ne; k += 4) {  // four loads in flight
+      double4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        v[u] = k + u < ne ? row[(int64_t)(k + u) * na] : make_double4(0, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        nx += v[u].x;
+        ny += v[u].y;
+        nz += v[u].z;
+        np += v[u].w;
+      }
     }
   }
   q.acc[i] = sgn * (nx - (double)gx * ih);
@@ -947,9 +962,9 @@ static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   const bool harm = KERNEL == 0;  // folded moments feed the harmonic M2L
   hipLaunchKernelGGL((k_p2m<T, P>), dim3((8 * ga + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, narg, harm);
-  if (nn <= SMALL_NODES && e.depth > 0) {
-    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t, e.depth, harm,
-                       e.dev);
+  if (e.small_tree || (nn <= SMALL_NODES && e.depth > 0)) {
+    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t,
+                       e.small_tree ? -1 : e.depth, harm, e.dev);
   } else {
     for (int l = e.depth - 1; l >= 0; --l) {
       int blocks, a0, a1;
@@ -974,6 +989,11 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   PhaseTimer *tm = e.tm;
   hipEventRecord(e.fork, s);
   hipStreamWaitEvent(e.side, e.fork, 0);
+  if (e.plan) {
+    launch_p2p_plan(t, *e.plan, e.side);
+    hipMemcpyAsync(e.pin_hdr, t.hdr, sizeof(Header), hipMemcpyDeviceToHost, e.side);
+    hipEventRecord(e.hdr_ev, e.side);
+  }
   const int tp = tm ? tm->begin(PH_P2P, e.side) : -1;
   const int p2p_blocks = (p2p_grid_items(e.n, ga) + P2P_WAVES - 1) / P2P_WAVES;
   if (e.eps > 0)
@@ -1000,8 +1020,9 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     tm->stop(s);
     tm->start(PH_DOWN, s);
   }
-  if (small && e.depth > 0) {
-    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t, e.depth, e.dev);
+  if (e.small_tree || (small && e.depth > 0)) {
+    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t,
+                       e.small_tree ? -1 : e.depth, e.dev);
   } else {
     for (int l = 1; l <= e.depth; ++l) {
       int blocks, a0, a1;

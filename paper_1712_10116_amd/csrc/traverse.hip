@@ -1172,7 +1172,8 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
   }
 }
 
-static void launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s) {
+hipError_t launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
   // a wavefront per cell where the systems are cut by windows (8 n / leaf_size
   // bounds the cells a context holds), a lane per cell where they are not: a
   // workgroup's items then follow 1024 cells in order, and so the XCDs' shares
@@ -1180,6 +1181,7 @@ static void launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s)
   const int npw = a.n_max > P2P_SHARE_FINE_N ? 64 : 1;
   const int blocks = (int)std::min<int64_t>(1024, (cells + npw * PLAN_WAVES - 1) / (npw * PLAN_WAVES));
   hipLaunchKernelGGL(k_p2p_plan, dim3(std::max(blocks, 1)), dim3(PLAN_WAVES * 64), 0, s, t, npw);
+  return hipGetLastError();
 }
 
 __global__ void k_reset_lists(Header *h) {
@@ -1208,7 +1210,6 @@ hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells
   if (a.tm) a.tm->start(PH_WALK, s);
   hipLaunchKernelGGL(k_walk_paths, dim3(std::max(cells, 1)), dim3(WALK_WAVES * 64), 0, s, t,
                      a.theta * a.theta, a.eps);
-  launch_p2p_plan(t, a, s);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }
@@ -1230,7 +1231,6 @@ hipError_t launch_traverse(const DevTree &t, const BuildArgs &a, hipStream_t s) 
       hipLaunchKernelGGL(k_walk_waves, dim3((nw + TRAV_WAVES - 1) / TRAV_WAVES),
                          dim3(TRAV_WAVES * 64), 0, s, t, l, ps, pe, th2, a.eps);
   }
-  launch_p2p_plan(t, a, s);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }
@@ -1246,7 +1246,6 @@ hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels,
   for (int l = 0; l <= levels && l <= FMM_MAXLEVEL; ++l)
     hipLaunchKernelGGL(k_walk_waves_dev, dim3(blocks), dim3(TRAV_WAVES * 64), 0, s, t, l, th2,
                        a.eps);
-  launch_p2p_plan(t, a, s);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();
 }

@@ -48,3 +48,23 @@ def test_lists_bit_exact(oracle, name):
         for k in ("perm", "begin", "end", "m2l", "p2p"):
             np.testing.assert_array_equal(ex[k], ref[k], err_msg=k)
     s.close()
+
+
+@pytest.mark.parametrize("n,leaf", [(900, 2), (1500, 4)])
+def test_small_tree_that_outgrows_its_lists(oracle, n, leaf):
+    """Solves queued without reading sizes back (one-workgroup build and small
+    tree) whose lists do not fit at first: redone on regrown buffers, and right
+    again when repeated."""
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    pos, _, m = W.uniform_sphere(n, seed=36)
+    ra, rp = oracle.fmm(pos, m, p=4, theta=0.5, eps=1.0, leaf_size=leaf, kernel=0)
+    s = F.Solver(n, p_max=4, leaf_size=leaf, kernel=0, precision=0)
+    tp, tm = torch.from_numpy(pos).cuda(), torch.from_numpy(m).cuda()
+    for _ in range(2):
+        a, pt = s.forces(tp, tm, eps=1.0, theta=0.5, p=4)
+        a, pt = a.cpu().numpy(), pt.cpu().numpy()
+        mag = np.sqrt((ra * ra).sum(0))
+        e = np.sqrt(((a - ra) ** 2).sum(0)) / np.maximum(mag, 1e-6 * np.sqrt((mag ** 2).mean()))
+        assert e.max() < 1e-12 and (np.abs(pt - rp) / np.abs(rp)).max() < 1e-12
+    s.close()

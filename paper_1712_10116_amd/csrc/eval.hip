@@ -57,15 +57,19 @@ __device__ __forceinline__ void store_folded(const DevTree &t, int node, const T
 }
 
 // a system whose mass pointer is NULL is skipped by this evaluation
+// (with one system, without waiting for the cell's system first)
+__device__ __forceinline__ const DevReq &request_of(const DevTree &t, int node) {
+  return t.reqs[t.n_req == 1 ? 0 : t.nreq[node]];
+}
 __device__ __forceinline__ bool skipped(const DevTree &t, int node) {
-  return t.reqs[t.nreq[node]].mass == nullptr;
+  return request_of(t, node).mass == nullptr;
 }
 
 // Whether leaf A (sorted particles bA .. bA+nA-1) holds a sink of its
 // system's evaluation; every one does when the system has no sink flags.
 // Called by a whole wavefront with A the same in every lane.
 __device__ __forceinline__ bool has_sink(const DevTree &t, int A, int bA, int nA) {
-  const DevReq &q = t.reqs[t.nreq[A]];
+  const DevReq &q = request_of(t, A);
   if (!q.sinks) return true;
   bool any = false;
   for (int j = bA + (int)(threadIdx.x & 63); j < bA + nA; j += 64)
@@ -423,17 +427,26 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2l(DevTree t, int s, int e) {
 }
 
 // Small trees: all M2M levels (deepest first) or all L2L levels (root first)
-// in one workgroup, a barrier between levels.
+// in one workgroup, a barrier between levels.  Latency bound: a level is one or
+// two rounds of dependent loads (cell, child, row), so the workgroup is as wide
+// as the coefficients' registers allow (8 wavefronts up to 256 registers).
+// 4 -> 8 wavefronts, mean us: M2M of 12,526 particles, p 4, mixed, 40 -> 29, of
+// 4096, p 4, FP64, 61 -> 44; L2L 22 -> 20 and 32 -> 32.
 __device__ __forceinline__ int tree_depth(const Header *h) {
   int l = 0;
   while (l < FMM_MAXLEVEL && h->lvl_start[l + 2] > h->lvl_start[l + 1]) ++l;
   return l;
 }
 
+template <typename T, int P>
+constexpr int small_threads() {
+  return MI<P>::K * sizeof(T) <= 280 ? 2 * FMM_BLOCK : FMM_BLOCK;
+}
+
 // depth < 0: read from the header
 template <typename T, int P>
-__global__ __launch_bounds__(FMM_BLOCK) void k_m2m_small(DevTree t, int depth, bool harm,
-                                                         bool dev) {
+__global__ __launch_bounds__((small_threads<T, P>())) void k_m2m_small(DevTree t, int depth,
+                                                                       bool harm, bool dev) {
   const Header *h = t.hdr;
   if (dev && tree_incomplete(t)) return;
   if (depth < 0) depth = tree_depth(h);
@@ -446,7 +459,8 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_m2m_small(DevTree t, int depth, b
 }
 
 template <typename T, int P>
-__global__ __launch_bounds__(FMM_BLOCK) void k_l2l_small(DevTree t, int depth, bool dev) {
+__global__ __launch_bounds__((small_threads<T, P>())) void k_l2l_small(DevTree t, int depth,
+                                                                       bool dev) {
   const Header *h = t.hdr;
   if (dev && tree_incomplete(t)) return;
   if (depth < 0) depth = tree_depth(h);
@@ -963,7 +977,7 @@ static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   hipLaunchKernelGGL((k_p2m<T, P>), dim3((8 * ga + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, narg, harm);
   if (e.small_tree || (nn <= SMALL_NODES && e.depth > 0)) {
-    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t,
+    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t,
                        e.small_tree ? -1 : e.depth, harm, e.dev);
   } else {
     for (int l = e.depth - 1; l >= 0; --l) {
@@ -1021,7 +1035,7 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     tm->start(PH_DOWN, s);
   }
   if (e.small_tree || (small && e.depth > 0)) {
-    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t,
+    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t,
                        e.small_tree ? -1 : e.depth, e.dev);
   } else {
     for (int l = 1; l <= e.depth; ++l) {
@@ -1110,7 +1124,8 @@ static void run_dipole(const DevTree &t, const EvalArgs &e, const double *vec, d
   hipLaunchKernelGGL((k_p2m_dip<T, P>), dim3((8 * nn + FMM_BLOCK - 1) / FMM_BLOCK),
                      dim3(FMM_BLOCK), 0, s, t, nn, (const double *)dv, harm);
   if (nn <= SMALL_NODES && e.depth > 0) {
-    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t, e.depth, harm,
+    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t, e.depth,
+                       harm,
                        false);
   } else {
     for (int l = e.depth - 1; l >= 0; --l) {
@@ -1123,7 +1138,8 @@ static void run_dipole(const DevTree &t, const EvalArgs &e, const double *vec, d
   hipLaunchKernelGGL((k_m2l<T, P, KERNEL>), dim3((nn + 3) / 4), dim3(FMM_BLOCK), 0, s, t, nn,
                      e.eps);
   if (nn <= SMALL_NODES && e.depth > 0) {
-    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(FMM_BLOCK), 0, s, t, e.depth, false);
+    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t, e.depth,
+                       false);
   } else {
     for (int l = 1; l <= e.depth; ++l) {
       int blocks, a0, a1;

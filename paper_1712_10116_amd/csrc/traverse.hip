@@ -1028,7 +1028,7 @@ __device__ __forceinline__ void emit_whole_chunks(const DevTree &t, int A, int n
                   k ? (int32_t)(r0 + (int64_t)(k - 1) * nA) : -1};
 }
 
-#define PLAN_WAVES 16
+#define PLAN_WAVES 4
 #define PLAN_CHUNKS 256  // window counts of list chunks a wavefront keeps
 
 // Source windows of the four chunks of 64 list entries from qb on, summed over

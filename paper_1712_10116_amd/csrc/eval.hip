@@ -579,8 +579,7 @@ struct PairKernel {
 // of UNROLL sources.
 #define P2P_WAVES 1
 #define P2P_XCD_CHUNK 128  // items per XCD chunk
-#define P2P_UNROLL 8
-#define P2P_MAXPH 16  // at most 16 phases, so a window pads to a multiple of 128
+#define P2P_MAXPH 16  // at most 16 phases, a window pads to a multiple of UNROLL times that
 
 template <bool MIXED>
 struct P2PTypes;
@@ -588,13 +587,20 @@ template <>
 struct P2PTypes<true> {
   typedef float R;
   typedef float4 R4;
-  static constexpr int SRC = 384;  // multiple of P2P_UNROLL * P2P_MAXPH
+  static constexpr int UNROLL = 8;
+  static constexpr int SRC = 384;  // multiple of UNROLL * P2P_MAXPH
   __device__ static R4 far() { return make_float4(1e15f, 1e15f, 1e15f, 0.f); }
 };
 template <>
 struct P2PTypes<false> {
   typedef double R;
   typedef double4 R4;
+  // Bound by FP64 issue once enough wavefronts cover the LDS reads.  8 sources
+  // at a time take 205 registers (2 wavefronts per SIMD), 4 take 148 (3); with
+  // the five-operation rsqrt, p2p of 100,003 particles (leaf 40), beside the
+  // M2L: 221 -> 207 -> 195 us, of 300,007 586 -> 561 -> 510 (VALU issuing 74-80%
+  // of the time).
+  static constexpr int UNROLL = 4;
   static constexpr int SRC = 256;
   __device__ static R4 far() { return make_double4(1e150, 1e150, 1e150, 0.0); }
 };
@@ -609,14 +615,15 @@ template <typename R, typename R4, int KERNEL, bool SELF, int NPH>
 __device__ __forceinline__ void p2p_block(const R4 *src, int f0, int self_idx, R xi, R yi, R zi,
                                           R eps2, R inv_eps, R inv_eps3, R &sx, R &sy, R &sz,
                                           R &sp) {
+  constexpr int U = P2PTypes<sizeof(R) == 4>::UNROLL;
   if (KERNEL == 0) {
-    R dx[P2P_UNROLL], dy[P2P_UNROLL], dz[P2P_UNROLL], r2[P2P_UNROLL], mj[P2P_UNROLL];
+    R dx[U], dy[U], dz[U], r2[U], mj[U];
     {
-      R4 svs[P2P_UNROLL];  // the block's sources, read before any use
+      R4 svs[U];  // the block's sources, read before any use
 #pragma unroll
-      for (int u = 0; u < P2P_UNROLL; ++u) svs[u] = src[f0 + u * NPH];
+      for (int u = 0; u < U; ++u) svs[u] = src[f0 + u * NPH];
 #pragma unroll
-      for (int u = 0; u < P2P_UNROLL; ++u) {
+      for (int u = 0; u < U; ++u) {
         dx[u] = svs[u].x - xi;
         dy[u] = svs[u].y - yi;
         dz[u] = svs[u].z - zi;
@@ -631,10 +638,10 @@ __device__ __forceinline__ void p2p_block(const R4 *src, int f0, int self_idx, R
     }
     R rmin = r2[0];
 #pragma unroll
-    for (int u = 1; u < P2P_UNROLL; ++u) rmin = fmin(rmin, r2[u]);
+    for (int u = 1; u < U; ++u) rmin = fmin(rmin, r2[u]);
     if (__ballot(rmin < eps2) == 0ull) {
 #pragma unroll
-      for (int u = 0; u < P2P_UNROLL; ++u) {
+      for (int u = 0; u < U; ++u) {
         const R rinv = fast_rsqrt<R>(r2[u]);
         const R t = mj[u] * rinv;
         const R mg = t * (rinv * rinv);
@@ -648,7 +655,7 @@ __device__ __forceinline__ void p2p_block(const R4 *src, int f0, int self_idx, R
     // a pair of the wavefront lies inside the radius: every pair of the block
     // through PairKernel, on the differences already formed
 #pragma unroll
-    for (int u = 0; u < P2P_UNROLL; ++u) {
+    for (int u = 0; u < U; ++u) {
       R mg, tp;
       PairKernel<R, KERNEL>::eval(r2[u], mj[u], eps2, inv_eps, inv_eps3, mg, tp);
       sx = fma(mg, dx[u], sx);
@@ -659,11 +666,11 @@ __device__ __forceinline__ void p2p_block(const R4 *src, int f0, int self_idx, R
     return;
   }
   // Plummer: every pair through PairKernel
-  R4 svs[P2P_UNROLL];
+  R4 svs[U];
 #pragma unroll
-  for (int u = 0; u < P2P_UNROLL; ++u) svs[u] = src[f0 + u * NPH];
+  for (int u = 0; u < U; ++u) svs[u] = src[f0 + u * NPH];
 #pragma unroll
-  for (int u = 0; u < P2P_UNROLL; ++u) {
+  for (int u = 0; u < U; ++u) {
     const R4 sv = svs[u];
     const R dx = sv.x - xi, dy = sv.y - yi, dz = sv.z - zi;
     R r2 = fma(dx, dx, fma(dy, dy, dz * dz));
@@ -688,7 +695,7 @@ template <typename R, typename R4, int KERNEL, bool SELF, int NPH>
 __device__ __forceinline__ void p2p_window(const R4 *src, int ph, int Wr, int self_idx, R xi,
                                            R yi, R zi, R eps2, R inv_eps, R inv_eps3, double &bx,
                                            double &by, double &bz, double &bp) {
-  constexpr int B = P2P_UNROLL * NPH;  // slots per block of all phases
+  constexpr int B = P2PTypes<sizeof(R) == 4>::UNROLL * NPH;  // slots per block of all phases
   int f0 = ph;
   // two blocks per update of the FP64 sums, then the odd block if any
   for (; f0 + B < Wr; f0 += 2 * B) {
@@ -778,11 +785,12 @@ __device__ __forceinline__ int p2p_lanes_log2(int ns) {
 // zero (dx = 0) -- and its potential term, reproduced bit for bit, is taken
 // off once per sink.
 template <bool MIXED, int KERNEL, bool SELF>
-__global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t, double eps) {
+__global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 3) void k_p2p(DevTree t, double eps) {
   typedef typename P2PTypes<MIXED>::R R;
   typedef typename P2PTypes<MIXED>::R4 R4;
   constexpr int SRC = P2PTypes<MIXED>::SRC;
-  static_assert(SRC % (P2P_UNROLL * P2P_MAXPH) == 0, "window must hold its padding");
+  constexpr int UNROLL = P2PTypes<MIXED>::UNROLL;
+  static_assert(SRC % (UNROLL * P2P_MAXPH) == 0, "window must hold its padding");
   __shared__ R4 src_all[P2P_WAVES][SRC];
   __shared__ int3 leaf_all[P2P_WAVES][64];  // per list entry of a chunk: stream position, size, first particle
   __shared__ R sink_all[P2P_WAVES][3][64];  // home sink position of each lane
@@ -817,7 +825,7 @@ __global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 2) void k_p2p(DevTree t
       const int nph = 64 >> lg;                // phases
       const int passes = (ns + LP - 1) >> lg;
       const int ti = lane >> (6 - lg), ph = lane & (nph - 1);
-      const int blk = P2P_UNROLL * nph;        // slots per unrolled block of all phases
+      const int blk = UNROLL * nph;        // slots per unrolled block of all phases
       // home sink of this lane: with one pass sink ti (summed at the end,
       // written by phase 0), else sink ph * LP + ti
       const int hs = passes > 1 ? ph * LP + ti : ti;

@@ -80,12 +80,14 @@ __device__ __forceinline__ float fast_rsqrt<float>(float s) {
 }
 template <>
 __device__ __forceinline__ double fast_rsqrt<double>(double s) {
-  // hardware estimate refined by two Newton steps to full double accuracy
-  double y = __builtin_amdgcn_rsq(s);
-  double hs = 0.5 * s;
-  y = y * fma(-hs * y, y, 1.5);
-  y = y * fma(-hs * y, y, 1.5);
-  return y;
+  // hardware estimate (relative error up to 5.2e-8) refined by one third-order
+  // step, 1/sqrt(1 - e) = 1 + e/2 + 3 e^2/8 + O(e^3) with e = 1 - s y^2: five
+  // operations instead of seven, and the last is a correction added to y.  Over
+  // 2^-40 .. 2^40 max / rms relative error 1.4e-16 / 5.3e-17 (two Newton steps:
+  // 2.4e-16 / 7.3e-17).  0 and infinity give NaN, as the Newton steps did.
+  const double y = __builtin_amdgcn_rsq(s);
+  const double e = fma(-(s * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
 // D[t] = d^{k_t} psi / dR^{k_t}, psi = -(|R|^2 + e2)^(-1/2), for the k_t with

@@ -152,7 +152,7 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
     return FMM_ENOMEM;
   }
   t.kmax = coeffs(prm->p_max);
-  t.khmax = (prm->p_max + 1) * (prm->p_max + 1);
+  t.khmax = ((prm->p_max + 1) * (prm->p_max + 1) + 1) & ~1;  // even: rows read in pairs
   t.cap_n = max_n;
   int64_t n = max_n;
   int64_t cap_nodes = 8 * n / prm->leaf_size + 1024;

@@ -18,6 +18,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 template <int P>
 struct MI {
   static constexpr int K = (P + 1) * (P + 2) * (P + 3) / 6;
@@ -135,6 +137,79 @@ __device__ __forceinline__ void derivatives(T X, T Y, T Z, T e2, T (&D)[MI<P>::K
 #pragma unroll
   for (int t = 0; t < K; ++t)
     if (mi.z[t] <= ZMAX) D[t] = Rn[0][t];
+}
+
+// The same in FP64 for the M2L that stages its source rows, with fewer
+// operations and registers: degrees taken downwards, so that level n overwrites
+// level n + 1 in place, and each tensor raised along the axis that needs least
+// (index 1: a product; 2: one fused multiply-add).
+template <int P, int ZMAX>
+struct RaiseOps {  // D[t] = C_ax D[lo] + f D[lo2] (f = 0: no second term; ax < 0: G[n])
+  static constexpr int N = 2 * MI<P>::K * P;
+  int t[N], ax[N], lo[N], lo2[N], f[N], count;
+  constexpr RaiseOps() : t(), ax(), lo(), lo2(), f(), count() {
+    constexpr MI<P> mi{};
+    int c = 0;
+    for (int n = P; n >= 0; --n)
+      for (int i = MI<P>::K - 1; i >= 0; --i) {
+        if (mi.deg[i] > P - n || mi.z[i] > ZMAX) continue;
+        t[c] = i;
+        ax[c] = -1;
+        lo[c] = n;
+        if (mi.deg[i] > 0) {
+          const int k[3] = {mi.x[i], mi.y[i], mi.z[i]};
+          int a = -1;
+          for (int b = 0; b < 3; ++b)
+            if (k[b] > 0 && (a < 0 || k[b] < k[a])) a = b;
+          ax[c] = a;
+          lo[c] = mi.at(k[0] - (a == 0), k[1] - (a == 1), k[2] - (a == 2));
+          f[c] = k[a] - 1;
+          if (f[c] > 0)
+            lo2[c] = mi.at(k[0] - 2 * (a == 0), k[1] - 2 * (a == 1), k[2] - 2 * (a == 2));
+        }
+        ++c;
+      }
+    count = c;
+  }
+};
+
+template <int P, int ZMAX>
+inline constexpr RaiseOps<P, ZMAX> raise_op_list{};
+
+template <int P, int ZMAX, int C>
+__device__ __forceinline__ void raise_op(const double (&R)[3], const double (&G)[P + 1],
+                                         double (&D)[MI<P>::K]) {
+  constexpr const RaiseOps<P, ZMAX> &ops = raise_op_list<P, ZMAX>;
+  constexpr int t = ops.t[C], ax = ops.ax[C], lo = ops.lo[C], lo2 = ops.lo2[C], f = ops.f[C];
+  if constexpr (ax < 0)
+    D[t] = G[lo];
+  else if constexpr (f == 0)
+    D[t] = R[ax] * D[lo];
+  else if constexpr (f == 1)
+    D[t] = fma(R[ax], D[lo], D[lo2]);
+  else
+    D[t] = fma(R[ax], D[lo], (double)f * D[lo2]);
+}
+
+template <int P, int ZMAX, int... C>
+__device__ __forceinline__ void raise_ops(std::integer_sequence<int, C...>, const double (&R)[3],
+                                          const double (&G)[P + 1], double (&D)[MI<P>::K]) {
+  const int done[] = {(raise_op<P, ZMAX, C>(R, G, D), 0)...};
+  (void)done;
+}
+
+template <int P, int ZMAX>
+__device__ __forceinline__ void derivatives_in_place(double X, double Y, double Z, double e2,
+                                                     double (&D)[MI<P>::K]) {
+  const double s = fma(X, X, fma(Y, Y, fma(Z, Z, e2)));
+  const double rinv = fast_rsqrt<double>(s);
+  const double sinv = rinv * rinv;
+  const double R[3] = {X, Y, Z};
+  double G[P + 1];
+  G[0] = -rinv;
+#pragma unroll
+  for (int n = 0; n < P; ++n) G[n + 1] = (double)(-(2 * n + 1)) * G[n] * sinv;
+  raise_ops<P, ZMAX>(std::make_integer_sequence<int, raise_op_list<P, ZMAX>.count>{}, R, G, D);
 }
 
 // Compile-time term lists: only the (n, m) index pairs that occur, so every

@@ -441,10 +441,12 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2l(DevTree t, int s, int e) {
     l2l_cell<T, P>(t, c);
 }
 
-// Small trees: all M2M levels (deepest first) or all L2L levels (root first)
-// in one workgroup, a barrier between levels.  Latency bound: a level is one or
-// two rounds of dependent loads (cell, child, row), so the workgroup is as wide
-// as the coefficients' registers allow (8 wavefronts up to 256 registers).
+// Several levels in one workgroup, a barrier between them: M2M into the cells of
+// levels hi .. lo (deepest first), L2L to those of levels lo .. hi; all levels of
+// a small tree, or a run of consecutive levels of few cells (level_run).
+// Latency bound: a level is one or two rounds of dependent loads (cell, child,
+// row), so the workgroup is as wide as the coefficients' registers allow (8
+// wavefronts up to 256 registers).
 // 4 -> 8 wavefronts, mean us: M2M of 12,526 particles, p 4, mixed, 40 -> 29, of
 // 4096, p 4, FP64, 61 -> 44; L2L 22 -> 20 and 32 -> 32.
 __device__ __forceinline__ int tree_depth(const Header *h) {
@@ -458,14 +460,14 @@ constexpr int small_threads() {
   return MI<P>::K * sizeof(T) <= 280 ? 2 * FMM_BLOCK : FMM_BLOCK;
 }
 
-// depth < 0: read from the header
+// hi < 0: the tree's last, read from the header
 template <typename T, int P>
-__global__ __launch_bounds__((small_threads<T, P>())) void k_m2m_small(DevTree t, int depth,
+__global__ __launch_bounds__((small_threads<T, P>())) void k_m2m_small(DevTree t, int lo, int hi,
                                                                        bool harm, bool dev) {
   const Header *h = t.hdr;
   if (dev && tree_incomplete(t)) return;
-  if (depth < 0) depth = tree_depth(h);
-  for (int l = depth - 1; l >= 0; --l) {
+  if (hi < 0) hi = tree_depth(h) - 1;
+  for (int l = hi; l >= lo; --l) {
     for (int i = h->lvl_start[l] + (threadIdx.x >> 3); i < h->lvl_start[l + 1];
          i += blockDim.x >> 3)
       m2m_cell8<T, P>(t, i, threadIdx.x & 7, harm);
@@ -474,12 +476,12 @@ __global__ __launch_bounds__((small_threads<T, P>())) void k_m2m_small(DevTree t
 }
 
 template <typename T, int P>
-__global__ __launch_bounds__((small_threads<T, P>())) void k_l2l_small(DevTree t, int depth,
+__global__ __launch_bounds__((small_threads<T, P>())) void k_l2l_small(DevTree t, int lo, int hi,
                                                                        bool dev) {
   const Header *h = t.hdr;
   if (dev && tree_incomplete(t)) return;
-  if (depth < 0) depth = tree_depth(h);
-  for (int l = 1; l <= depth; ++l) {
+  if (hi < 0) hi = tree_depth(h);
+  for (int l = lo; l <= hi; ++l) {
     for (int c = h->lvl_start[l] + threadIdx.x; c < h->lvl_start[l + 1]; c += blockDim.x)
       l2l_cell<T, P>(t, c);
     __syncthreads();
@@ -990,6 +992,67 @@ static void level_launch(const EvalArgs &e, int l, int per_cell, int &blocks, in
   }
 }
 
+// Levels from l on (in steps of step, within lo .. hi) of at most `width` cells:
+// one workgroup takes them in turn instead of a launch each.  Width: a level that
+// one round of the workgroup covers; a wider one is faster on many workgroups.
+// us per level, p 6, 300,007 particles, FP64: M2M 9 in a run, 14 a launch; L2L 6
+// and 17 (solve 1205 -> 1186; 131,073 of 2^20 kicked, mixed, 719 -> 703).
+static int level_run(const EvalArgs &e, int l, int step, int lo, int hi, int width) {
+  int n = 0;
+  for (; l >= lo && l <= hi && e.lvl_start_host[l + 1] - e.lvl_start_host[l] <= width; l += step)
+    ++n;
+  return n;
+}
+
+// M2M into, or L2L to, all levels of the tree.
+template <typename T, int P>
+static void run_m2m(const DevTree &t, const EvalArgs &e, bool harm, hipStream_t s) {
+  constexpr int threads = small_threads<T, P>();
+  if (e.small_tree || (e.n_nodes <= SMALL_NODES && e.depth > 0)) {
+    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(threads), 0, s, t, 0,
+                       e.small_tree ? -1 : e.depth - 1, harm, e.dev);
+    return;
+  }
+  for (int l = e.depth - 1; l >= 0;) {
+    const int run = level_run(e, l, -1, 0, e.depth - 1, threads / 8);
+    if (run > 1) {
+      hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(threads), 0, s, t, l - run + 1, l,
+                         harm, e.dev);
+      l -= run;
+      continue;
+    }
+    int blocks, a0, a1;
+    level_launch(e, l, 8, blocks, a0, a1);
+    if (blocks > 0)
+      hipLaunchKernelGGL((k_m2m<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1, harm);
+    --l;
+  }
+}
+
+template <typename T, int P>
+static void run_l2l(const DevTree &t, const EvalArgs &e, hipStream_t s) {
+  constexpr int threads = small_threads<T, P>();
+  if (e.small_tree || (e.n_nodes <= SMALL_NODES && e.depth > 0)) {
+    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(threads), 0, s, t, 1,
+                       e.small_tree ? -1 : e.depth, e.dev);
+    return;
+  }
+  for (int l = 1; l <= e.depth;) {
+    const int run = level_run(e, l, 1, 1, e.depth, threads);
+    if (run > 1) {
+      hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(threads), 0, s, t, l, l + run - 1,
+                         e.dev);
+      l += run;
+      continue;
+    }
+    int blocks, a0, a1;
+    level_launch(e, l, 1, blocks, a0, a1);
+    if (blocks > 0)
+      hipLaunchKernelGGL((k_l2l<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1);
+    ++l;
+  }
+}
+
 // Upward pass: P2M and M2M (far-field cell kernels: 8 lanes per cell).
 template <typename T, int P, int KERNEL>
 static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
@@ -999,17 +1062,7 @@ static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   const bool harm = KERNEL == 0;  // folded moments feed the harmonic M2L
   hipLaunchKernelGGL((k_p2m<T, P>), dim3((8 * ga + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, narg, harm);
-  if (e.small_tree || (nn <= SMALL_NODES && e.depth > 0)) {
-    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t,
-                       e.small_tree ? -1 : e.depth, harm, e.dev);
-  } else {
-    for (int l = e.depth - 1; l >= 0; --l) {
-      int blocks, a0, a1;
-      level_launch(e, l, 8, blocks, a0, a1);
-      if (blocks > 0)
-        hipLaunchKernelGGL((k_m2m<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1, harm);
-    }
-  }
+  run_m2m<T, P>(t, e, harm, s);
 }
 
 // Launch order: P2P goes to the side stream (after the walk and the mass
@@ -1045,7 +1098,6 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     hipStreamWaitEvent(s, e.up_done, 0);  // P2M / M2M ran beside the walk
   else
     run_upward<T, P, KERNEL>(t, e, s);
-  const bool small = nn <= SMALL_NODES;
   if (tm) {
     tm->stop(s);
     tm->start(PH_M2L, s);
@@ -1055,17 +1107,7 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     tm->stop(s);
     tm->start(PH_DOWN, s);
   }
-  if (e.small_tree || (small && e.depth > 0)) {
-    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t,
-                       e.small_tree ? -1 : e.depth, e.dev);
-  } else {
-    for (int l = 1; l <= e.depth; ++l) {
-      int blocks, a0, a1;
-      level_launch(e, l, 1, blocks, a0, a1);
-      if (blocks > 0)
-        hipLaunchKernelGGL((k_l2l<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1);
-    }
-  }
+  run_l2l<T, P>(t, e, s);
   hipStreamWaitEvent(s, e.join, 0);
   hipLaunchKernelGGL((k_l2p<T, P>), dim3((e.n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, e.n, e.dev, 1.0);
@@ -1144,30 +1186,9 @@ static void run_dipole(const DevTree &t, const EvalArgs &e, const double *vec, d
                      t, e.n, vec, dv);
   hipLaunchKernelGGL((k_p2m_dip<T, P>), dim3((8 * nn + FMM_BLOCK - 1) / FMM_BLOCK),
                      dim3(FMM_BLOCK), 0, s, t, nn, (const double *)dv, harm);
-  if (nn <= SMALL_NODES && e.depth > 0) {
-    hipLaunchKernelGGL((k_m2m_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t, e.depth,
-                       harm,
-                       false);
-  } else {
-    for (int l = e.depth - 1; l >= 0; --l) {
-      int blocks, a0, a1;
-      level_launch(e, l, 8, blocks, a0, a1);
-      if (blocks > 0)
-        hipLaunchKernelGGL((k_m2m<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1, harm);
-    }
-  }
+  run_m2m<T, P>(t, e, harm, s);
   launch_m2l<T, P, KERNEL>(t, nn, nn, e.eps, s);
-  if (nn <= SMALL_NODES && e.depth > 0) {
-    hipLaunchKernelGGL((k_l2l_small<T, P>), dim3(1), dim3(small_threads<T, P>()), 0, s, t, e.depth,
-                       false);
-  } else {
-    for (int l = 1; l <= e.depth; ++l) {
-      int blocks, a0, a1;
-      level_launch(e, l, 1, blocks, a0, a1);
-      if (blocks > 0)
-        hipLaunchKernelGGL((k_l2l<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1);
-    }
-  }
+  run_l2l<T, P>(t, e, s);
   launch_p2p_dipole(t, nn, e.n, e.kernel, sizeof(T) == 4, e.eps, dv, s);
   hipLaunchKernelGGL((k_l2p<T, P>), dim3((e.n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, e.n, false, -1.0);

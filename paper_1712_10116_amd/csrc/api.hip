@@ -12,6 +12,7 @@
 #include <algorithm>
 #include <cmath>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/fmm355.h"
@@ -51,37 +52,47 @@ void fmm_dfree(fmm_ctx *c, void *p) {
   (void)hipFree(p);
 }
 
-// node-sized arrays
+// Places several arrays in one device allocation: each costs the driver 5 to 10 us
+// whatever its size, and a context has some forty.  place() is called with a
+// Placer twice, for the size (a null base) and for the addresses.
+struct Placer {
+  char *base = nullptr;
+  size_t at = 0;
+  template <typename T>
+  void operator()(T *&p, size_t count, size_t bytes = 0) {  // bytes: of an element, if T is void
+    if constexpr (!std::is_void<T>::value) bytes = sizeof(T);
+    p = (T *)(base + at);
+    at += (count * bytes + 255) & ~(size_t)255;
+  }
+};
+
+template <typename F>
+static bool dalloc_block(fmm_ctx *c, F place) {
+  Placer size, block;
+  place(size);
+  if (!dalloc(c, &block.base, (int64_t)size.at)) return false;
+  place(block);
+  return true;
+}
+
+// node-sized arrays (nbeg first: free_nodes)
 static bool alloc_nodes(fmm_ctx *c, int64_t cap) {
   DevTree &t = c->t;
   if (cap >= ((int64_t)1 << 28)) return false;  // node ids carry a 3-bit tag in the walk
-  t.cap_nodes = cap;
-  size_t real = c->prm.precision == FMM_PREC_MIXED ? sizeof(float) : sizeof(double);
-  bool ok = dalloc(c, &t.nbeg, cap) && dalloc(c, &t.nend, cap) && dalloc(c, &t.nlev, cap) &&
-            dalloc(c, &t.nparent, cap) && dalloc(c, &t.nchild0, cap) &&
-            dalloc(c, &t.nnchild, cap) && dalloc(c, &t.ngeo, cap) &&
-            dalloc(c, &t.bounds, cap * 8) && dalloc(c, &t.m2l_off, cap) &&
-            dalloc(c, &t.m2l_cnt, cap) && dalloc(c, &t.p2p_off, cap) &&
-            dalloc(c, &t.p2p_cnt, cap) && dalloc(c, &t.open_off, cap) &&
-            dalloc(c, &t.open_cnt, cap) && dalloc(c, &t.nreq, cap) &&
-            dalloc(c, &t.ninfo, cap) && dalloc(c, &t.nshare, cap) && dalloc(c, &t.part_off, cap);
-  if (!ok) return false;
-  char *m = nullptr, *l = nullptr, *mh = nullptr;
-  ok = dalloc(c, &m, (int64_t)(cap * t.kmax * real)) && dalloc(c, &l, (int64_t)(cap * t.kmax * real)) &&
-       dalloc(c, &mh, (int64_t)(cap * t.khmax * real));
-  t.M = m;
-  t.L = l;
-  t.Mh = mh;
+  const size_t n = (size_t)cap;
+  const size_t real = c->prm.precision == FMM_PREC_MIXED ? sizeof(float) : sizeof(double);
+  const bool ok = dalloc_block(c, [&](Placer &at) {
+    at(t.nbeg, n), at(t.nend, n), at(t.nlev, n), at(t.nparent, n), at(t.nchild0, n);
+    at(t.nnchild, n), at(t.ngeo, n), at(t.bounds, 8 * n), at(t.m2l_off, n), at(t.m2l_cnt, n);
+    at(t.p2p_off, n), at(t.p2p_cnt, n), at(t.open_off, n), at(t.open_cnt, n), at(t.nreq, n);
+    at(t.ninfo, n), at(t.nshare, n), at(t.part_off, n);
+    at(t.M, n * t.kmax, real), at(t.L, n * t.kmax, real), at(t.Mh, n * t.khmax, real);
+  });
+  t.cap_nodes = ok ? cap : 0;
   return ok;
 }
 
-static void free_nodes(fmm_ctx *c) {
-  DevTree &t = c->t;
-  void *ptrs[] = {t.nbeg, t.nend, t.nlev, t.nparent, t.nchild0, t.nnchild, t.ngeo, t.bounds,
-                  t.m2l_off, t.m2l_cnt, t.p2p_off, t.p2p_cnt, t.open_off, t.open_cnt, t.M, t.L,
-                  t.Mh, t.nreq, t.ninfo, t.nshare, t.part_off};
-  for (void *p : ptrs) dfree(c, p);
-}
+static void free_nodes(fmm_ctx *c) { dfree(c, c->t.nbeg); }
 
 // Request-sized arrays (regrown when a batch holds more requests).  The
 // request table, its particle offsets and its block offsets share one device
@@ -160,14 +171,12 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
   // of the tree build
   const int64_t sort_tiles = (n + SORT_TILE - 1) / SORT_TILE;
   const int64_t sort_hist_n = std::max<int64_t>(256 * sort_tiles, FMM_MAXLEVEL * ((n + 1023) / 1024)) + 256;
-  bool ok = dalloc(c, &t.key, n) && dalloc(c, &t.key2, n) && dalloc(c, &t.slot, n) &&
-            dalloc(c, &t.slot2, n) && dalloc(c, &t.sx, n) && dalloc(c, &t.sy, n) &&
-            dalloc(c, &t.sz, n) && dalloc(c, &t.sm, n) && dalloc(c, &t.sm32, n) &&
-            dalloc(c, &t.leaf_of, n) && dalloc(c, &t.near, 4 * n) && dalloc(c, &t.pak, n) &&
-            dalloc(c, &t.scan_part, FMM_SCAN_BLOCKS) && dalloc(c, &t.slot_req, n) &&
-            dalloc(c, &t.sort_hist, sort_hist_n) &&
-            dalloc(c, &t.sort_dtot, 256) && dalloc(c, &t.scan_blk, n / 1024 + 64) &&
-            dalloc(c, &t.hdr, 1) && alloc_reqs(c, 16) && alloc_nodes(c, cap_nodes);
+  bool ok = dalloc_block(c, [&](Placer &at) {
+    at(t.key, n), at(t.key2, n), at(t.slot, n), at(t.slot2, n), at(t.sx, n), at(t.sy, n);
+    at(t.sz, n), at(t.sm, n), at(t.sm32, n), at(t.leaf_of, n), at(t.near, 4 * n), at(t.pak, n);
+    at(t.scan_part, FMM_SCAN_BLOCKS), at(t.slot_req, n), at(t.sort_hist, sort_hist_n);
+    at(t.sort_dtot, 256), at(t.scan_blk, n / 1024 + 64), at(t.hdr, 1);
+  }) && alloc_reqs(c, 16) && alloc_nodes(c, cap_nodes);
   if (ok) {
     t.cap_m2l = 96 * cap_nodes;
     t.cap_p2p = 32 * cap_nodes;
@@ -409,6 +418,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   if (!(theta > 0.0) || !(eps >= 0.0) || !std::isfinite(theta) || !std::isfinite(eps))
     return fail(c, FMM_EINVAL, "need theta > 0 and eps >= 0");
   c->tree_valid = false;
+  if (c->t.cap_nodes < 1) return fail(c, FMM_ENOMEM, "no node workspace");
   int n_blk = 0;
   st = upload_requests(c, n_req, reqs, &n_blk);
   if (st != FMM_OK) return st;
@@ -584,9 +594,12 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     int64_t need = std::max<int64_t>(std::max<int64_t>((int64_t)c->hh.lvl_start[FMM_NLEVELS],
                                                        n_req),
                                      2 * c->t.cap_nodes);
+    const int64_t old = c->t.cap_nodes;
     free_nodes(c);
-    if (!alloc_nodes(c, need + need / 4))
+    if (!alloc_nodes(c, need + need / 4)) {
+      (void)alloc_nodes(c, old);  // as it was, for later builds
       return fail(c, FMM_ENOMEM, "node workspace regrow to %lld failed", (long long)need);
+    }
   }
   const int depth = tree_depth();
   int32_t lvl[FMM_NLEVELS + 2];

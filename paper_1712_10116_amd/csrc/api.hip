@@ -184,8 +184,8 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
     // near-field items and partial rows: small systems are cut fine (up to a
     // share per window), large ones only at long lists
     t.p2p_src_window = p2p_window_sources(prm->precision == FMM_PREC_MIXED);
-    t.cap_items = 2 * cap_nodes + 65536;
-    t.cap_part = std::min<int64_t>(4 * n, n / 4 + (4 << 20)) + 65536;
+    t.cap_items = 2 * cap_nodes + std::min<int64_t>(8 * n, 65536);
+    t.cap_part = std::min<int64_t>(4 * n, n / 4 + (4 << 20)) + std::min<int64_t>(16 * n, 65536);
     ok = dalloc(c, &t.items, t.cap_items) && dalloc(c, &t.part, t.cap_part) &&
          dalloc(c, &t.m2l_src, t.cap_m2l) && dalloc(c, &t.p2p_src, t.cap_p2p) &&
          dalloc(c, &t.open_buf0, t.cap_open) && dalloc(c, &t.open_buf1, t.cap_open);

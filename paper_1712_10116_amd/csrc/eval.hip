@@ -158,6 +158,14 @@ __device__ __forceinline__ T wave_total_last(T v) {
   return v;
 }
 
+// Workgroups of the far-field cell kernels are one wavefront: at up to 400
+// registers four of them fill a CU, and they share its path to memory, on which a
+// lane's row of 16 to 672 bytes takes a line per load; a wavefront alone also finds
+// room beside the P2P sooner.  256 -> 64 threads, us: P2M of 2^24 particles (leaf
+// 64, p 6, mixed) 5044 -> 1551, of 131,073 105 -> 64; 300,007, p 6, FP64, mean of a
+// level: M2M 14.5 -> 9.9, L2L 16.6 -> 7.6.
+#define CELL_BLOCK 64
+
 // The far-field cell kernels give each cell an aligned group of 8 lanes;
 // g8 = lane & 7 is the lane's place in it.  Branches on the cell are uniform
 // over the group, so its 8 lanes are active at every group sum.
@@ -202,7 +210,7 @@ __device__ __forceinline__ void p2m_cell8(const DevTree &t, int i, int g8, bool 
 }
 
 template <typename T, int P>
-__global__ __launch_bounds__(FMM_BLOCK) void k_p2m(DevTree t, int n_nodes, bool harm) {
+__global__ __launch_bounds__(CELL_BLOCK) void k_p2m(DevTree t, int n_nodes, bool harm) {
   n_nodes = node_count(t, n_nodes);
   const int stride = (gridDim.x * blockDim.x) >> 3;
   for (int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 3; i < n_nodes; i += stride)
@@ -258,7 +266,7 @@ __device__ __forceinline__ void p2m_dip_cell8(const DevTree &t, const double *__
 }
 
 template <typename T, int P>
-__global__ __launch_bounds__(FMM_BLOCK) void k_p2m_dip(DevTree t, int n_nodes,
+__global__ __launch_bounds__(CELL_BLOCK) void k_p2m_dip(DevTree t, int n_nodes,
                                                        const double *__restrict__ dv, bool harm) {
   const int stride = (gridDim.x * blockDim.x) >> 3;
   for (int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 3; i < n_nodes; i += stride)
@@ -316,7 +324,7 @@ __device__ __forceinline__ void m2m_cell8(const DevTree &t, int i, int g8, bool 
 }
 
 template <typename T, int P>
-__global__ __launch_bounds__(FMM_BLOCK) void k_m2m(DevTree t, int s, int e, bool harm) {
+__global__ __launch_bounds__(CELL_BLOCK) void k_m2m(DevTree t, int s, int e, bool harm) {
   level_range(t, s, e);
   const int stride = (gridDim.x * blockDim.x) >> 3;
   for (int i = s + ((blockIdx.x * blockDim.x + threadIdx.x) >> 3); i < e; i += stride)
@@ -332,7 +340,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_m2m(DevTree t, int s, int e, bool
 // pairs separated by more than eps), so the harmonic form is used: folded
 // moments, contraction onto n_z <= 1, unfolding after the wave reduction.
 template <typename T, int P, int KERNEL>
-__global__ __launch_bounds__(FMM_BLOCK) void k_m2l(DevTree t, int n_nodes, double eps) {
+__global__ __launch_bounds__(CELL_BLOCK) void k_m2l(DevTree t, int n_nodes, double eps) {
   constexpr int K = MI<P>::K;
   constexpr int KH = HI<P>::KH;
   constexpr MI<P> mi{};
@@ -342,8 +350,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_m2l(DevTree t, int n_nodes, doubl
   const T *Mh = (const T *)t.Mh;
   T *L = (T *)t.L;
   const int lane = threadIdx.x & 63;
-  const int wave = (xcd_block<32>(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x) >> 6;
-  const int nwaves = (gridDim.x * blockDim.x) >> 6;
+  const int wave = xcd_block<128>(blockIdx.x, gridDim.x), nwaves = gridDim.x;
   n_nodes = node_count(t, n_nodes);
   for (int A = wave; A < n_nodes; A += nwaves) {
     if (skipped(t, A)) continue;
@@ -413,7 +420,7 @@ static void launch_m2l(const DevTree &t, int cells, int n_nodes, double eps, hip
   if constexpr (sizeof(T) == 8 && P >= 5)
     hipLaunchKernelGGL((k_m2l_staged<P, KERNEL>), dim3(cells), dim3(64), 0, s, t, n_nodes, eps);
   else
-    hipLaunchKernelGGL((k_m2l<T, P, KERNEL>), dim3((cells + 3) / 4), dim3(FMM_BLOCK), 0, s, t,
+    hipLaunchKernelGGL((k_m2l<T, P, KERNEL>), dim3(cells), dim3(CELL_BLOCK), 0, s, t,
                        n_nodes, eps);
 }
 
@@ -435,7 +442,7 @@ __device__ __forceinline__ void l2l_cell(const DevTree &t, int c) {
 }
 
 template <typename T, int P>
-__global__ __launch_bounds__(FMM_BLOCK) void k_l2l(DevTree t, int s, int e) {
+__global__ __launch_bounds__(CELL_BLOCK) void k_l2l(DevTree t, int s, int e) {
   level_range(t, s, e);
   for (int c = s + blockIdx.x * blockDim.x + threadIdx.x; c < e; c += gridDim.x * blockDim.x)
     l2l_cell<T, P>(t, c);
@@ -978,15 +985,15 @@ static void level_launch(const EvalArgs &e, int l, int per_cell, int &blocks, in
   const int ls = e.lvl_start_host[l], le = e.lvl_start_host[l + 1];
   const int cnt = le - ls;
   if (!e.dev) {
-    blocks = cnt > 0 ? (per_cell * cnt + FMM_BLOCK - 1) / FMM_BLOCK : 0;
+    blocks = cnt > 0 ? (per_cell * cnt + CELL_BLOCK - 1) / CELL_BLOCK : 0;
     a0 = ls;
     a1 = le;
   } else if (e.exact) {
-    blocks = cnt > 0 ? (per_cell * cnt + FMM_BLOCK - 1) / FMM_BLOCK : 0;
+    blocks = cnt > 0 ? (per_cell * cnt + CELL_BLOCK - 1) / CELL_BLOCK : 0;
     a0 = -1 - l;
     a1 = 0;
   } else {
-    blocks = (per_cell * (cnt + cnt / 4 + 32) + FMM_BLOCK - 1) / FMM_BLOCK;
+    blocks = (per_cell * (cnt + cnt / 4 + 32) + CELL_BLOCK - 1) / CELL_BLOCK;
     a0 = -1 - l;
     a1 = 0;
   }
@@ -995,8 +1002,8 @@ static void level_launch(const EvalArgs &e, int l, int per_cell, int &blocks, in
 // Levels from l on (in steps of step, within lo .. hi) of at most `width` cells:
 // one workgroup takes them in turn instead of a launch each.  Width: a level that
 // one round of the workgroup covers; a wider one is faster on many workgroups.
-// us per level, p 6, 300,007 particles, FP64: M2M 9 in a run, 14 a launch; L2L 6
-// and 17 (solve 1205 -> 1186; 131,073 of 2^20 kicked, mixed, 719 -> 703).
+// us per level, p 6, 300,007 particles, FP64: M2M 5 in a run, 10 a launch; L2L 6
+// and 8 (solve, when launches took 14 and 17, 1205 -> 1186).
 static int level_run(const EvalArgs &e, int l, int step, int lo, int hi, int width) {
   int n = 0;
   for (; l >= lo && l <= hi && e.lvl_start_host[l + 1] - e.lvl_start_host[l] <= width; l += step)
@@ -1024,7 +1031,7 @@ static void run_m2m(const DevTree &t, const EvalArgs &e, bool harm, hipStream_t 
     int blocks, a0, a1;
     level_launch(e, l, 8, blocks, a0, a1);
     if (blocks > 0)
-      hipLaunchKernelGGL((k_m2m<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1, harm);
+      hipLaunchKernelGGL((k_m2m<T, P>), dim3(blocks), dim3(CELL_BLOCK), 0, s, t, a0, a1, harm);
     --l;
   }
 }
@@ -1048,7 +1055,7 @@ static void run_l2l(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     int blocks, a0, a1;
     level_launch(e, l, 1, blocks, a0, a1);
     if (blocks > 0)
-      hipLaunchKernelGGL((k_l2l<T, P>), dim3(blocks), dim3(FMM_BLOCK), 0, s, t, a0, a1);
+      hipLaunchKernelGGL((k_l2l<T, P>), dim3(blocks), dim3(CELL_BLOCK), 0, s, t, a0, a1);
     ++l;
   }
 }
@@ -1060,8 +1067,8 @@ static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   const int ga = e.dev ? nn + nn / 4 + 64 : nn;
   const int narg = e.dev ? -1 : nn;
   const bool harm = KERNEL == 0;  // folded moments feed the harmonic M2L
-  hipLaunchKernelGGL((k_p2m<T, P>), dim3((8 * ga + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
-                     s, t, narg, harm);
+  hipLaunchKernelGGL((k_p2m<T, P>), dim3((8 * ga + CELL_BLOCK - 1) / CELL_BLOCK),
+                     dim3(CELL_BLOCK), 0, s, t, narg, harm);
   run_m2m<T, P>(t, e, harm, s);
 }
 
@@ -1184,8 +1191,8 @@ static void run_dipole(const DevTree &t, const EvalArgs &e, const double *vec, d
   const bool harm = KERNEL == 0;
   hipLaunchKernelGGL(k_gather_dip, dim3((e.n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0, s,
                      t, e.n, vec, dv);
-  hipLaunchKernelGGL((k_p2m_dip<T, P>), dim3((8 * nn + FMM_BLOCK - 1) / FMM_BLOCK),
-                     dim3(FMM_BLOCK), 0, s, t, nn, (const double *)dv, harm);
+  hipLaunchKernelGGL((k_p2m_dip<T, P>), dim3((8 * nn + CELL_BLOCK - 1) / CELL_BLOCK),
+                     dim3(CELL_BLOCK), 0, s, t, nn, (const double *)dv, harm);
   run_m2m<T, P>(t, e, harm, s);
   launch_m2l<T, P, KERNEL>(t, nn, nn, e.eps, s);
   run_l2l<T, P>(t, e, s);

@@ -11,6 +11,8 @@
 #include "common.h"
 #include "expansion.h"
 
+#include <type_traits>
+
 namespace {
 
 constexpr int CA[6] = {0, 1, 2, 0, 0, 1}, CB[6] = {0, 1, 2, 1, 2, 2};
@@ -45,6 +47,14 @@ struct alignas(4 * sizeof(R)) SrcR {
   R x, y, z, m;
 };
 
+// What fills the slots past a leaf's end: no mass, so far away that the pair
+// kernel stays finite (and its products with the mass zero) in R.
+template <typename R>
+__device__ __forceinline__ SrcR<R> far_source() {
+  const R far = sizeof(R) == 4 ? R(1e15) : R(1e150);  // as P2P pads
+  return SrcR<R>{far, far, far, R(0)};
+}
+
 // The entries of its leaf's P2P list that a near-field work item covers here.
 // The items are those of P2P (groups of 64 sinks, shares of the list), but the
 // sums below run leaf by leaf, so share grp of ng takes the grp-th part of the
@@ -66,7 +76,10 @@ __device__ __forceinline__ ItemRange item_range(const DevTree &t, int it) {
 // forces' P2P); pair terms in R, summed in R over one source leaf and then into
 // FP64.  Per pair: m h d (3 products) and six FMAs of it with d for the h d d^T
 // part; the g I part is one sum of m g per source leaf.  The self pair (d = 0)
-// is masked by a select, so an infinite g or h there never reaches a sum.
+// is masked by a select, so an infinite g or h there never reaches a sum; only
+// the leaf itself, which alone holds it, runs the form with the select (seven of
+// 41 instructions a pair in FP64: 65,536 particles, this kernel and the
+// vector-source one 364 -> 339 us at most, solve and field 1656 -> 1567).
 // Written in sorted order to stage (6 rows of stride cap_n), shares past the
 // first to gpart (6 values a row); k_l2p_grad adds them and the far part and
 // writes each particle's tensor once in active order.  One wavefront per leaf
@@ -108,33 +121,39 @@ __global__ __launch_bounds__(64) void k_p2p_grad(DevTree t, double eps,
         for (int jb = t.nbeg[B]; jb < eB; jb += 64) {
           // up to 64 sources of leaf B staged in LDS by the wave's lanes
           const int nj = min(64, eB - jb);
-          SrcR<R> e{R(0), R(0), R(0), R(0)};
+          SrcR<R> e = far_source<R>();
           if (lane < nj)
             e = SrcR<R>{(R)(t.sx[jb + lane] - gA.x), (R)(t.sy[jb + lane] - gA.y),
                         (R)(t.sz[jb + lane] - gA.z), (R)t.sm[jb + lane]};
           st[lane] = e;
           __builtin_amdgcn_wave_barrier();
           // every lane takes the same number of steps: slot ph + k, k = 0, nph,
-          // ..., stays below 64 (nph divides 64); slots past nj hold zeros
-          const int si = i - jb - ph, lim = nj - ph;
-          for (int k = 0; k < nj; k += nph) {
-            const SrcR<R> sv = st[ph + k];
-            const R dx = sv.x - xi, dy = sv.y - yi, dz = sv.z - zi;
-            const R r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-            R g, h;
-            pair_gh<R, KERNEL>(r2, reps, ie, g, h);
-            const bool skip = k == si || k >= lim;
-            const R mg = skip ? R(0) : sv.m * g;
-            const R mh = skip ? R(0) : sv.m * h;
-            const R hx = mh * dx, hy = mh * dy, hz = mh * dz;
-            Gg += mg;
-            Gs[0] = fma(-hx, dx, Gs[0]);
-            Gs[1] = fma(-hy, dy, Gs[1]);
-            Gs[2] = fma(-hz, dz, Gs[2]);
-            Gs[3] = fma(-hx, dy, Gs[3]);
-            Gs[4] = fma(-hx, dz, Gs[4]);
-            Gs[5] = fma(-hy, dz, Gs[5]);
-          }
+          // ..., stays below 64 (nph divides 64); slots past nj hold no mass
+          auto pairs = [&](auto own) {
+            const int si = i - jb - ph;
+            for (int k = 0; k < nj; k += nph) {
+              const SrcR<R> sv = st[ph + k];
+              const R dx = sv.x - xi, dy = sv.y - yi, dz = sv.z - zi;
+              const R r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+              R g, h;
+              pair_gh<R, KERNEL>(r2, reps, ie, g, h);
+              const bool skip = own && k == si;
+              const R mg = skip ? R(0) : sv.m * g;
+              const R mh = skip ? R(0) : sv.m * h;
+              const R hx = mh * dx, hy = mh * dy, hz = mh * dz;
+              Gg += mg;
+              Gs[0] = fma(-hx, dx, Gs[0]);
+              Gs[1] = fma(-hy, dy, Gs[1]);
+              Gs[2] = fma(-hz, dz, Gs[2]);
+              Gs[3] = fma(-hx, dy, Gs[3]);
+              Gs[4] = fma(-hx, dz, Gs[4]);
+              Gs[5] = fma(-hy, dz, Gs[5]);
+            }
+          };
+          if (B == A)
+            pairs(std::true_type{});
+          else
+            pairs(std::false_type{});
           __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll
@@ -272,7 +291,7 @@ __global__ __launch_bounds__(64) void k_p2p_dip(DevTree t, double eps,
         R Us[4] = {0, 0, 0, 0};
         for (int jb = t.nbeg[B]; jb < eB; jb += 64) {
           const int nj = min(64, eB - jb);
-          SrcR<R> ex{R(0), R(0), R(0), R(0)}, ev{R(0), R(0), R(0), R(0)};
+          SrcR<R> ex = far_source<R>(), ev{R(0), R(0), R(0), R(0)};
           if (lane < nj) {
             const int j = jb + lane;
             ex = SrcR<R>{(R)(t.sx[j] - gA.x), (R)(t.sy[j] - gA.y), (R)(t.sz[j] - gA.z),
@@ -283,23 +302,29 @@ __global__ __launch_bounds__(64) void k_p2p_dip(DevTree t, double eps,
           sv[lane] = ev;
           __builtin_amdgcn_wave_barrier();
           // same number of steps on every lane, as in k_p2p_grad
-          const int si = i - jb - ph, lim = nj - ph;
-          for (int k = 0; k < nj; k += nph) {
-            const SrcR<R> p = sx[ph + k], v = sv[ph + k];
-            const R dx = p.x - xi, dy = p.y - yi, dz = p.z - zi;
-            const R r2 = fma(dz, dz, fma(dy, dy, dx * dx));
-            R g, h;
-            pair_gh<R, KERNEL>(r2, reps, ie, g, h);
-            const bool skip = k == si || k >= lim;
-            const R mg = skip ? R(0) : p.m * g;
-            const R mh = skip ? R(0) : p.m * h;
-            const R dvv = fma(dz, v.z, fma(dy, v.y, dx * v.x));
-            const R mhd = mh * dvv;
-            Us[0] = fma(mg, v.x, fma(mhd, dx, Us[0]));
-            Us[1] = fma(mg, v.y, fma(mhd, dy, Us[1]));
-            Us[2] = fma(mg, v.z, fma(mhd, dz, Us[2]));
-            Us[3] = fma(-mg, dvv, Us[3]);
-          }
+          auto pairs = [&](auto own) {
+            const int si = i - jb - ph;
+            for (int k = 0; k < nj; k += nph) {
+              const SrcR<R> p = sx[ph + k], v = sv[ph + k];
+              const R dx = p.x - xi, dy = p.y - yi, dz = p.z - zi;
+              const R r2 = fma(dz, dz, fma(dy, dy, dx * dx));
+              R g, h;
+              pair_gh<R, KERNEL>(r2, reps, ie, g, h);
+              const bool skip = own && k == si;
+              const R mg = skip ? R(0) : p.m * g;
+              const R mh = skip ? R(0) : p.m * h;
+              const R dvv = fma(dz, v.z, fma(dy, v.y, dx * v.x));
+              const R mhd = mh * dvv;
+              Us[0] = fma(mg, v.x, fma(mhd, dx, Us[0]));
+              Us[1] = fma(mg, v.y, fma(mhd, dy, Us[1]));
+              Us[2] = fma(mg, v.z, fma(mhd, dz, Us[2]));
+              Us[3] = fma(-mg, dvv, Us[3]);
+            }
+          };
+          if (B == A)
+            pairs(std::true_type{});
+          else
+            pairs(std::false_type{});
           __builtin_amdgcn_wave_barrier();
         }
 #pragma unroll

@@ -39,8 +39,6 @@ fmm_status fmm_fail(fmm_ctx *c, fmm_status st, const char *fmt, ...) {
       return fail((c), FMM_EDEVICE, "%s failed: %s", #call, hipGetErrorString(e_));          \
   } while (0)
 
-static int coeffs(int p) { return (p + 1) * (p + 2) * (p + 3) / 6; }
-
 #define fail fmm_fail
 #define dalloc fmm_dalloc
 #define dfree fmm_dfree
@@ -162,8 +160,8 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
     fmm_destroy(c);
     return FMM_ENOMEM;
   }
-  t.kmax = coeffs(prm->p_max);
-  t.khmax = ((prm->p_max + 1) * (prm->p_max + 1) + 1) & ~1;  // even: rows read in pairs
+  t.kmax = coeff_row(prm->p_max);
+  t.khmax = folded_row(prm->p_max);
   t.cap_n = max_n;
   int64_t n = max_n;
   int64_t cap_nodes = 8 * n / prm->leaf_size + 1024;

@@ -347,6 +347,11 @@ static inline int p2p_grid_items(int n, int n_nodes) {
 }
 // sources of one staged P2P window
 int p2p_window_sources(bool mixed);
+// Strides of the cells' rows at maximum degree p, of coefficients and of folded
+// moments: even, so that every FP64 row starts on 16 bytes, whatever the order
+// evaluated (the staged M2L reads rows in 16-byte units; at p 8 a row holds 165).
+static inline int coeff_row(int p) { return ((p + 1) * (p + 2) * (p + 3) / 6 + 1) & ~1; }
+static inline int folded_row(int p) { return ((p + 1) * (p + 1) + 1) & ~1; }
 // grad.hip: force gradient of one system's n active particles (SoA 6 x n) on
 // the tree and local expansions of the evaluation just queued on stream s
 hipError_t launch_force_gradient(const DevTree &t, int n_nodes, int n, int p, int kernel,

@@ -411,9 +411,8 @@ __global__ __launch_bounds__(CELL_BLOCK) void k_m2l(DevTree t, int n_nodes, doub
   }
 }
 
-// FP64 at p >= 5 takes the staged form (its rows hold an even number of values,
-// so that 16-byte units are aligned); below, a row is short and all fits in
-// registers.  Beside the P2P, p 5, 100,003 particles: 49 -> 38 us; p 6, 300,007:
+// FP64 at p >= 5 takes the staged form (every row starts on 16 bytes: coeff_row,
+// folded_row); below, a row is short and all fits in registers.  Beside the P2P, p 5, 100,003 particles: 49 -> 38 us; p 6, 300,007:
 // 731 -> 620 (solve 1333 -> 1205).
 template <typename T, int P, int KERNEL>
 static void launch_m2l(const DevTree &t, int cells, int n_nodes, double eps, hipStream_t s) {

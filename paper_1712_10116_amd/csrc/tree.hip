@@ -1137,8 +1137,8 @@ __global__ __launch_bounds__(SMALL_N) void k_build_small(DevTree t, int n, int l
   sort_tile(t, n, 0, t.key, t.slot, true, lds.tile);
   __syncthreads();
   if (leaf_size >= n) {  // no cell is split: every window would reach past its system
-    if (tid < t.n_req) node_info(t, tid, true);
-    for (int r = tid + SMALL_N; r < t.n_req; r += SMALL_N) node_info(t, r, true);
+    const int roots = min(t.n_req, (int)t.cap_nodes);  // empty systems have a root too
+    for (int r = tid; r < roots; r += SMALL_N) node_info(t, r, true);
     return;
   }
   tree_levels(t, n, leaf_size, 0, 1, t.sort_hist, lds.level);

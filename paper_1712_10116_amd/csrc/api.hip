@@ -90,7 +90,17 @@ static bool alloc_nodes(fmm_ctx *c, int64_t cap) {
   return ok;
 }
 
-static void free_nodes(fmm_ctx *c) { dfree(c, c->t.nbeg); }
+static void free_nodes(fmm_ctx *c) {
+  dfree(c, c->t.nbeg);
+  c->t.nbeg = nullptr;
+  c->t.cap_nodes = 0;
+}
+
+// capacities of a context that has grown nothing
+static int64_t first_nodes(const fmm_ctx *c) { return 8 * c->max_n / c->prm.leaf_size + 1024; }
+static int64_t first_list(int which, int64_t cap_nodes) {
+  return (which == OVF_M2L ? 96 : which == OVF_P2P ? 32 : 16) * cap_nodes;
+}
 
 // Request-sized arrays (regrown when a batch holds more requests).  The
 // request table, its particle offsets and its block offsets share one device
@@ -106,20 +116,27 @@ static bool alloc_reqs(fmm_ctx *c, int cap) {
   void *ptrs[] = {t.reqs, t.box, t.bbox_part};
   for (void *p : ptrs) dfree(c, p);
   t.reqs = nullptr;
-  t.cap_req = cap;
+  t.box = nullptr;
+  t.bbox_part = nullptr;
+  t.cap_req = 0;  // until all of it is there
   const size_t bytes = req_region_bytes(cap);
   char *region = nullptr;
-  if (!dalloc(c, &region, (int64_t)bytes) || !dalloc(c, &t.box, cap) ||
+  if (!dalloc(c, &region, (int64_t)bytes)) return false;
+  t.reqs = (DevReq *)region;
+  if (!dalloc(c, &t.box, cap) ||
       !dalloc(c, &t.bbox_part, (int64_t)cap * FMM_BBOX_BLOCKS * FMM_BBOX_COLS))
     return false;
-  t.reqs = (DevReq *)region;
   t.req_off = (int32_t *)(region + sizeof(DevReq) * (size_t)cap);
   t.blk_off = t.req_off + cap + 1;
   for (int k = 0; k < fmm_ctx::UP_SLOTS; ++k) {
     if (c->up_pin[k]) (void)hipHostFree(c->up_pin[k]);
     c->up_pin[k] = nullptr;
-    if (hipHostMalloc((void **)&c->up_pin[k], bytes) != hipSuccess) return false;
+    if (hipHostMalloc((void **)&c->up_pin[k], bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
   }
+  t.cap_req = cap;
   c->up_bytes = bytes;
   c->up_valid = false;
   return true;
@@ -164,7 +181,7 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
   t.khmax = folded_row(prm->p_max);
   t.cap_n = max_n;
   int64_t n = max_n;
-  int64_t cap_nodes = 8 * n / prm->leaf_size + 1024;
+  int64_t cap_nodes = first_nodes(c);
   // radix histograms: one column per tile; also the cells per level and block
   // of the tree build
   const int64_t sort_tiles = (n + SORT_TILE - 1) / SORT_TILE;
@@ -176,9 +193,9 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
     at(t.sort_dtot, 256), at(t.scan_blk, n / 1024 + 64), at(t.hdr, 1);
   }) && alloc_reqs(c, 16) && alloc_nodes(c, cap_nodes);
   if (ok) {
-    t.cap_m2l = 96 * cap_nodes;
-    t.cap_p2p = 32 * cap_nodes;
-    t.cap_open = 16 * cap_nodes;
+    t.cap_m2l = first_list(OVF_M2L, cap_nodes);
+    t.cap_p2p = first_list(OVF_P2P, cap_nodes);
+    t.cap_open = first_list(OVF_OPEN, cap_nodes);
     // near-field items and partial rows: small systems are cut fine (up to a
     // share per window), large ones only at long lists
     t.p2p_src_window = p2p_window_sources(prm->precision == FMM_PREC_MIXED);
@@ -338,28 +355,21 @@ static fmm_status read_header(fmm_ctx *c) {
 
 // Regrow the list buffer that overflowed.  A walk that overflows stops
 // writing, so `need` (the entries it tried to place) can undercount what the
-// whole walk needs: the capacity at least doubles each time.
+// whole walk needs: the capacity at least doubles each time (from the first
+// one if an earlier growth failed and left none).
 static fmm_status regrow_lists(fmm_ctx *c, int which, int64_t need) {
   DevTree &t = c->t;
   const int64_t old = which == OVF_M2L ? t.cap_m2l : which == OVF_P2P ? t.cap_p2p : t.cap_open;
-  int64_t cap = std::max(need + need / 4 + 1024, 2 * old);
+  int64_t cap = std::max(need + need / 4 + 1024, old > 0 ? 2 * old : first_list(which, t.cap_nodes));
   if (which == OVF_M2L) {
-    dfree(c, t.m2l_src);
-    t.m2l_src = nullptr;
-    if (!dalloc(c, &t.m2l_src, cap)) return fail(c, FMM_ENOMEM, "M2L list regrow failed");
-    t.cap_m2l = cap;
+    if (!fmm_regrow(c, &t.m2l_src, &t.cap_m2l, cap)) return fail(c, FMM_ENOMEM, "M2L list regrow failed");
   } else if (which == OVF_P2P) {
-    dfree(c, t.p2p_src);
-    t.p2p_src = nullptr;
-    if (!dalloc(c, &t.p2p_src, cap)) return fail(c, FMM_ENOMEM, "P2P list regrow failed");
-    t.cap_p2p = cap;
+    if (!fmm_regrow(c, &t.p2p_src, &t.cap_p2p, cap)) return fail(c, FMM_ENOMEM, "P2P list regrow failed");
   } else {
-    dfree(c, t.open_buf0);
-    dfree(c, t.open_buf1);
-    t.open_buf0 = t.open_buf1 = nullptr;
-    if (!dalloc(c, &t.open_buf0, cap) || !dalloc(c, &t.open_buf1, cap))
-      return fail(c, FMM_ENOMEM, "open list regrow failed");
-    t.cap_open = cap;
+    int64_t cap0 = old, cap1 = old;
+    const bool ok = fmm_regrow(c, &t.open_buf0, &cap0, cap) && fmm_regrow(c, &t.open_buf1, &cap1, cap);
+    t.cap_open = std::min(cap0, cap1);
+    if (!ok) return fail(c, FMM_ENOMEM, "open list regrow failed");
   }
   return FMM_OK;
 }
@@ -368,18 +378,12 @@ static fmm_status regrow_lists(fmm_ctx *c, int which, int64_t need) {
 // workgroup counts its cells, also when they do not fit).
 static fmm_status regrow_items(fmm_ctx *c, int64_t items, int64_t rows) {
   DevTree &t = c->t;
-  if (items > t.cap_items) {
-    dfree(c, t.items);
-    t.items = nullptr;
-    t.cap_items = items + items / 4;
-    if (!dalloc(c, &t.items, t.cap_items)) return fail(c, FMM_ENOMEM, "P2P item regrow failed");
-  }
+  if (items > t.cap_items && !fmm_regrow(c, &t.items, &t.cap_items, items + items / 4))
+    return fail(c, FMM_ENOMEM, "P2P item regrow failed");
   if (rows > t.cap_part) {
     if (rows > INT32_MAX) return fail(c, FMM_EOVERFLOW, "P2P partial sums of %lld rows", (long long)rows);
-    dfree(c, t.part);
-    t.part = nullptr;
-    t.cap_part = std::min<int64_t>(rows + rows / 4, INT32_MAX);
-    if (!dalloc(c, &t.part, t.cap_part)) return fail(c, FMM_ENOMEM, "P2P partial-sum regrow failed");
+    if (!fmm_regrow(c, &t.part, &t.cap_part, std::min<int64_t>(rows + rows / 4, INT32_MAX)))
+      return fail(c, FMM_ENOMEM, "P2P partial-sum regrow failed");
   }
   return FMM_OK;
 }
@@ -416,7 +420,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   if (!(theta > 0.0) || !(eps >= 0.0) || !std::isfinite(theta) || !std::isfinite(eps))
     return fail(c, FMM_EINVAL, "need theta > 0 and eps >= 0");
   c->tree_valid = false;
-  if (c->t.cap_nodes < 1) return fail(c, FMM_ENOMEM, "no node workspace");
+  if (c->t.cap_nodes < 1 && !alloc_nodes(c, first_nodes(c)))  // an earlier growth failed
+    return fail(c, FMM_ENOMEM, "no node workspace");
   int n_blk = 0;
   st = upload_requests(c, n_req, reqs, &n_blk);
   if (st != FMM_OK) return st;

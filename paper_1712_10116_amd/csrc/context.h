@@ -70,9 +70,30 @@ template <typename T>
 bool fmm_dalloc(fmm_ctx *c, T **p, int64_t count) {
   void *q = nullptr;
   size_t bytes = (size_t)(count > 1 ? count : 1) * sizeof(T);
-  if (hipMalloc(&q, bytes) != hipSuccess) return false;
+  if (hipMalloc(&q, bytes) != hipSuccess) {
+    (void)hipGetLastError();  // reported here, not by the next launch
+    return false;
+  }
   c->allocs.push_back(q);
   *p = (T *)q;
   return true;
 }
 void fmm_dfree(fmm_ctx *c, void *p);
+
+// Grows a buffer of *cap elements to want (its content is not kept).  If that
+// fails it has its former size again or, failing that too, capacity 0, which
+// the kernels report as too small before they write: the context stays usable
+// and its next build tries again.
+template <typename T>
+bool fmm_regrow(fmm_ctx *c, T **p, int64_t *cap, int64_t want) {
+  const int64_t old = *cap;
+  fmm_dfree(c, *p);
+  *p = nullptr;
+  *cap = 0;
+  if (fmm_dalloc(c, p, want)) {
+    *cap = want;
+    return true;
+  }
+  if (old > 0 && fmm_dalloc(c, p, old)) *cap = old;
+  return false;
+}

@@ -1,7 +1,9 @@
-"""Host-side sizing rules of the HIP library, compiled for the CPU from its header.
+"""Host-side sizing rules of the HIP library, compiled for the CPU from its headers.
 
-Rows of the cells' expansions start on 16 bytes at every maximum degree that a
-context accepts."""
+* rows of the cells' expansions start on 16 bytes at every maximum degree that a
+  context accepts;
+* a buffer that cannot grow has its former size, or none: never a capacity
+  without memory behind it."""
 import os
 import shutil
 import subprocess
@@ -15,9 +17,10 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 pytestmark = pytest.mark.skipif(shutil.which(HIPCC) is None, reason="needs hipcc")
 
 
-def _run(tmp_path, body):
+def _run(tmp_path, body, before=""):
     src = tmp_path / "rules.hip"
-    src.write_text('#include "common.h"\n#include <stdio.h>\nint main() {\n%s\n}\n' % body)
+    src.write_text('#include "context.h"\n#include <stdio.h>\n%s\nint main() {\n%s\n}\n'
+                   % (before, body))
     exe = str(tmp_path / "rules")
     subprocess.run([HIPCC, "-std=c++17", "-O0", "--cuda-host-only", "-Wno-unused-value",
                     "-Wno-unused-result", "-I", CSRC, str(src), "-o", exe], check=True,
@@ -31,3 +34,40 @@ def test_rows_start_on_16_bytes(tmp_path):
         coeffs, folded = int(out[2 * p - 2]), int(out[2 * p - 1])
         for row, values in ((coeffs, (p + 1) * (p + 2) * (p + 3) // 6), (folded, (p + 1) ** 2)):
             assert row % 2 == 0 and values <= row <= values + 1
+
+
+ALLOCATOR = r"""
+#include <stdlib.h>
+#include <algorithm>
+static int refused, cleared;  // calls still to refuse; errors taken from the runtime
+extern "C" hipError_t hipMalloc(void **p, size_t n) {
+  if (refused > 0) { --refused; return hipErrorOutOfMemory; }
+  *p = malloc(n);
+  return hipSuccess;
+}
+extern "C" hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+extern "C" hipError_t hipGetLastError(void) { ++cleared; return hipSuccess; }
+void fmm_dfree(fmm_ctx *c, void *p) {
+  if (!p) return;
+  c->allocs.erase(std::find(c->allocs.begin(), c->allocs.end(), p));
+  (void)hipFree(p);
+}
+"""
+
+
+def test_failed_growth_leaves_no_capacity_without_memory(tmp_path):
+    out = _run(tmp_path, """
+  fmm_ctx c{};
+  int32_t *p = nullptr;
+  int64_t cap = 0;
+  for (int k = 0; k < 3; ++k) {
+    fmm_regrow(&c, &p, &cap, 100);
+    refused = k;
+    cleared = 0;
+    const bool ok = fmm_regrow(&c, &p, &cap, 200);
+    refused = 0;
+    printf("%d %d %d %d %d ", ok, (int)cap, p != nullptr, (int)c.allocs.size(), cleared);
+  }
+  printf("%d %d", fmm_regrow(&c, &p, &cap, 50), (int)cap);  // and grows again from nothing
+""", ALLOCATOR)
+    assert [int(x) for x in out] == [1, 200, 1, 1, 0, 0, 100, 1, 1, 1, 0, 0, 0, 0, 2, 1, 50]

@@ -197,9 +197,10 @@ extern "C" fmm_status fmm_create(const fmm_params *prm, int64_t max_n, void *str
     t.cap_p2p = first_list(OVF_P2P, cap_nodes);
     t.cap_open = first_list(OVF_OPEN, cap_nodes);
     // near-field items and partial rows: small systems are cut fine (up to a
-    // share per window), large ones only at long lists
+    // share per window), large ones only at long lists.  Uncut, a leaf has an
+    // item per 64 particles begun, which always fit.
     t.p2p_src_window = p2p_window_sources(prm->precision == FMM_PREC_MIXED);
-    t.cap_items = 2 * cap_nodes + std::min<int64_t>(8 * n, 65536);
+    t.cap_items = 2 * cap_nodes + std::max(std::min<int64_t>(8 * n, 65536), n / 64);
     t.cap_part = std::min<int64_t>(4 * n, n / 4 + (4 << 20)) + std::min<int64_t>(16 * n, 65536);
     ok = dalloc(c, &t.items, t.cap_items) && dalloc(c, &t.part, t.cap_part) &&
          dalloc(c, &t.m2l_src, t.cap_m2l) && dalloc(c, &t.p2p_src, t.cap_p2p) &&
@@ -375,16 +376,18 @@ static fmm_status regrow_lists(fmm_ctx *c, int which, int64_t need) {
 }
 
 // Regrow the near-field items and partial rows to what a plan counted (every
-// workgroup counts its cells, also when they do not fit).
+// workgroup counts its cells, also when they do not fit).  Without the memory
+// for them this context cuts no list any more: that takes no rows, and the items
+// that it has from the start.  Sums then differ in rounding only.
 static fmm_status regrow_items(fmm_ctx *c, int64_t items, int64_t rows) {
   DevTree &t = c->t;
-  if (items > t.cap_items && !fmm_regrow(c, &t.items, &t.cap_items, items + items / 4))
-    return fail(c, FMM_ENOMEM, "P2P item regrow failed");
-  if (rows > t.cap_part) {
-    if (rows > INT32_MAX) return fail(c, FMM_EOVERFLOW, "P2P partial sums of %lld rows", (long long)rows);
-    if (!fmm_regrow(c, &t.part, &t.cap_part, std::min<int64_t>(rows + rows / 4, INT32_MAX)))
-      return fail(c, FMM_ENOMEM, "P2P partial-sum regrow failed");
-  }
+  const bool ok =
+      (items <= t.cap_items || fmm_regrow(c, &t.items, &t.cap_items, items + items / 4)) &&
+      (rows <= t.cap_part ||
+       (rows <= INT32_MAX && fmm_regrow(c, &t.part, &t.cap_part,
+                                        std::min<int64_t>(rows + rows / 4, INT32_MAX))));
+  if (!ok && t.uncut) return fail(c, FMM_ENOMEM, "P2P item regrow failed");
+  if (!ok) t.uncut = 1;
   return FMM_OK;
 }
 
@@ -790,20 +793,19 @@ extern "C" fmm_status fmm_forces_grad(fmm_ctx *c, const double *pos, const doubl
                                       double *grad) {
   if (!c) return FMM_EINVAL;
   if (n_active > 0 && !grad) return fail(c, FMM_EINVAL, "grad is NULL");
+  if (!c->gstage && !dalloc(c, &c->gstage, 6 * c->max_n))
+    return fail(c, FMM_ENOMEM, "force-gradient staging");
   fmm_status st = fmm_forces(c, pos, mass, n_total, active, n_active, eps, theta, p, acc, pot);
   if (st != FMM_OK || n_active == 0) return st;
-  if (c->gpart_rows < c->t.cap_part) {  // the partial rows grow with those of the forces
-    dfree(c, c->gstage);
-    c->gstage = nullptr;
-    c->gpart_rows = 0;
-    if (!dalloc(c, &c->gstage, 6 * (c->max_n + c->t.cap_part)))
-      return fail(c, FMM_ENOMEM, "force-gradient staging");
-    c->gpart_rows = c->t.cap_part;
+  const int64_t rows = (int64_t)c->hh.part_cursor;
+  if (6 * rows > c->gpart_len && !fmm_regrow(c, &c->gpart, &c->gpart_len, 6 * (rows + rows / 4))) {
+    c->t.uncut = 1;  // as in regrow_items
+    st = fmm_forces(c, pos, mass, n_total, active, n_active, eps, theta, p, acc, pot);
+    if (st != FMM_OK) return st;
   }
   HIPCHK(c, launch_force_gradient(c->t, c->n_nodes, (int)n_active, p, c->prm.kernel,
-                                  c->prm.precision == FMM_PREC_MIXED, eps, c->gstage, c->gstage + 6 * c->max_n,
-                                  grad,
-                                  c->stream));
+                                  c->prm.precision == FMM_PREC_MIXED, eps, c->gstage, c->gpart,
+                                  grad, c->stream));
   return FMM_OK;
 }
 

@@ -140,6 +140,7 @@ struct DevTree {
   Box *box;  // [cap_req]
   int64_t cap_n, cap_nodes, cap_m2l, cap_p2p, cap_open, cap_items, cap_part;
   int p2p_src_window;  // sources of one staged P2P window (by precision)
+  int uncut;  // no list is cut into shares: there was no memory for the partial sums
   int kmax, khmax;
 };
 
@@ -347,6 +348,21 @@ static inline int p2p_grid_items(int n, int n_nodes) {
 }
 // sources of one staged P2P window
 int p2p_window_sources(bool mixed);
+// Most shares of a leaf's near list in a system of n particles.  The lists of a
+// concentrated system are long at a few leaves only (at most 39 shares of 12,526
+// to 500,000 particles of a Plummer sphere); where the softening makes every pair
+// near, all are, and each share of each particle takes a row of partial sums:
+// 2^25 rows (1 GiB) in all up to 2^20 particles, 32 a particle beyond.
+__host__ __device__ static inline int p2p_share_max(int n) {
+  const int s = (1 << 25) / (n > 0 ? n : 1);
+  return s > 128 ? 128 : s < 32 ? 32 : s;
+}
+// chunks of 64 list entries in a share of whole chunks
+#define P2P_SHARE_CHUNKS 4
+__host__ __device__ static inline int p2p_share_chunks(int cnt, int share_max) {
+  const int per = ((cnt + 63) / 64 + share_max - 1) / share_max;
+  return per > P2P_SHARE_CHUNKS ? per : P2P_SHARE_CHUNKS;
+}
 // Strides of the cells' rows at maximum degree p, of coefficients and of folded
 // moments: even, so that every FP64 row starts on 16 bytes, whatever the order
 // evaluated (the staged M2L reads rows in 16-byte units; at p 8 a row holds 165).

@@ -55,9 +55,9 @@ struct fmm_ctx {
   double *dvec;            // [3][max_n] sorted source vectors of the vector-source pass
                            // (allocated by its first call)
   double *gstage;          // [6][max_n] near part of the force gradient in sorted order
-                           // (allocated by the first fmm_forces_grad), then its
-                           // partial rows [gpart_rows][6] (as DevTree::part)
-  int64_t gpart_rows;
+                           // (allocated by the first fmm_forces_grad)
+  double *gpart;           // [gpart_rows][6] its partial rows (as DevTree::part)
+  int64_t gpart_len;       // values of gpart: 6 gpart_rows
   int64_t stat_calls, stat_parts, stat_builds;
   PhaseTimer timer;
   char err[512];

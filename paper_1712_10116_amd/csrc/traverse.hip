@@ -1000,27 +1000,27 @@ __global__ __launch_bounds__(WALK_WAVES * 64, 4) void k_walk_level(DevTree t, in
 // have leaves enough and are cut only where a list is long (disk galaxy 2^22:
 // solve 14.4 -> 13.1 ms).  Systems of at most 1024 particles have no list
 // longer than a few windows and the multipole passes beside P2P take longer:
-// not cut, which needs no look at the sources.
-// ---------------------------------------------------------------------------
-#define P2P_SHARE_CHUNKS 4
+// not cut, which needs no look at the sources.  A list that would be cut into
+// more than p2p_share_max shares takes twice or four times the windows a share,
+// or whole chunks, as many as it needs.
 #define P2P_SHARE_MAX_LEAF 4096  // larger leaves (coincident particles) are cut by sinks only
 #define P2P_SHARE_FINE_N 524288  // largest system cut by windows
+#define P2P_SHARE_STEPS 3        // windows per share tried: g, 2 g, 4 g
 __device__ __forceinline__ int p2p_share_windows(int n) {
   if (n <= SMALL_N || n > P2P_SHARE_FINE_N) return 0;
   return n <= 32768 ? 1 : n <= 131072 ? 2 : 4;
 }
 
-// shares of a leaf of nA particles whose list of cnt entries is cut by whole chunks
-__device__ __forceinline__ int whole_chunk_shares(int nA, int cnt) {
-  return nA > P2P_SHARE_MAX_LEAF
-             ? 1
-             : max(1, (cnt + 64 * P2P_SHARE_CHUNKS - 1) / (64 * P2P_SHARE_CHUNKS));
+// list entries of a share of a leaf of nA particles whose list of cnt entries is
+// cut by whole chunks into at most share_max
+__device__ __forceinline__ int whole_chunk_entries(const DevTree &t, int nA, int cnt,
+                                                   int share_max) {
+  return nA > P2P_SHARE_MAX_LEAF || t.uncut ? max(cnt, 1) : 64 * p2p_share_chunks(cnt, share_max);
 }
 
-__device__ __forceinline__ void emit_whole_chunks(const DevTree &t, int A, int nA, int cnt,
+__device__ __forceinline__ void emit_whole_chunks(const DevTree &t, int A, int nA, int cnt, int per,
                                                   int groups, int64_t i0, int64_t r0) {
   const int T = (nA + 63) >> 6;
-  const int per = groups > 1 ? 64 * P2P_SHARE_CHUNKS : max(cnt, 1);
   for (int k = 0; k < groups; ++k)
     for (int q = 0; q < T; ++q)
       t.items[i0 + (int64_t)k * T + q] =
@@ -1070,20 +1070,27 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
     const int64_t id = first + b + lane;
     const bool leaf = b + lane < npw && id < nn && t.nnchild[id] == 0;
     const int A = leaf ? (int)id : 0;
-    int nA = 0, cnt = 0, off = 0, g = 0, groups = 0;
+    int nA = 0, cnt = 0, off = 0, g = 0, groups = 0, share_max = 1, per = 1;
     if (leaf) {
+      const int n = t.reqs[t.nreq[A]].n;
       nA = t.nend[A] - t.nbeg[A];
       cnt = t.p2p_cnt[A];
       off = t.p2p_off[A];
-      g = p2p_share_windows(t.reqs[t.nreq[A]].n);
-      groups = whole_chunk_shares(nA, cnt);
+      g = t.uncut ? 0 : p2p_share_windows(n);
+      share_max = p2p_share_max(n);
+      per = whole_chunk_entries(t, nA, cnt, share_max);
+      groups = max(1, (cnt + per - 1) / per);
     }
-    const unsigned long long fine = __ballot(leaf && g > 0 && nA <= P2P_SHARE_MAX_LEAF && cnt > 0);
+    // leaves whose chunks are counted, and those cut by windows
+    const unsigned long long counted =
+        __ballot(leaf && g > 0 && nA <= P2P_SHARE_MAX_LEAF && cnt > 0);
+    unsigned long long fine = counted;
     int used = 0;  // chunks counted so far in this batch (kept up to PLAN_CHUNKS)
-    for (unsigned long long m = fine; m; m &= m - 1) {
+    for (unsigned long long m = counted; m; m &= m - 1) {
       const int l = (int)__ffsll((long long)m) - 1;
       const int c = __shfl(cnt, l, 64), o = __shfl(off, l, 64), gl = __shfl(g, l, 64);
-      int sum = 0;
+      const int most = __shfl(share_max, l, 64), gs = 31 - __clz(gl);  // gl: a power of two
+      int sum[P2P_SHARE_STEPS] = {};
       for (int qb = 0; qb < c; qb += 256) {
         int nw[4];
         chunk_windows(t, o, c, qb, nw);
@@ -1093,10 +1100,23 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
             if (lane == 0 && used < PLAN_CHUNKS) s_nw[w][used] = (uint16_t)nw[k];
             ++used;
           }
-          sum += (nw[k] + gl - 1) / gl;
+#pragma unroll
+          for (int j = 0; j < P2P_SHARE_STEPS; ++j) sum[j] += (nw[k] + (gl << j) - 1) >> (gs + j);
         }
       }
-      if (lane == l) groups = max(1, sum);
+      int step = 0, shares = sum[0];
+#pragma unroll
+      for (int j = 1; j < P2P_SHARE_STEPS; ++j)
+        if (shares > most) {
+          step = j;
+          shares = sum[j];
+        }
+      if (shares > most) {
+        fine &= ~(1ull << l);
+      } else if (lane == l) {
+        g = gl << step;
+        groups = max(1, shares);
+      }
     }
     const int T = (nA + 63) >> 6;
     const int items = leaf ? groups * T : 0;
@@ -1137,12 +1157,16 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
     if (leaf) {
       t.nshare[A] = groups - 1;
       t.part_off[A] = (int32_t)r0;
-      if (!(fine >> lane & 1)) emit_whole_chunks(t, A, nA, cnt, groups, i0, r0);
+      if (!(fine >> lane & 1)) emit_whole_chunks(t, A, nA, cnt, per, groups, i0, r0);
     }
     int at = 0;  // the batch's chunks in the order counted
-    for (unsigned long long m = fine; m; m &= m - 1) {
+    for (unsigned long long m = counted; m; m &= m - 1) {
       const int l = (int)__ffsll((long long)m) - 1;
       const int c = __shfl(cnt, l, 64), o = __shfl(off, l, 64), gl = __shfl(g, l, 64);
+      if (!(fine >> l & 1)) {
+        at += (c + 63) >> 6;
+        continue;
+      }
       const int Al = __shfl(A, l, 64), nl = __shfl(nA, l, 64), Tl = __shfl(T, l, 64);
       const int64_t il = (int64_t)__shfl((unsigned long long)i0, l, 64);
       const int64_t rl = (int64_t)__shfl((unsigned long long)r0, l, 64);

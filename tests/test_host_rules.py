@@ -3,7 +3,9 @@
 * rows of the cells' expansions start on 16 bytes at every maximum degree that a
   context accepts;
 * a buffer that cannot grow has its former size, or none: never a capacity
-  without memory behind it."""
+  without memory behind it;
+* the shares that a leaf's near list is cut into are bounded, and so is the
+  memory of their partial sums."""
 import os
 import shutil
 import subprocess
@@ -71,3 +73,25 @@ def test_failed_growth_leaves_no_capacity_without_memory(tmp_path):
   printf("%d %d", fmm_regrow(&c, &p, &cap, 50), (int)cap);  // and grows again from nothing
 """, ALLOCATOR)
     assert [int(x) for x in out] == [1, 200, 1, 1, 0, 0, 100, 1, 1, 1, 0, 0, 0, 0, 2, 1, 50]
+
+
+def test_shares_are_bounded(tmp_path):
+    ns = [1, 1024, 1025, 32768, 131072, 262144, 262145, 524288, 524289, 1 << 20, (1 << 20) + 1,
+          1 << 24, 1 << 30]
+    cnts = [0, 1, 64, 65, 256, 257, 8192, 8193, 8449, 32768, 32769, 1 << 20, (1 << 31) - 64]
+    out = [int(x) for x in _run(tmp_path, """
+  const int ns[] = {%s}, cnts[] = {%s};
+  for (int n : ns) {
+    const int most = p2p_share_max(n);
+    printf("%%d ", most);
+    for (int c : cnts) printf("%%d ", p2p_share_chunks(c, most));
+  }
+""" % (",".join(map(str, ns)), ",".join(map(str, cnts))))]
+    for n in ns:
+        most, out = out[0], out[1:]
+        assert 32 <= most <= 128 and (most == 128 or n * most <= 2 ** 25 or most == 32)
+        assert n * most <= max(2 ** 25, 32 * n)
+        for c in cnts:
+            per, out = out[0], out[1:]
+            assert per >= 4 and -(-c // (64 * per)) <= most
+            assert per == 4 or -(-c // (64 * (per - 1))) > most  # no longer than need be

@@ -454,6 +454,12 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       if (c->hh.lvl_start[l + 1] > c->hh.lvl_start[l]) depth = l;
     return depth;
   };
+  // an error found behind a queued evaluation (whose kernels then do nothing):
+  // nothing reads the caller's arrays any more when it is returned
+  auto fail_queued = [&](fmm_status e, const char *what) {
+    (void)hipStreamSynchronize(c->stream);
+    return fail(c, e, "%s", what);
+  };
   // 0. small trees: everything is queued without reading a size back (the walk's
   // path form, M2M and L2L in one workgroup, sizes read on the device), with
   // one header readback at the end; anything that needs more room falls
@@ -498,8 +504,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       st = read_header(c);
       if (st != FMM_OK) return st;
     }
-    if (c->hh.nonfinite) return fail(c, FMM_ENONFINITE, "non-finite input position");
-    if (c->hh.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
+    if (c->hh.nonfinite) return fail_queued(FMM_ENONFINITE, "non-finite input position");
+    if (c->hh.overflow & OVF_STACK) return fail_queued(FMM_EOVERFLOW, "walk descent stack overflow");
     if (!(c->hh.overflow & OVF_ANY)) {
       record_levels(c, std::min(FMM_MAXLEVEL, c->hh.max_prefix + 1));
       st = finish(tree_depth());
@@ -567,7 +573,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     }
     HIPCHK(c, hipEventSynchronize(c->hdr_ev));
     memcpy(&c->hh, c->pin_hdr, sizeof(Header));
-    if (c->hh.nonfinite) return fail(c, FMM_ENONFINITE, "non-finite input position");
+    if (c->hh.nonfinite) return fail_queued(FMM_ENONFINITE, "non-finite input position");
     const int need = std::min(FMM_MAXLEVEL, c->hh.max_prefix + 1);
     if (need <= pred && !(c->hh.overflow & OVF_ANY)) {
       record_levels(c, need);

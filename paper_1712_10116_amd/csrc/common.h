@@ -42,8 +42,11 @@
 #define OVF_ITEMS 64
 // an open list outgrew the walk's path form (the host walks by levels)
 #define OVF_PATH 128
+// an input position was not finite: what was queued behind the build does nothing
+#define OVF_INPUT 256
 #define OVF_ANY                                                                            \
-  (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH | OVF_ITEMS | OVF_PATH)
+  (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH | OVF_ITEMS | OVF_PATH | \
+   OVF_INPUT)
 
 struct Header {
   int32_t lvl_start[FMM_NLEVELS + 2];  // nodes of level l: [lvl_start[l], lvl_start[l+1])
@@ -51,7 +54,7 @@ struct Header {
   uint32_t p2p_cursor;                 // ordered P2P entries written (or needed)
   uint32_t open_cursor[FMM_NLEVELS];   // open-list entries per level
   int32_t overflow;                    // OVF_* bits
-  int32_t nonfinite;                   // an input position was not finite
+  int32_t nonfinite;                   // an input position was not finite (OVF_INPUT too)
   unsigned long long p2p_pairs;        // ordered particle interactions in P2P
   int32_t n_leaves;
   int32_t max_prefix;  // deepest level of a cell holding more than leaf_size particles

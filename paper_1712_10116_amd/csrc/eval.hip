@@ -81,7 +81,8 @@ __device__ __forceinline__ bool has_sink(const DevTree &t, int A, int bA, int nA
 // before the host read the tree header (the tree is checked afterwards and
 // the evaluation redone if it fails): the count comes from the header, and
 // nothing is evaluated on a tree or lists whose build overflowed a
-// workspace (node arrays, list buffers or descent stack).
+// workspace (node arrays, list buffers or descent stack), nor on positions that
+// are not finite.
 __device__ __forceinline__ bool tree_incomplete(const DevTree &t) {
   return (t.hdr->overflow & OVF_ANY) != 0;
 }

@@ -835,12 +835,13 @@ __global__ __launch_bounds__(TRAV_WAVES * 64) void k_walk_waves(DevTree t, int l
 
 // Level l with its bounds read from the tree header (queued before the
 // level sizes are known on the host): the waves of the grid stride over the
-// parents; nothing is done on a tree whose node workspace overflowed.
+// parents; nothing is done on a tree whose node workspace overflowed, nor of
+// positions that are not finite.
 __global__ __launch_bounds__(TRAV_WAVES * 64) void k_walk_waves_dev(DevTree t, int l, double th2,
                                                                     double eps) {
   __shared__ WaveLds lds[TRAV_WAVES];
   const Header *h = t.hdr;
-  if (h->overflow & OVF_NODES) return;
+  if (h->overflow & (OVF_NODES | OVF_INPUT)) return;
   const int ps = l == 0 ? 0 : h->lvl_start[l - 1];
   const int pe = l == 0 ? t.n_req : h->lvl_start[l];
   const int w = threadIdx.x >> 6;
@@ -937,7 +938,7 @@ __global__ __launch_bounds__(WALK_WAVES * 64, 4) void k_walk_paths(DevTree t, do
                                                                    double eps) {
   __shared__ GroupLds lds;
   Header *h = t.hdr;
-  if (h->overflow & OVF_NODES) return;
+  if (h->overflow & (OVF_NODES | OVF_INPUT)) return;
   const int nn = min(h->lvl_start[FMM_NLEVELS], (int)t.cap_nodes);
   for (int P = blockIdx.x; P < nn; P += gridDim.x) {
     const int4 ip = t.ninfo[P];
@@ -1214,7 +1215,7 @@ __global__ void k_reset_lists(Header *h) {
     h->m2l_cursor = 0;
     h->p2p_cursor = 0;
     h->p2p_pairs = 0;
-    h->overflow &= OVF_NODES | OVF_DEPTH;
+    h->overflow &= OVF_NODES | OVF_DEPTH | OVF_INPUT;
     h->item_cursor = 0;
     h->part_cursor = 0;
   }

@@ -577,12 +577,13 @@ __device__ __forceinline__ double4 cell_geometry(const Box &b, uint64_t prefix, 
 
 // header of a new tree (one thread) and the root of request r, covering its
 // sorted range [off, off + n)
-__device__ __forceinline__ void header_init(const DevTree &t) {
+__device__ __forceinline__ void header_init(const DevTree &t, bool nonfinite) {
   Header *h = t.hdr;
   const int R = t.n_req;
   h->lvl_start[0] = 0;
   for (int l = 1; l < FMM_NLEVELS + 2; ++l) h->lvl_start[l] = R;
-  h->overflow = R > t.cap_nodes ? OVF_NODES : 0;
+  h->overflow = (R > t.cap_nodes ? OVF_NODES : 0) | (nonfinite ? OVF_INPUT : 0);
+  h->nonfinite = nonfinite ? 1 : 0;
   h->max_prefix = 0;
   h->n_leaves = 0;
 }
@@ -633,25 +634,22 @@ __global__ __launch_bounds__(INIT_WAVES * 64) void k_init(DevTree t, int leaf_si
   bool bad = false;
   for (int r = threadIdx.x >> 6; r < t.n_req; r += INIT_WAVES) bad |= box_of_request(t, r);
   const int any = __syncthreads_or(bad);
-  if (threadIdx.x == 0) {
-    header_init(t);
-    t.hdr->nonfinite = any ? 1 : 0;
-  }
+  if (threadIdx.x == 0) header_init(t, any != 0);
   __syncthreads();
   for (int r = threadIdx.x; r < t.n_req; r += INIT_WAVES * 64) root_init(t, r, leaf_size);
 }
 
-__global__ void k_header_init(DevTree t) {
-  header_init(t);
-  t.hdr->nonfinite = 0;
-}
+__global__ void k_header_init(DevTree t) { header_init(t, false); }
 
 __global__ __launch_bounds__(FMM_BLOCK) void k_boxes(DevTree t, int leaf_size) {
   const int r = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   if (r >= t.n_req) return;
   const bool bad = box_of_request(t, r);
   if ((threadIdx.x & 63) == 0) {
-    if (bad) atomicOr(&t.hdr->nonfinite, 1);
+    if (bad) {
+      atomicOr(&t.hdr->nonfinite, 1);
+      atomicOr(&t.hdr->overflow, OVF_INPUT);
+    }
     root_init(t, r, leaf_size);
   }
 }
@@ -1128,10 +1126,7 @@ __global__ __launch_bounds__(SMALL_N) void k_build_small(DevTree t, int n, int l
     if (lane == 0) finish_box(t.box[r], lo, hi, q.n == 0);
   }
   const int any = __syncthreads_or(bad);
-  if (tid == 0) {
-    header_init(t);
-    t.hdr->nonfinite = any ? 1 : 0;
-  }
+  if (tid == 0) header_init(t, any != 0);
   __syncthreads();
   for (int r = tid; r < t.n_req; r += SMALL_N) root_init(t, r, leaf_size);
   sort_tile(t, n, 0, t.key, t.slot, true, lds.tile);

@@ -48,6 +48,12 @@
   (OVF_NODES | OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_DEPTH | OVF_ITEMS | OVF_PATH | \
    OVF_INPUT)
 
+// What a queued kernel heeds: only bits that are final when it runs.  The build's
+// are final for the upward pass (which runs beside the walk), those of build and
+// walk for M2L and L2L (beside the near-field plan), all for what follows the plan.
+#define OVF_BUILD (OVF_NODES | OVF_DEPTH | OVF_INPUT)
+#define OVF_WALK (OVF_ANY & ~OVF_ITEMS)
+
 struct Header {
   int32_t lvl_start[FMM_NLEVELS + 2];  // nodes of level l: [lvl_start[l], lvl_start[l+1])
   uint32_t m2l_cursor;                 // ordered M2L entries written (or needed)

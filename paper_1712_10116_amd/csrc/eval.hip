@@ -82,20 +82,24 @@ __device__ __forceinline__ bool has_sink(const DevTree &t, int A, int bA, int nA
 // the evaluation redone if it fails): the count comes from the header, and
 // nothing is evaluated on a tree or lists whose build overflowed a
 // workspace (node arrays, list buffers or descent stack), nor on positions that
-// are not finite.
+// are not finite.  WHAT: the bits that are final when the kernel runs (a bit set
+// meanwhile could part the wavefronts of a workgroup at its barriers).
+template <int WHAT>
 __device__ __forceinline__ bool tree_incomplete(const DevTree &t) {
-  return (t.hdr->overflow & OVF_ANY) != 0;
+  return (t.hdr->overflow & WHAT) != 0;
 }
+template <int WHAT>
 __device__ __forceinline__ int node_count(const DevTree &t, int n) {
   if (n >= 0) return n;
-  return tree_incomplete(t) ? 0 : min(t.hdr->lvl_start[FMM_NLEVELS], (int)t.cap_nodes);
+  return tree_incomplete<WHAT>(t) ? 0 : min(t.hdr->lvl_start[FMM_NLEVELS], (int)t.cap_nodes);
 }
 // cells of one level: [s, e) from the host, or s = -1 - l for level l read
 // from the header as above
+template <int WHAT>
 __device__ __forceinline__ void level_range(const DevTree &t, int &s, int &e) {
   if (s >= 0) return;
   const int l = -1 - s;
-  if (tree_incomplete(t)) {
+  if (tree_incomplete<WHAT>(t)) {
     s = e = 0;
     return;
   }
@@ -212,7 +216,7 @@ __device__ __forceinline__ void p2m_cell8(const DevTree &t, int i, int g8, bool 
 
 template <typename T, int P>
 __global__ __launch_bounds__(CELL_BLOCK) void k_p2m(DevTree t, int n_nodes, bool harm) {
-  n_nodes = node_count(t, n_nodes);
+  n_nodes = node_count<OVF_BUILD>(t, n_nodes);
   const int stride = (gridDim.x * blockDim.x) >> 3;
   for (int i = (blockIdx.x * blockDim.x + threadIdx.x) >> 3; i < n_nodes; i += stride)
     p2m_cell8<T, P>(t, i, threadIdx.x & 7, harm);
@@ -326,7 +330,7 @@ __device__ __forceinline__ void m2m_cell8(const DevTree &t, int i, int g8, bool 
 
 template <typename T, int P>
 __global__ __launch_bounds__(CELL_BLOCK) void k_m2m(DevTree t, int s, int e, bool harm) {
-  level_range(t, s, e);
+  level_range<OVF_BUILD>(t, s, e);
   const int stride = (gridDim.x * blockDim.x) >> 3;
   for (int i = s + ((blockIdx.x * blockDim.x + threadIdx.x) >> 3); i < e; i += stride)
     m2m_cell8<T, P>(t, i, threadIdx.x & 7, harm);
@@ -352,7 +356,7 @@ __global__ __launch_bounds__(CELL_BLOCK) void k_m2l(DevTree t, int n_nodes, doub
   T *L = (T *)t.L;
   const int lane = threadIdx.x & 63;
   const int wave = xcd_block<128>(blockIdx.x, gridDim.x), nwaves = gridDim.x;
-  n_nodes = node_count(t, n_nodes);
+  n_nodes = node_count<OVF_WALK>(t, n_nodes);
   for (int A = wave; A < n_nodes; A += nwaves) {
     if (skipped(t, A)) continue;
     const double4 gA = t.ngeo[A];
@@ -443,7 +447,7 @@ __device__ __forceinline__ void l2l_cell(const DevTree &t, int c) {
 
 template <typename T, int P>
 __global__ __launch_bounds__(CELL_BLOCK) void k_l2l(DevTree t, int s, int e) {
-  level_range(t, s, e);
+  level_range<OVF_WALK>(t, s, e);
   for (int c = s + blockIdx.x * blockDim.x + threadIdx.x; c < e; c += gridDim.x * blockDim.x)
     l2l_cell<T, P>(t, c);
 }
@@ -472,7 +476,7 @@ template <typename T, int P>
 __global__ __launch_bounds__((small_threads<T, P>())) void k_m2m_small(DevTree t, int lo, int hi,
                                                                        bool harm, bool dev) {
   const Header *h = t.hdr;
-  if (dev && tree_incomplete(t)) return;
+  if (dev && tree_incomplete<OVF_BUILD>(t)) return;
   if (hi < 0) hi = tree_depth(h) - 1;
   for (int l = hi; l >= lo; --l) {
     for (int i = h->lvl_start[l] + (threadIdx.x >> 3); i < h->lvl_start[l + 1];
@@ -486,7 +490,7 @@ template <typename T, int P>
 __global__ __launch_bounds__((small_threads<T, P>())) void k_l2l_small(DevTree t, int lo, int hi,
                                                                        bool dev) {
   const Header *h = t.hdr;
-  if (dev && tree_incomplete(t)) return;
+  if (dev && tree_incomplete<OVF_WALK>(t)) return;
   if (hi < 0) hi = tree_depth(h);
   for (int l = lo; l <= hi; ++l) {
     for (int c = h->lvl_start[l] + threadIdx.x; c < h->lvl_start[l + 1]; c += blockDim.x)
@@ -504,7 +508,7 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_l2p(DevTree t, int n, bool dev, d
   const T *L = (const T *)t.L;
   int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
-  if (dev && tree_incomplete(t)) return;  // leaf_of not written for this tree
+  if (dev && tree_incomplete<OVF_ANY>(t)) return;  // leaf_of not written for this tree
   // the system first: leaf_of is written only for systems this evaluation covers
   const DevReq q = t.reqs[upper_index(t.req_off, t.n_req, j)];
   if (!q.mass) return;
@@ -832,7 +836,7 @@ __global__ __launch_bounds__(P2P_WAVES * 64, MIXED ? 4 : 3) void k_p2p(DevTree t
   const R inv_eps = eps > 0 ? (R)(1.0 / eps) : R(0);
   const R inv_eps3 = eps > 0 ? (R)(1.0 / (eps * eps * eps)) : R(0);
   const int64_t cap = t.cap_n;
-  const int n_items = tree_incomplete(t) ? 0 : (int)t.hdr->item_cursor;
+  const int n_items = tree_incomplete<OVF_ANY>(t) ? 0 : (int)t.hdr->item_cursor;
   for (int it = wave; it < n_items; it += nwaves) {
     const P2PItem im = t.items[it];
     const int A = im.A;

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(64) void k_m2l_staged(DevTree t, int n_nodes, doubl
   for (int c = 0; c < 4; ++c)
     rb[c] = rows + (lane >> 4) * (Row::PIECES * 64) + (lane & 15) * 4 +
             (c ^ ((lane >> 2) & 3));
-  n_nodes = node_count(t, n_nodes);
+  n_nodes = node_count<OVF_WALK>(t, n_nodes);
   for (int A = xcd_block<128>(blockIdx.x, gridDim.x); A < n_nodes; A += gridDim.x) {
     if (skipped(t, A)) continue;
     const double4 gA = t.ngeo[A];

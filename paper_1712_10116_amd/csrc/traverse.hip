@@ -1061,7 +1061,7 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
   __shared__ unsigned long long s_row0;
   __shared__ uint16_t s_nw[PLAN_WAVES][PLAN_CHUNKS];
   Header *h = t.hdr;
-  if (h->overflow & (OVF_ANY & ~OVF_ITEMS)) return;
+  if (h->overflow & OVF_WALK) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int nn = min(h->lvl_start[FMM_NLEVELS], (int)t.cap_nodes);
   const int nwaves = gridDim.x * PLAN_WAVES;
@@ -1215,7 +1215,7 @@ __global__ void k_reset_lists(Header *h) {
     h->m2l_cursor = 0;
     h->p2p_cursor = 0;
     h->p2p_pairs = 0;
-    h->overflow &= OVF_NODES | OVF_DEPTH | OVF_INPUT;
+    h->overflow &= OVF_BUILD;
     h->item_cursor = 0;
     h->part_cursor = 0;
   }

@@ -5,8 +5,10 @@
 * a buffer that cannot grow has its former size, or none: never a capacity
   without memory behind it;
 * the shares that a leaf's near list is cut into are bounded, and so is the
-  memory of their partial sums."""
+  memory of their partial sums;
+* queued kernels heed no overflow bit that a kernel beside them may set."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -95,3 +97,25 @@ def test_shares_are_bounded(tmp_path):
             per, out = out[0], out[1:]
             assert per >= 4 and -(-c // (64 * per)) <= most
             assert per == 4 or -(-c // (64 * (per - 1))) > most  # no longer than need be
+
+
+def test_kernels_heed_final_overflow_bits(tmp_path):
+    src = os.path.join(CSRC, "eval.hip")
+    out = _run(tmp_path, """
+  printf("%d %d %d %d %d", OVF_BUILD, OVF_WALK, OVF_ANY, OVF_ITEMS,
+         OVF_M2L | OVF_P2P | OVF_OPEN | OVF_STACK | OVF_PATH);
+""")
+    build, walk, every, plan_sets, walk_sets = (int(x) for x in out)
+    assert build & (walk_sets | plan_sets) == 0 and walk & plan_sets == 0
+    assert build | walk_sets == walk and walk | plan_sets == every
+    heeds = {}  # kernel -> mask, from the kernels that look at the bits
+    with open(src) as a, open(os.path.join(CSRC, "m2l_staged.h")) as b:
+        for part in (a.read() + b.read()).split("__global__")[1:]:
+            name = re.search(r"\b(k_\w+)\(", part).group(1)
+            for mask in re.findall(r"(?:tree_incomplete|node_count|level_range)<(OVF_\w+)>\(t", part):
+                heeds.setdefault(name, set()).add(mask)
+    beside_walk = {"k_p2m", "k_m2m", "k_m2m_small"}
+    beside_plan = {"k_m2l", "k_m2l_staged", "k_l2l", "k_l2l_small"}
+    assert heeds == dict({k: {"OVF_BUILD"} for k in beside_walk},
+                         **{k: {"OVF_WALK"} for k in beside_plan},
+                         **{k: {"OVF_ANY"} for k in ("k_p2p", "k_l2p")})

@@ -440,6 +440,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   auto finish = [&](int depth) {
     c->n_nodes = c->hh.lvl_start[FMM_NLEVELS];
     c->depth = depth;
+    c->last = c->hh;
     c->tree_valid = true;
     c->b_reqs.assign(reqs, reqs + n_req);
     c->b_n = n_all;
@@ -453,6 +454,19 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     for (int l = 0; l < FMM_NLEVELS; ++l)
       if (c->hh.lvl_start[l + 1] > c->hh.lvl_start[l]) depth = l;
     return depth;
+  };
+  // The walk's path form does not take open lists of more than WALK_OPEN cells
+  // (wide softening).  It is tried once a build, and after it failed the next
+  // PATH_HOLD builds of systems of that size (within a quarter) or larger walk by
+  // levels at once: else a build of such a system is queued, built and walked two
+  // or three times over.
+  bool paths_ok = c->path_hold <= 0 || a.n_max < c->path_hold_n;
+  if (!paths_ok) --c->path_hold;
+  auto heed_path = [&]() {
+    if (!(c->hh.overflow & OVF_PATH)) return;
+    paths_ok = false;
+    c->path_hold = PATH_HOLD;
+    c->path_hold_n = a.n_max - a.n_max / 4;
   };
   // an error found behind a queued evaluation (whose kernels then do nothing):
   // nothing reads the caller's arrays any more when it is returned
@@ -469,7 +483,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   // 25 us of a 12,526-particle solve.
   const bool direct = build_tree_direct_ok(a.leaf_size);
   const bool one_wg = n_all <= c->small_max && direct;
-  if (one_wg || (direct && c->small_max >= 0 && n_all <= SMALL_TREE_LEAVES * (int64_t)a.leaf_size)) {
+  if (one_wg || (direct && paths_ok && c->small_max >= 0 &&
+                 n_all <= SMALL_TREE_LEAVES * (int64_t)a.leaf_size)) {
     if (one_wg) {
       HIPCHK(c, launch_build_small(c->t, a, c->stream));
     } else {
@@ -515,6 +530,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       }
       return st;
     }
+    heed_path();
   }
   // 1a. split levels predicted from recent builds: tree and walk queued behind
   // the sort, one readback.  The tree equals the one built below whenever the
@@ -523,7 +539,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   const int pred = c->predict_levels ? predicted_levels(c) : 0;
   if (pred > 0) {
     int32_t prev[FMM_NLEVELS + 2];  // level starts of the last tree: grid estimates
-    memcpy(prev, c->hh.lvl_start, sizeof(prev));
+    memcpy(prev, c->last.lvl_start, sizeof(prev));
     const int prev_nodes = c->n_nodes;
     // the evaluation's grids come from the last tree: only for a batch of
     // the same systems within a quarter of its size
@@ -547,8 +563,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, hipEventRecord(c->up_done, c->side));
     }
     // split cells of the last tree
-    const int groups = prev_nodes - c->hh.n_leaves;
-    if (prev_nodes > 0 && groups <= WALK_PATH_GROUPS)
+    const int groups = prev_nodes - c->last.n_leaves;
+    if (paths_ok && prev_nodes > 0 && groups <= WALK_PATH_GROUPS)
       HIPCHK(c, launch_traverse_paths(c->t, a, prev_nodes + prev_nodes / 4, c->stream));
     else
       HIPCHK(c, launch_traverse_dev(c->t, a, pred, c->stream));
@@ -584,6 +600,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       }
       return st;
     }
+    heed_path();
   }
   // 1. tree; one readback of the level sizes (exact launches for the walk).
   // With the direct build the split depth need not be read first.
@@ -640,9 +657,9 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   // node count and level bounds from the header and do nothing if a list
   // buffer overflowed; then the lists are regrown, the walk is redone and
   // *evaluated stays false (the caller evaluates again).
-  bool paths = lvl[FMM_NLEVELS] - c->hh.n_leaves <= WALK_PATH_GROUPS;
+  const bool few_groups = lvl[FMM_NLEVELS] - c->hh.n_leaves <= WALK_PATH_GROUPS;
   for (int attempt = 0; attempt < 10; ++attempt) {
-    if (paths)
+    if (paths_ok && few_groups)
       HIPCHK(c, launch_traverse_paths(c->t, a, lvl[FMM_NLEVELS], c->stream));
     else
       HIPCHK(c, launch_traverse(c->t, a, c->stream));
@@ -674,7 +691,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     const Header &h = c->hh;
     if (h.overflow & OVF_STACK) return fail(c, FMM_EOVERFLOW, "walk descent stack overflow");
     if (h.overflow & (OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS | OVF_PATH)) {
-      if (h.overflow & OVF_PATH) paths = false;
+      heed_path();
       if (h.overflow & OVF_M2L) {
         st = regrow_lists(c, OVF_M2L, h.m2l_cursor);
         if (st != FMM_OK) return st;

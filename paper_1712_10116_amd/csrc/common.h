@@ -302,7 +302,7 @@ hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels,
 // it took 175 us against some 280 by levels, at 2,769 (2^20 sphere) a
 // workgroup per group takes longer than the wavefront form's 168.
 #define WALK_PATH_GROUPS 1600
-#define WALK_PATH_SMALL_GRID 512  // workgroups for a tree of unknown, small size
+#define PATH_HOLD 32  // builds that walk by levels after a path walk failed
 // the whole walk in one launch (trees of few split cells), sizes read on the
 // device; flags OVF_PATH when an open list is too long for it
 hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, hipStream_t s);

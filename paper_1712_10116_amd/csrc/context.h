@@ -16,8 +16,9 @@ struct fmm_ctx {
   int device;
   DevTree t;
   std::vector<void *> allocs;
-  // host copy of the last build
-  Header hh;
+  // host copy of the header last read, and of the last complete build's (sizes to
+  // expect of the next)
+  Header hh, last;
   bool tree_valid;
   std::vector<fmm_request> b_reqs;  // requests of the last build
   int64_t b_n;                      // their active particles in all
@@ -46,6 +47,9 @@ struct fmm_ctx {
   int lvl_hist[LEVEL_HIST];
   int lvl_hist_n;
   bool predict_levels;
+  // builds still to walk by levels, of systems of at least path_hold_n particles
+  // (the path form failed for one: see build_impl)
+  int path_hold, path_hold_n;
   // integrator
   hhs_run *own_run;       // scratch of hhs_init / hhs_step (one system)
   int32_t *split_cnt;     // [cap_split] fast-set sizes of pending splits

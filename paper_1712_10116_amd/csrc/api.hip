@@ -522,7 +522,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     if (c->hh.nonfinite) return fail_queued(FMM_ENONFINITE, "non-finite input position");
     if (c->hh.overflow & OVF_STACK) return fail_queued(FMM_EOVERFLOW, "walk descent stack overflow");
     if (!(c->hh.overflow & OVF_ANY)) {
-      record_levels(c, std::min(FMM_MAXLEVEL, c->hh.max_prefix + 1));
+      // a tree of one workgroup says nothing about the depth of larger ones
+      if (!one_wg) record_levels(c, std::min(FMM_MAXLEVEL, c->hh.max_prefix + 1));
       st = finish(tree_depth());
       if (st == FMM_OK && fuse) {
         count_evaluation(c, n_req, reqs);

@@ -1,0 +1,33 @@
+"""Level prediction in a context that solves systems of different sizes.
+
+* Solves of a few hundred particles between those of a large system (the rungs
+  of an integrator) leave its predicted depth alone: one sort and one walk each."""
+import numpy as np
+import pytest
+
+from conftest import gpu_available
+from paper_1712_10116_amd import workloads as W
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a GPU")]
+
+
+def test_small_solves_between_large_ones():
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    prm = dict(eps=0.01, theta=0.5, p=4)
+    large, small = ([torch.from_numpy(x).cuda() for x in (s[0], s[2])]
+                    for s in (W.plummer(30000, seed=61), W.uniform_sphere(500, seed=62)))
+    s = F.Solver(30000, p_max=4, leaf_size=16, kernel=0, precision=0)
+    s.set_level_prediction(True)
+    s.forces(*large, **prm)
+    ref = [x.clone() for x in s.forces(*large, **prm)]
+    for _ in range(5):
+        s.forces(*small, **prm)
+    s.profile(True)
+    out = s.forces(*large, **prm)
+    prof = s.profile_read()
+    assert (prof["sort"][1], prof["walk"][1]) == (1, 1)
+    for a, b in zip(out, ref):
+        assert torch.equal(a, b)
+    s.close()

@@ -563,12 +563,13 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, launch_upward(c->t, u, c->side));
       HIPCHK(c, hipEventRecord(c->up_done, c->side));
     }
-    // split cells of the last tree
-    const int groups = prev_nodes - c->last.n_leaves;
-    if (paths_ok && prev_nodes > 0 && groups <= WALK_PATH_GROUPS)
-      HIPCHK(c, launch_traverse_paths(c->t, a, prev_nodes + prev_nodes / 4, c->stream));
-    else
+    if (paths_ok && walk_paths_expected(prev_nodes - c->last.n_leaves, c->b_n, n_all)) {
+      const int64_t cells = prev_nodes * n_all / c->b_n;
+      HIPCHK(c, launch_traverse_paths(c->t, a, (int)std::min(c->t.cap_nodes, cells + cells / 4 + 64),
+                                      c->stream));
+    } else {
       HIPCHK(c, launch_traverse_dev(c->t, a, pred, c->stream));
+    }
     if (!fuse) {
       HIPCHK(c, launch_p2p_plan(c->t, a, c->stream));
       HIPCHK(c, hipMemcpyAsync(c->pin_hdr, c->t.hdr, sizeof(Header), hipMemcpyDeviceToHost,

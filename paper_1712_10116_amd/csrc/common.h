@@ -302,6 +302,11 @@ hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels,
 // it took 175 us against some 280 by levels, at 2,769 (2^20 sphere) a
 // workgroup per group takes longer than the wavefront form's 168.
 #define WALK_PATH_GROUPS 1600
+// Whether a tree of n particles, not yet built, is expected to have that few split
+// cells: those of the last tree (of last_n) in proportion.
+static inline bool walk_paths_expected(int64_t last_groups, int64_t last_n, int64_t n) {
+  return last_n > 0 && (last_groups + 1) * n <= (int64_t)WALK_PATH_GROUPS * last_n;
+}
 #define PATH_HOLD 32  // builds that walk by levels after a path walk failed
 // the whole walk in one launch (trees of few split cells), sizes read on the
 // device; flags OVF_PATH when an open list is too long for it

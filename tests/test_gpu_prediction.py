@@ -1,7 +1,9 @@
 """Level prediction in a context that solves systems of different sizes.
 
 * Solves of a few hundred particles between those of a large system (the rungs
-  of an integrator) leave its predicted depth alone: one sort and one walk each."""
+  of an integrator) leave its predicted depth alone: one sort and one walk each.
+* Systems of very different sizes in turn: the walk's form for the next one does
+  not follow the last one's tree; values equal those of a fresh context."""
 import numpy as np
 import pytest
 
@@ -30,4 +32,27 @@ def test_small_solves_between_large_ones():
     assert (prof["sort"][1], prof["walk"][1]) == (1, 1)
     for a, b in zip(out, ref):
         assert torch.equal(a, b)
+    s.close()
+
+
+def test_sizes_in_turn():
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    prm = dict(eps=0.01, theta=0.5, p=4)
+    kw = dict(p_max=4, leaf_size=16, kernel=0, precision=0)
+    systems = [[torch.from_numpy(x).cuda() for x in (s[0], s[2])]
+               for s in (W.plummer(7000, seed=63), W.plummer(400000, seed=64))]
+    ref = []
+    for pos, m in systems:
+        f = F.Solver(m.numel(), **kw)
+        f.build(pos, eps=0.01, theta=0.5)
+        ref.append(f.evaluate(pos, m, p=4))
+        torch.cuda.synchronize()
+        f.close()
+    s = F.Solver(400000, **kw)
+    s.set_level_prediction(True)
+    for k in (0, 0, 1, 1, 0, 1, 0):
+        out = s.forces(*systems[k], **prm)
+        for a, b in zip(out, ref[k]):
+            assert torch.equal(a, b), k
     s.close()

@@ -6,6 +6,7 @@
   without memory behind it;
 * the shares that a leaf's near list is cut into are bounded, and so is the
   memory of their partial sums;
+* the walk's form for a tree not yet built follows its size, not the last tree's;
 * queued kernels heed no overflow bit that a kernel beside them may set."""
 import os
 import re
@@ -119,3 +120,14 @@ def test_kernels_heed_final_overflow_bits(tmp_path):
     assert heeds == dict({k: {"OVF_BUILD"} for k in beside_walk},
                          **{k: {"OVF_WALK"} for k in beside_plan},
                          **{k: {"OVF_ANY"} for k in ("k_p2p", "k_l2p")})
+
+
+def test_walk_form_follows_the_size_of_the_tree_to_come(tmp_path):
+    cases = [  # split cells and particles of the last tree, particles of the next
+        (0, 0, 1000, 0), (0, 10, 10, 1), (0, 10, 1 << 20, 0), (100, 30000, 30000, 1),
+        (100, 30000, 400000, 1), (100, 30000, 1 << 20, 0), (1598, 300007, 300007, 1),
+        (1600, 300007, 300007, 0), (2769, 1 << 20, 1 << 20, 0), (2769, 1 << 20, 300000, 1),
+        (1 << 27, 1 << 30, 1 << 30, 0), (0, 1, 1 << 30, 0)]
+    out = _run(tmp_path, "".join('printf("%%d ", walk_paths_expected(%dll, %dll, %dll));'
+                                 % c[:3] for c in cases))
+    assert [int(x) for x in out] == [c[3] for c in cases]

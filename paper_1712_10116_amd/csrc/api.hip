@@ -734,8 +734,19 @@ extern "C" fmm_status fmm_build_batched(fmm_ctx *c, int n_req, const fmm_request
 static fmm_status evaluate_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, int p,
                                 bool upward_done);
 
+// A runtime call that failed may have left one stream's work without the other's
+// to wait for: neither runs on into the next build.
+static fmm_status settled(fmm_ctx *c, fmm_status st) {
+  if (c && st == FMM_EDEVICE) {
+    (void)hipStreamSynchronize(c->side);
+    (void)hipStreamSynchronize(c->stream);
+    (void)hipGetLastError();
+  }
+  return st;
+}
+
 extern "C" fmm_status fmm_evaluate_batched(fmm_ctx *c, int n_req, const fmm_request *reqs, int p) {
-  return evaluate_impl(c, n_req, reqs, p, false);
+  return settled(c, evaluate_impl(c, n_req, reqs, p, false));
 }
 
 // upward_done: the build of these requests already queued the mass gather,
@@ -774,8 +785,8 @@ extern "C" fmm_status fmm_forces_batched(fmm_ctx *c, int n_req, const fmm_reques
     return fail(c, FMM_EINVAL, "order p=%d unsupported", p);
   bool evaluated = false, upward = false;
   fmm_status st = build_impl(c, n_req, reqs, eps, theta, p, &evaluated, &upward);
-  if (st != FMM_OK || evaluated) return st;
-  return evaluate_impl(c, n_req, reqs, p, upward);
+  if (st != FMM_OK || evaluated) return settled(c, st);
+  return settled(c, evaluate_impl(c, n_req, reqs, p, upward));
 }
 
 static fmm_request one_request(const double *pos, const double *mass, int64_t n_total,

@@ -1076,6 +1076,12 @@ static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   run_m2m<T, P>(t, e, harm, s);
 }
 
+#define RETURN_IF(call)                     \
+  do {                                      \
+    const hipError_t e_ = (call);           \
+    if (e_ != hipSuccess) return e_;        \
+  } while (0)
+
 // Launch order: P2P goes to the side stream (after the walk and the mass
 // gather, by an event) and runs concurrently with M2L and L2L on the main
 // stream, which waits for it (second event) before L2P adds the near field.
@@ -1083,17 +1089,17 @@ static void run_upward(const DevTree &t, const EvalArgs &e, hipStream_t s) {
 // queued them on the side stream beside the walk (e.upward_done): then the
 // main stream waits for e.up_done instead.
 template <typename T, int P, int KERNEL>
-static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
+static hipError_t run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   const int nn = e.n_nodes;  // exact, or (e.dev) an estimate that sets grid sizes
   const int ga = e.dev && !e.exact ? nn + nn / 4 + 64 : nn;
   const int narg = e.dev ? -1 : nn;  // -1: node count read on the device
   PhaseTimer *tm = e.tm;
-  hipEventRecord(e.fork, s);
-  hipStreamWaitEvent(e.side, e.fork, 0);
-  if (e.plan) {
-    launch_p2p_plan(t, *e.plan, e.side);
-    hipMemcpyAsync(e.pin_hdr, t.hdr, sizeof(Header), hipMemcpyDeviceToHost, e.side);
-    hipEventRecord(e.hdr_ev, e.side);
+  RETURN_IF(hipEventRecord(e.fork, s));
+  RETURN_IF(hipStreamWaitEvent(e.side, e.fork, 0));
+  if (e.plan) {  // the host decides by the header copied here
+    RETURN_IF(launch_p2p_plan(t, *e.plan, e.side));
+    RETURN_IF(hipMemcpyAsync(e.pin_hdr, t.hdr, sizeof(Header), hipMemcpyDeviceToHost, e.side));
+    RETURN_IF(hipEventRecord(e.hdr_ev, e.side));
   }
   const int tp = tm ? tm->begin(PH_P2P, e.side) : -1;
   const int p2p_blocks = (p2p_grid_items(e.n, ga) + P2P_WAVES - 1) / P2P_WAVES;
@@ -1104,9 +1110,9 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     hipLaunchKernelGGL((k_p2p<(sizeof(T) == 4), KERNEL, true>), dim3(p2p_blocks),
                        dim3(P2P_WAVES * 64), 0, e.side, t, e.eps);
   if (tm) tm->end(tp, e.side);
-  hipEventRecord(e.join, e.side);
+  RETURN_IF(hipEventRecord(e.join, e.side));
   if (e.upward_done)
-    hipStreamWaitEvent(s, e.up_done, 0);  // P2M / M2M ran beside the walk
+    RETURN_IF(hipStreamWaitEvent(s, e.up_done, 0));  // P2M / M2M ran beside the walk
   else
     run_upward<T, P, KERNEL>(t, e, s);
   if (tm) {
@@ -1119,22 +1125,23 @@ static void run_passes(const DevTree &t, const EvalArgs &e, hipStream_t s) {
     tm->start(PH_DOWN, s);
   }
   run_l2l<T, P>(t, e, s);
-  hipStreamWaitEvent(s, e.join, 0);
+  RETURN_IF(hipStreamWaitEvent(s, e.join, 0));
   hipLaunchKernelGGL((k_l2p<T, P>), dim3((e.n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                      s, t, e.n, e.dev, 1.0);
   if (tm) tm->stop(s);
+  return hipGetLastError();
 }
 
 template <typename T, int KERNEL>
-static bool dispatch_order(const DevTree &t, const EvalArgs &e, hipStream_t s) {
+static hipError_t dispatch_order(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   switch (e.p) {
-    case 1: run_passes<T, 1, KERNEL>(t, e, s); return true;
-    case 2: run_passes<T, 2, KERNEL>(t, e, s); return true;
-    case 3: run_passes<T, 3, KERNEL>(t, e, s); return true;
-    case 4: run_passes<T, 4, KERNEL>(t, e, s); return true;
-    case 5: run_passes<T, 5, KERNEL>(t, e, s); return true;
-    case 6: run_passes<T, 6, KERNEL>(t, e, s); return true;
-    default: return false;
+    case 1: return run_passes<T, 1, KERNEL>(t, e, s);
+    case 2: return run_passes<T, 2, KERNEL>(t, e, s);
+    case 3: return run_passes<T, 3, KERNEL>(t, e, s);
+    case 4: return run_passes<T, 4, KERNEL>(t, e, s);
+    case 5: return run_passes<T, 5, KERNEL>(t, e, s);
+    case 6: return run_passes<T, 6, KERNEL>(t, e, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -1174,13 +1181,9 @@ hipError_t launch_evaluate(const DevTree &t, const EvalArgs &e, hipStream_t s) {
   if (!e.upward_done)
     hipLaunchKernelGGL(k_gather_mass, dim3((e.n + FMM_BLOCK - 1) / FMM_BLOCK), dim3(FMM_BLOCK), 0,
                        s, t, e.n);
-  bool ok;
   if (e.mixed)
-    ok = e.kernel == 1 ? dispatch_order<float, 1>(t, e, s) : dispatch_order<float, 0>(t, e, s);
-  else
-    ok = e.kernel == 1 ? dispatch_order<double, 1>(t, e, s) : dispatch_order<double, 0>(t, e, s);
-  if (!ok) return hipErrorInvalidValue;
-  return hipGetLastError();
+    return e.kernel == 1 ? dispatch_order<float, 1>(t, e, s) : dispatch_order<float, 0>(t, e, s);
+  return e.kernel == 1 ? dispatch_order<double, 1>(t, e, s) : dispatch_order<double, 0>(t, e, s);
 }
 
 // ---------------------------------------------------------------------------

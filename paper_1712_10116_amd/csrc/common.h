@@ -355,10 +355,13 @@ hipError_t launch_upward(const DevTree &t, const EvalArgs &e, hipStream_t s);
 bool eval_order_supported(int p);
 // Wavefronts for the near-field items of a tree of n particles and some
 // n_nodes cells; their number is read on the device: about one to two per leaf
-// of a large system, up to one per staged window of a small one.
+// of a large system, up to one per staged window of a small one.  The wavefronts
+// stride over the items, so more than GRID_WAVES (a launch holds less than 2^32
+// threads) are not needed.
+#define GRID_WAVES (1 << 24)
 static inline int p2p_grid_items(int n, int n_nodes) {
   const int64_t w = (n <= 131072 ? 8 : 2) * (int64_t)n_nodes;
-  return (int)(w < 1 ? 1 : w);
+  return (int)(w < 1 ? 1 : w > GRID_WAVES ? GRID_WAVES : w);
 }
 // sources of one staged P2P window
 int p2p_window_sources(bool mixed);

@@ -1233,7 +1233,8 @@ hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells
   launch_reset_lists(t, s);
   if (a.n <= 0) return hipGetLastError();
   if (a.tm) a.tm->start(PH_WALK, s);
-  hipLaunchKernelGGL(k_walk_paths, dim3(std::max(cells, 1)), dim3(WALK_WAVES * 64), 0, s, t,
+  const int blocks = std::min(std::max(cells, 1), GRID_WAVES / WALK_WAVES);
+  hipLaunchKernelGGL(k_walk_paths, dim3(blocks), dim3(WALK_WAVES * 64), 0, s, t,
                      a.theta * a.theta, a.eps);
   if (a.tm) a.tm->stop(s);
   return hipGetLastError();

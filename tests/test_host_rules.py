@@ -7,6 +7,7 @@
 * the shares that a leaf's near list is cut into are bounded, and so is the
   memory of their partial sums;
 * the walk's form for a tree not yet built follows its size, not the last tree's;
+* grids that grow with the tree stay below 2^32 threads;
 * queued kernels heed no overflow bit that a kernel beside them may set."""
 import os
 import re
@@ -131,3 +132,13 @@ def test_walk_form_follows_the_size_of_the_tree_to_come(tmp_path):
     out = _run(tmp_path, "".join('printf("%%d ", walk_paths_expected(%dll, %dll, %dll));'
                                  % c[:3] for c in cases))
     assert [int(x) for x in out] == [c[3] for c in cases]
+
+
+def test_near_field_grid_stays_launchable(tmp_path):
+    trees = [(1, 0), (1000, 90), (131072, 17408), (131073, 17408), (1 << 24, 4000000),
+             (1 << 25, 1 << 25), (1 << 28, (1 << 28) - 1), (100000, (1 << 28) - 1)]
+    out = _run(tmp_path, "".join('printf("%%d ", p2p_grid_items(%d, %d));' % t for t in trees)
+               + 'printf("%d", GRID_WAVES);')
+    for (n, cells), waves in zip(trees, map(int, out)):
+        assert 1 <= waves and waves * 64 < 2 ** 32
+        assert waves == max(1, min((8 if n <= 131072 else 2) * cells, int(out[-1])))

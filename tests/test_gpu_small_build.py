@@ -3,7 +3,10 @@
 * More systems than the context has cells (most of them empty): no cell is
   written past the workspace, which then grows, whether a system is split (leaf
   4) or none can be (leaf 128), with build and evaluation in two calls and in
-  one.  Against the oracle with the parity bound (1e-12)."""
+  one.  Against the oracle with the parity bound (1e-12).
+* Up to 1,024 particles in several systems, some empty, with coincident
+  particles and particles on cell faces: cells, lists and values equal those of
+  the multi-workgroup build bit for bit, system by system and together."""
 import numpy as np
 import pytest
 
@@ -60,3 +63,55 @@ def test_more_systems_than_cells(oracle, leaf, each, one_call):
             assert np.abs(a - ra).max() <= 1e-12 * np.abs(ra).max()
             assert np.abs(pt - rp).max() <= 1e-12 * np.abs(rp).max()
     s.close()
+
+
+def _lattice(n, seed):
+    """Particles on the faces of their box's cells, in random order."""
+    g = np.random.default_rng(seed)
+    return g.integers(0, 17, (3, n)) / 16.0, g.uniform(0.5, 1.0, n)
+
+
+def _same(n, seed):
+    """Most of the particles at one point."""
+    pos, _, m = W.plummer(n, seed=seed)
+    pos[:, : 2 * n // 3] = pos[:, :1]
+    return pos, m
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("leaf", [1, 7, 64])
+@pytest.mark.parametrize("sizes", [[1024], [1023, 0, 1], [0, 300, 0, 0, 1, 2, 400, 63, 64, 65, 0],
+                                   [0, 0, 5], [64] * 16])
+def test_equals_general_build(sizes, leaf, precision):
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    prm = dict(eps=0.01, theta=0.5)
+    host, dev = _systems(sizes, 900)
+    for k, n in enumerate(sizes):
+        if n >= 64:
+            pos, m = (_lattice, _same)[k % 2](n, 40 + k) if k % 3 else host[k]
+            dev[k].update(pos=torch.from_numpy(pos).cuda(), mass=torch.from_numpy(m).cuda())
+    res = []
+    for small in (True, False):
+        s = F.Solver(1024, p_max=4, leaf_size=leaf, kernel=0, precision=precision)
+        s.set_small_path(small)
+        s.profile(True)
+        s.build_batched(dev, **prm)
+        calls = {k: c for k, (_, c) in s.profile_read().items()}
+        assert (calls["sort"] == 0) == small  # the one-workgroup build has no sort of its own
+        info = s.tree_info()
+        out = [x.cpu().numpy() for o in s.evaluate_batched(dev, p=4) for x in o]
+        trees = []
+        for d, n in zip(dev, sizes):
+            if n:
+                s.build(d["pos"], **prm)
+                trees.append(s.export_tree())
+        res.append((info, out, trees))
+        s.close()
+    (i1, o1, t1), (i2, o2, t2) = res
+    assert i1 == i2
+    for a, b in zip(o1, o2):
+        np.testing.assert_array_equal(a, b)
+    for a, b in zip(t1, t2):
+        for key in a:
+            np.testing.assert_array_equal(a[key], b[key], err_msg=key)

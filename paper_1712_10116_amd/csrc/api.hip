@@ -932,6 +932,13 @@ extern "C" fmm_status fmm_export_tree(fmm_ctx *c, int64_t *perm, int32_t *level,
   HIPCHK(c, d2h(psrc, t.p2p_src, (int64_t)c->hh.p2p_cursor, s));
   HIPCHK(c, hipMemcpyAsync(&hb, t.box, sizeof(Box), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
+  if (n == 0) {  // the root of an empty system: no walk wrote its lists, no key its prefix
+    mcnt.assign(nn, 0);
+    pcnt.assign(nn, 1);  // itself, as fmm_tree_info counts
+    poff.assign(nn, 0);
+    psrc.assign(1, 0);
+    key.assign(1, 0);
+  }
   // canonical pre-order id: nodes sorted by (begin, level)
   std::vector<int64_t> order(nn), canon(nn);
   for (int64_t i = 0; i < nn; ++i) order[i] = i;

@@ -544,8 +544,8 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     const int prev_nodes = c->n_nodes;
     // the evaluation's grids come from the last tree: only for a batch of
     // the same systems within a quarter of its size
-    const bool fuse = p_fused > 0 && n_req == (int)c->b_reqs.size() && 4 * n_all >= 3 * c->b_n &&
-                      4 * n_all <= 5 * c->b_n;
+    const bool fuse = p_fused > 0 && n_all > 0 && n_req == (int)c->b_reqs.size() &&
+                      4 * n_all >= 3 * c->b_n && 4 * n_all <= 5 * c->b_n;
     HIPCHK(c, launch_sort(c->t, a, c->stream));
     if (build_tree_direct_ok(a.leaf_size))
       HIPCHK(c, launch_build_tree_direct(c->t, a, pred, c->stream));

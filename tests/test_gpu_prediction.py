@@ -3,7 +3,8 @@
 * Solves of a few hundred particles between those of a large system (the rungs
   of an integrator) leave its predicted depth alone: one sort and one walk each.
 * Systems of very different sizes in turn: the walk's form for the next one does
-  not follow the last one's tree; values equal those of a fresh context."""
+  not follow the last one's tree; values equal those of a fresh context.
+* An empty system after a solve that failed reads its own header."""
 import numpy as np
 import pytest
 
@@ -55,4 +56,23 @@ def test_sizes_in_turn():
         out = s.forces(*systems[k], **prm)
         for a, b in zip(out, ref[k]):
             assert torch.equal(a, b), k
+    s.close()
+
+
+def test_empty_system_after_a_failed_solve():
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    prm = dict(eps=0.01, theta=0.5, p=4)
+    pos, m = (torch.from_numpy(x).cuda() for x in W.plummer(5000, seed=65)[::2])
+    none = torch.zeros(0, dtype=torch.int32, device="cuda")
+    bad = pos.clone()
+    bad[2, 17] = float("nan")
+    s = F.Solver(5000, p_max=4, leaf_size=2048, kernel=0, precision=0)
+    s.set_level_prediction(True)
+    s.forces(pos, m, **prm)
+    s.forces(pos, m, none, **prm)
+    with pytest.raises(F.FMMError):
+        s.forces(bad, m, **prm)
+    s.forces(pos, m, none, **prm)
+    assert s.tree_info()["n"] == 0 and s.tree_info()["nodes"] == 1
     s.close()

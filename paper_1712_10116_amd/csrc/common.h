@@ -285,6 +285,32 @@ struct BuildArgs {
 };
 
 // tree.hip
+#define MSORT_TILE 1024  // slots of a tile of the merge sort
+#define MSORT_FAN 16     // runs merged at a time
+// Merges of the merge sort over a batch of n particles in n_req systems, the largest
+// of n_max: until a run holds the largest system (one system starts at slot 0,
+// others anywhere in a tile).  -1: the radix sort is the faster.  A merge reads 15
+// searches a key, so what it costs grows with n and with the runs it joins; the
+// radix passes are 27 launches that 500,000 keys do not fill.  `full`: merges
+// without the one that joins two runs only, for systems that start within a tile.
+// Sort of a build, us, merge and radix, in systems of the size given:
+//   1: 4.2 M in 3,000 467 and 765, 16.8 M in 10,007 2505 and 3169, in 16,384 2647
+//      and 3491;
+//   2: 0.5 M in 131,072 143 and 193, 1.05 M 233 and 224, 4.2 M 895 and 676; 0.5 M
+//      in 262,144 179 and 191, 1.05 M 301 and 223;
+//   3: one of 300,007 146 and 153, 393,216 160 and 161, 430,000 185 and 162.
+static inline int sort_merges(int n, int n_max, int n_req) {
+  const int64_t reach = n_req == 1 ? n : (int64_t)n_max + MSORT_TILE - 1;
+  int merges = 0, full = 0;
+  for (int64_t R = MSORT_TILE; R < reach; R *= MSORT_FAN) {
+    ++merges;
+    full += R < n_max;
+  }
+  const int most = full <= 1 ? INT32_MAX
+                   : full == 2 ? (n_max <= 131072 ? 917504 : 589824)
+                   : full == 3 ? 393216 : 0;
+  return n <= most ? merges : -1;
+}
 hipError_t launch_sort(const DevTree &t, const BuildArgs &a, hipStream_t s);
 // whole build up to the walk in one workgroup (a.n <= SMALL_N)
 hipError_t launch_build_small(const DevTree &t, const BuildArgs &a, hipStream_t s);

@@ -7,7 +7,7 @@
 //   2. 63-bit Morton keys from q_d = clamp(floor((x_d - o_d) s), 0, 2^21-1),
 //      x bits at 3b+2, y at 3b+1, z at 3b;
 //   3. stable sort of (key, active slot): tiles sorted in LDS and merged by
-//      rank, or for systems of more than MSORT_MAX_N particles an LSD radix
+//      rank, or for large systems and batches (sort_merges) an LSD radix
 //      sort, 8 passes of 8 bits, ranks inside a wavefront from 8 ballots per 64
 //      keys;
 //   4. top-down split (the paper's recursive build, Sec. 2.3, done level by
@@ -334,9 +334,8 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
 }
 
 // ---------------------------------------------------------------------------
-// Merge sort, for batches whose largest system has at most MSORT_MAX_N
-// particles: tiles of 1024 slots sorted in LDS (the kernel that makes the
-// keys), then 16 runs at a time merged by rank.  An element's place in the
+// Merge sort, where sort_merges finds it the faster: tiles of 1024 slots sorted
+// in LDS (the kernel that makes the keys), then 16 runs at a time merged by rank.  An element's place in the
 // merged run is its place in its own run plus, for each other run, the number
 // of keys before it there, a binary search; the searches of 8 runs go on side
 // by side, so a merge costs some 20 dependent reads whatever its size.  The 8
@@ -353,10 +352,6 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(
 // keep slot order: runs before its own count keys up to and including an
 // element's, runs after it keys below.
 // ---------------------------------------------------------------------------
-#define MSORT_TILE 1024
-#define MSORT_FAN 16
-#define MSORT_MAX_N 524288
-
 // Sorted LDS runs of RUN elements merged four at a time: the element at
 // position p of kin (its system's slots lie in [s0, s1) of the tile) moves to
 // its place in kout.
@@ -1163,12 +1158,8 @@ hipError_t launch_sort(const DevTree &t, const BuildArgs &a, hipStream_t s) {
     hipLaunchKernelGGL(k_header_init, dim3(1), dim3(1), 0, s, t);
     hipLaunchKernelGGL(k_boxes, dim3((a.n_req + 3) / 4), dim3(FMM_BLOCK), 0, s, t, a.leaf_size);
   }
-  if (n > 0 && a.n_max <= MSORT_MAX_N) {
-    // merges until a run holds the largest system; one system starts at slot
-    // 0, others anywhere in a tile
-    const int64_t reach = a.n_req == 1 ? n : (int64_t)a.n_max + MSORT_TILE - 1;
-    int merges = 0;
-    for (int64_t R = MSORT_TILE; R < reach; R *= MSORT_FAN) ++merges;
+  const int merges = sort_merges(n, a.n_max, a.n_req);
+  if (n > 0 && merges >= 0) {
     // the result always lands in key / slot
     uint64_t *k0 = merges & 1 ? t.key2 : t.key, *k1 = merges & 1 ? t.key : t.key2;
     int32_t *s0 = merges & 1 ? t.slot2 : t.slot, *s1 = merges & 1 ? t.slot : t.slot2;

@@ -3,7 +3,8 @@
 The tree's permutation against numpy's stable sort of the keys (formed here as
 the build defines them), and for several systems each one's own solve.  Sizes
 around the tiles (1,024) and merges (16 tiles, 256 tiles: three merges above
-262,144), the radix sort above 524,288; keys equal across tiles and runs."""
+262,144), and around the change to the radix sort; keys equal across tiles and
+runs."""
 import numpy as np
 import pytest
 
@@ -39,7 +40,8 @@ def _particles(n, kind, seed):
 
 
 @pytest.mark.parametrize("kind", ["random", "equal", "sorted", "reversed"])
-@pytest.mark.parametrize("n", [1023, 1024, 1025, 2049, 16384, 16385, 262144, 262145, 524288, 524289])
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 2049, 16384, 16385, 262144, 262145, 393216, 393217,
+                               524289])
 def test_one_system(n, kind):
     import torch
     from paper_1712_10116_amd import fmm as F
@@ -54,7 +56,9 @@ def test_one_system(n, kind):
 
 @pytest.mark.parametrize("kind", ["random", "equal"])
 @pytest.mark.parametrize("sizes", [[1000, 1100, 0, 1, 3000, 24, 1024, 17000, 5, 16400],
-                                   [300, 263000, 700, 40], [524289, 3, 2000]])
+                                   [300, 263000, 700, 40], [524289, 3, 2000],
+                                   [200000, 189824, 200000], [200000, 189825, 200000],
+                                   [131072] * 6 + [131071, 1], [131072] * 6 + [131071, 2]])
 def test_several_systems(sizes, kind):
     import torch
     from paper_1712_10116_amd import fmm as F

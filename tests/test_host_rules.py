@@ -7,6 +7,8 @@
 * the shares that a leaf's near list is cut into are bounded, and so is the
   memory of their partial sums;
 * the walk's form for a tree not yet built follows its size, not the last tree's;
+* the merge sort is taken where it measured faster than the radix sort, with
+  merges enough for the largest system wherever it starts in a tile;
 * grids that grow with the tree stay below 2^32 threads;
 * queued kernels heed no overflow bit that a kernel beside them may set."""
 import os
@@ -142,3 +144,29 @@ def test_near_field_grid_stays_launchable(tmp_path):
     for (n, cells), waves in zip(trees, map(int, out)):
         assert 1 <= waves and waves * 64 < 2 ** 32
         assert waves == max(1, min((8 if n <= 131072 else 2) * cells, int(out[-1])))
+
+
+def test_sort_rule(tmp_path):
+    # (largest system, systems, us of the radix sort, us of the merge sort)
+    measured = [
+        (32768, 1, 131.9, 57.9), (131072, 1, 139.5, 71.8), (262144, 1, 151.4, 105.6),
+        (300007, 1, 152.9, 145.6), (393216, 1, 160.6, 159.6), (430000, 1, 162.2, 185.0),
+        (524288, 1, 169.2, 218.8), (1 << 20, 1, 197.8, 373.7), (3000, 43, 162.0, 47.7),
+        (131072, 4, 192.8, 143.0), (131072, 8, 223.7, 232.7), (100003, 5, 191.3, 139.8),
+        (100003, 10, 223.5, 231.5), (200003, 2, 184.2, 148.8), (200003, 5, 221.6, 283.5),
+        (262144, 2, 190.7, 179.3), (16384, 64, 242.8, 186.6), (16384, 1024, 3490.9, 2647.4),
+        (262144, 4, 222.5, 300.9),
+        (300007, 3, 218.5, 308.7), (65536, 64, 682.6, 853.8), (10007, 1676, 3168.9, 2505.2),
+        (3000, 5592, 3199.7, 1821.9), (524288, 32, 2779.9, 5288.3)]
+    edges = [(n, n, 1) for n in (1, 1024, 1025, 16384, 16385, 262144, 262145, 393216, 393217)]
+    edges += [(917504, 100000, 10), (917505, 100000, 10), (589824, 200000, 3), (589825, 200000, 3),
+              (2000, 2, 1000), (1 << 30, 16384, 70000), (1 << 30, 16385, 70000)]
+    calls = [(n * k, n, k) for n, k, _, _ in measured] + edges
+    out = [int(x) for x in _run(tmp_path, "".join(
+        'printf("%%d ", sort_merges(%d, %d, %d));' % c for c in calls))]
+    for (n, k, radix, merge), m in zip(measured, out):
+        assert (m >= 0) == (merge < radix), (n, k, m)
+    for (n, n_max, k), m in zip(calls, out):
+        reach = n if k == 1 else n_max + 1023
+        assert m < 0 or 1024 * 16 ** m >= reach > (1024 * 16 ** (m - 1) if m else 0)
+    assert out[len(measured):] == [0, 0, 1, 1, 2, 2, 3, 3, -1, 2, -1, 2, -1, 1, 2, -1]

@@ -96,10 +96,13 @@ static void free_nodes(fmm_ctx *c) {
   c->t.cap_nodes = 0;
 }
 
+// entries of a list buffer, at most: offsets into it are int32
+static const int64_t MAX_LIST = INT32_MAX;
+
 // capacities of a context that has grown nothing
 static int64_t first_nodes(const fmm_ctx *c) { return 8 * c->max_n / c->prm.leaf_size + 1024; }
 static int64_t first_list(int which, int64_t cap_nodes) {
-  return (which == OVF_M2L ? 96 : which == OVF_P2P ? 32 : 16) * cap_nodes;
+  return std::min<int64_t>((which == OVF_M2L ? 96 : which == OVF_P2P ? 32 : 16) * cap_nodes, MAX_LIST);
 }
 
 // Request-sized arrays (regrown when a batch holds more requests).  The
@@ -361,7 +364,10 @@ static fmm_status read_header(fmm_ctx *c) {
 static fmm_status regrow_lists(fmm_ctx *c, int which, int64_t need) {
   DevTree &t = c->t;
   const int64_t old = which == OVF_M2L ? t.cap_m2l : which == OVF_P2P ? t.cap_p2p : t.cap_open;
-  int64_t cap = std::max(need + need / 4 + 1024, old > 0 ? 2 * old : first_list(which, t.cap_nodes));
+  if (need > MAX_LIST || old == MAX_LIST)
+    return fail(c, FMM_EOVERFLOW, "interaction lists of more than 2^31 - 1 entries");
+  const int64_t cap = std::min(
+      MAX_LIST, std::max(need + need / 4 + 1024, old > 0 ? 2 * old : first_list(which, t.cap_nodes)));
   if (which == OVF_M2L) {
     if (!fmm_regrow(c, &t.m2l_src, &t.cap_m2l, cap)) return fail(c, FMM_ENOMEM, "M2L list regrow failed");
   } else if (which == OVF_P2P) {
@@ -695,17 +701,17 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     if (h.overflow & (OVF_M2L | OVF_P2P | OVF_OPEN | OVF_ITEMS | OVF_PATH)) {
       heed_path();
       if (h.overflow & OVF_M2L) {
-        st = regrow_lists(c, OVF_M2L, h.m2l_cursor);
+        st = regrow_lists(c, OVF_M2L, (int64_t)h.m2l_cursor);
         if (st != FMM_OK) return st;
       }
       if (h.overflow & OVF_P2P) {
-        st = regrow_lists(c, OVF_P2P, h.p2p_cursor);
+        st = regrow_lists(c, OVF_P2P, (int64_t)h.p2p_cursor);
         if (st != FMM_OK) return st;
       }
       if (h.overflow & OVF_OPEN) {
-        uint32_t mx = 0;
+        unsigned long long mx = 0;
         for (int l = 0; l < FMM_NLEVELS; ++l) mx = std::max(mx, h.open_cursor[l]);
-        st = regrow_lists(c, OVF_OPEN, mx);
+        st = regrow_lists(c, OVF_OPEN, (int64_t)mx);
         if (st != FMM_OK) return st;
       }
       if (h.overflow & OVF_ITEMS) {
@@ -885,12 +891,12 @@ extern "C" fmm_status fmm_tree_info(fmm_ctx *c, int64_t info[9]) {
   int64_t leaves = h.n_leaves;
   info[0] = c->b_n;  // active particles over all requests
   info[1] = c->n_nodes;
-  info[2] = h.m2l_cursor / 2;
+  info[2] = (int64_t)(h.m2l_cursor / 2);
   info[3] = ((int64_t)h.p2p_cursor - leaves) / 2 + leaves;
   info[4] = c->depth;
   info[5] = leaves;
-  info[6] = h.m2l_cursor;
-  info[7] = h.p2p_cursor;
+  info[6] = (int64_t)h.m2l_cursor;
+  info[7] = (int64_t)h.p2p_cursor;
   info[8] = (int64_t)h.p2p_pairs;
   return FMM_OK;
 }

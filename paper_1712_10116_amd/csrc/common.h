@@ -56,9 +56,12 @@
 
 struct Header {
   int32_t lvl_start[FMM_NLEVELS + 2];  // nodes of level l: [lvl_start[l], lvl_start[l+1])
-  uint32_t m2l_cursor;                 // ordered M2L entries written (or needed)
-  uint32_t p2p_cursor;                 // ordered P2P entries written (or needed)
-  uint32_t open_cursor[FMM_NLEVELS];   // open-list entries per level
+  // list entries written (or needed): counted in 64 bits, since lists that do not
+  // fit are counted too, and some 50,000 leaves that all list each other already
+  // need 2^31 (capacities stay below that: the lists' offsets are int32)
+  unsigned long long m2l_cursor;               // ordered M2L entries
+  unsigned long long p2p_cursor;               // ordered P2P entries
+  unsigned long long open_cursor[FMM_NLEVELS]; // open-list entries per level
   int32_t overflow;                    // OVF_* bits
   int32_t nonfinite;                   // an input position was not finite (OVF_INPUT too)
   unsigned long long p2p_pairs;        // ordered particle interactions in P2P
@@ -214,6 +217,13 @@ __device__ __forceinline__ int wave_excl_scan_int(int v, int *total) {
   x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
   *total = __builtin_amdgcn_readlane(x, 63);
   return x - v;
+}
+
+// v of a lane, the same in every lane
+__device__ __forceinline__ unsigned long long readlane_u64(unsigned long long v, int lane) {
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)v, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(v >> 32), lane);
+  return (unsigned long long)hi << 32 | lo;
 }
 
 // ---------------------------------------------------------------------------

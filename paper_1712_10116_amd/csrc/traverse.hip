@@ -382,7 +382,7 @@ __device__ __forceinline__ bool allocate_lists(const DevTree &t, int l, const Gr
                                                const int (&mine)[3], int (&o)[3]) {
   const int lane = threadIdx.x & 63;
   Header *h = t.hdr;
-  unsigned *const cur[3] = {&h->m2l_cursor, &h->p2p_cursor, &h->open_cursor[l]};
+  unsigned long long *const cur[3] = {&h->m2l_cursor, &h->p2p_cursor, &h->open_cursor[l]};
   const int64_t cap[3] = {t.cap_m2l, t.cap_p2p, t.cap_open};
   const int ovf_bit[3] = {OVF_M2L, OVF_P2P, OVF_OPEN};
   int bits = 0, incl[3], tot[3];
@@ -398,14 +398,14 @@ __device__ __forceinline__ bool allocate_lists(const DevTree &t, int l, const Gr
   }
   // lane k allocates list k: the three in one instruction, one round trip
   const int tk = lane == 0 ? tot[0] : lane == 1 ? tot[1] : tot[2];
-  int got = 0;
+  unsigned long long got = 0;
   if (lane < 3 && tk > 0)
-    got = (int)atomicAdd(lane == 0 ? cur[0] : lane == 1 ? cur[1] : cur[2], (unsigned)tk);
+    got = atomicAdd(lane == 0 ? cur[0] : lane == 1 ? cur[1] : cur[2], (unsigned long long)tk);
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const int base = __builtin_amdgcn_readlane(got, k);
-    o[k] = base + incl[k] - mine[k];
-    if (lane < G.n && (int64_t)base + tot[k] > cap[k]) bits |= ovf_bit[k];
+    const int64_t base = (int64_t)readlane_u64(got, k);
+    o[k] = (int)base + incl[k] - mine[k];
+    if (lane < G.n && base + tot[k] > cap[k]) bits |= ovf_bit[k];
   }
   const bool ovf = __ballot(bits != 0) != 0ull;
   if (lane < G.n) {
@@ -771,7 +771,7 @@ __device__ __forceinline__ void wave_parent(const DevTree &t, int l, int P, doub
   int o[3] = {0, 0, 0};
   int bits = 0;
   {
-    unsigned *const cur[3] = {&h->m2l_cursor, &h->p2p_cursor, &h->open_cursor[l]};
+    unsigned long long *const cur[3] = {&h->m2l_cursor, &h->p2p_cursor, &h->open_cursor[l]};
     const int64_t cap[3] = {t.cap_m2l, t.cap_p2p, t.cap_open};
     const int ovf_bit[3] = {OVF_M2L, OVF_P2P, OVF_OPEN};
     int incl[3], tot[3];
@@ -787,14 +787,14 @@ __device__ __forceinline__ void wave_parent(const DevTree &t, int l, int P, doub
     }
     // lane k allocates list k: the three in one instruction, one round trip
     const int tk = lane == 0 ? tot[0] : lane == 1 ? tot[1] : tot[2];
-    int got = 0;
-    if (lane < 3 && tk > 0) got = (int)atomicAdd(lane == 0 ? cur[0] : lane == 1 ? cur[1] : cur[2],
-                                                 (unsigned)tk);
+    unsigned long long got = 0;
+    if (lane < 3 && tk > 0)
+      got = atomicAdd(lane == 0 ? cur[0] : lane == 1 ? cur[1] : cur[2], (unsigned long long)tk);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const int base = __shfl(got, k, 64);
-      o[k] = base + incl[k] - mine[k];
-      if (lane < S.n && (int64_t)base + tot[k] > cap[k]) bits |= ovf_bit[k];
+      const int64_t base = (int64_t)readlane_u64(got, k);
+      o[k] = (int)base + incl[k] - mine[k];
+      if (lane < S.n && base + tot[k] > cap[k]) bits |= ovf_bit[k];
     }
   }
   // if any target's lists do not fit, the wavefront writes none of them and
@@ -944,7 +944,7 @@ __global__ __launch_bounds__(WALK_WAVES * 64, 4) void k_walk_paths(DevTree t, do
     const int4 ip = t.ninfo[P];
     if (P < t.n_req && threadIdx.x == 0) {  // a root: itself its only candidate
       const bool leaf = ip.y == 0;
-      const int64_t at = leaf ? (int64_t)atomicAdd(&h->p2p_cursor, 1u) : 0;
+      const int64_t at = leaf ? (int64_t)atomicAdd(&h->p2p_cursor, 1ull) : 0;
       const bool fits = at < t.cap_p2p;
       if (leaf && !fits) atomicOr(&h->overflow, OVF_P2P);
       if (leaf && fits) t.p2p_src[at] = P;

@@ -391,12 +391,14 @@ hipError_t launch_upward(const DevTree &t, const EvalArgs &e, hipStream_t s);
 bool eval_order_supported(int p);
 // Wavefronts for the near-field items of a tree of n particles and some
 // n_nodes cells; their number is read on the device: about one to two per leaf
-// of a large system, up to one per staged window of a small one.  The wavefronts
-// stride over the items, so more than GRID_WAVES (a launch holds less than 2^32
-// threads) are not needed.
+// of a large system, up to one per staged window of a small one of few leaves.
+// The wavefronts stride over the items, so more than GRID_WAVES (a launch holds
+// less than 2^32 threads) are not needed, and one without an item costs 0.25 ns
+// (100,000 particles in leaves of 4, 8 for each of 68,350 cells: P2P 106 -> 219 us).
 #define GRID_WAVES (1 << 24)
 static inline int p2p_grid_items(int n, int n_nodes) {
-  const int64_t w = (n <= 131072 ? 8 : 2) * (int64_t)n_nodes;
+  int64_t w = 2 * (int64_t)n_nodes;
+  if (n <= 131072) w = n_nodes > 32768 ? n_nodes : n_nodes > 4096 ? 32768 : 8 * (int64_t)n_nodes;
   return (int)(w < 1 ? 1 : w > GRID_WAVES ? GRID_WAVES : w);
 }
 // sources of one staged P2P window
@@ -410,11 +412,29 @@ __host__ __device__ static inline int p2p_share_max(int n) {
   const int s = (1 << 25) / (n > 0 ? n : 1);
   return s > 128 ? 128 : s < 32 ? 32 : s;
 }
-// chunks of 64 list entries in a share of whole chunks
+// Source windows of a share in a system of n particles (0: shares of whole chunks):
+// small systems have too few leaves to fill the chip, so every window is a share;
+// large ones have leaves enough and are cut only where a list is long (disk galaxy
+// 2^22: solve 14.4 -> 13.1 ms).  Systems of at most 1024 particles have no list
+// longer than a few windows and the multipole passes beside P2P take longer: not
+// cut, which needs no look at the sources.
+#define P2P_SHARE_FINE_N 524288  // largest system cut by windows
+__host__ __device__ static inline int p2p_share_windows(int n) {
+  if (n <= SMALL_N || n > P2P_SHARE_FINE_N) return 0;
+  return n <= 32768 ? 1 : n <= 131072 ? 2 : 4;
+}
+// Chunks of 64 list entries in a share of whole chunks: P2P_SHARE_CHUNKS, or where
+// g windows of `window` sources make a share, as many as hold them at half full
+// leaves.  Two or more (small leaves): the shares are whole chunks then, since a
+// share cut at windows ends with its chunk.  Fewer: cut at windows.
 #define P2P_SHARE_CHUNKS 4
-__host__ __device__ static inline int p2p_share_chunks(int cnt, int share_max) {
+__host__ __device__ static inline int p2p_leaf_chunks(int g, int window, int leaf_size) {
+  return g > 0 ? g * window / (32 * leaf_size) : P2P_SHARE_CHUNKS;
+}
+// at most share_max shares of a list of cnt entries, of at least `chunks` chunks
+__host__ __device__ static inline int p2p_share_chunks(int cnt, int share_max, int chunks) {
   const int per = ((cnt + 63) / 64 + share_max - 1) / share_max;
-  return per > P2P_SHARE_CHUNKS ? per : P2P_SHARE_CHUNKS;
+  return per > chunks ? per : chunks;
 }
 // Strides of the cells' rows at maximum degree p, of coefficients and of folded
 // moments: even, so that every FP64 row starts on 16 bytes, whatever the order

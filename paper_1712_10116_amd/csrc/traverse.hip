@@ -996,28 +996,11 @@ __global__ __launch_bounds__(WALK_WAVES * 64, 4) void k_walk_level(DevTree t, in
 // sinks asked for.  Shares consist of whole windows of the source stream, so
 // the FP32 partial sums of the mixed form are those of the uncut list.
 //
-// Windows per share (0: whole chunks, P2P_SHARE_CHUNKS of them): small systems
-// have too few leaves to fill the chip, so every window is a share; large ones
-// have leaves enough and are cut only where a list is long (disk galaxy 2^22:
-// solve 14.4 -> 13.1 ms).  Systems of at most 1024 particles have no list
-// longer than a few windows and the multipole passes beside P2P take longer:
-// not cut, which needs no look at the sources.  A list that would be cut into
-// more than p2p_share_max shares takes twice or four times the windows a share,
-// or whole chunks, as many as it needs.
+// How many windows or chunks a share has: p2p_share_windows, p2p_leaf_chunks.  A
+// list that would be cut into more than p2p_share_max shares takes twice or four
+// times the windows a share, or whole chunks, as many as it needs.
 #define P2P_SHARE_MAX_LEAF 4096  // larger leaves (coincident particles) are cut by sinks only
-#define P2P_SHARE_FINE_N 524288  // largest system cut by windows
 #define P2P_SHARE_STEPS 3        // windows per share tried: g, 2 g, 4 g
-__device__ __forceinline__ int p2p_share_windows(int n) {
-  if (n <= SMALL_N || n > P2P_SHARE_FINE_N) return 0;
-  return n <= 32768 ? 1 : n <= 131072 ? 2 : 4;
-}
-
-// list entries of a share of a leaf of nA particles whose list of cnt entries is
-// cut by whole chunks into at most share_max
-__device__ __forceinline__ int whole_chunk_entries(const DevTree &t, int nA, int cnt,
-                                                   int share_max) {
-  return nA > P2P_SHARE_MAX_LEAF || t.uncut ? max(cnt, 1) : 64 * p2p_share_chunks(cnt, share_max);
-}
 
 __device__ __forceinline__ void emit_whole_chunks(const DevTree &t, int A, int nA, int cnt, int per,
                                                   int groups, int64_t i0, int64_t r0) {
@@ -1054,7 +1037,8 @@ __device__ __forceinline__ void chunk_windows(const DevTree &t, int off, int cnt
 // and for systems cut by windows the whole wavefront on one leaf after the
 // other (it adds up the source counts of the leaf's chunks).  A workgroup
 // allocates its items and rows with one atomic each.
-__global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw_min) {
+__global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw_min,
+                                                               int leaf_size) {
   __shared__ int s_items[PLAN_WAVES];
   __shared__ unsigned long long s_rows[PLAN_WAVES];
   __shared__ unsigned s_item0;
@@ -1077,9 +1061,14 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
       nA = t.nend[A] - t.nbeg[A];
       cnt = t.p2p_cnt[A];
       off = t.p2p_off[A];
-      g = t.uncut ? 0 : p2p_share_windows(n);
+      g = p2p_share_windows(n);
+      const int chunks = p2p_leaf_chunks(g, t.p2p_src_window, leaf_size);
+      if (chunks > 1 || t.uncut) g = 0;
       share_max = p2p_share_max(n);
-      per = whole_chunk_entries(t, nA, cnt, share_max);
+      // list entries of a share of whole chunks
+      per = nA > P2P_SHARE_MAX_LEAF || t.uncut
+                ? max(cnt, 1)
+                : 64 * p2p_share_chunks(cnt, share_max, max(chunks, 1));
       groups = max(1, (cnt + per - 1) / per);
     }
     // leaves whose chunks are counted, and those cut by windows
@@ -1203,9 +1192,13 @@ hipError_t launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s) 
   // bounds the cells a context holds), a lane per cell where they are not: a
   // workgroup's items then follow 1024 cells in order, and so the XCDs' shares
   const int64_t cells = std::min<int64_t>(t.cap_nodes, (int64_t)a.n + 1024);
-  const int npw = a.n_max > P2P_SHARE_FINE_N ? 64 : 1;
+  const int g = a.n_req == 1 ? p2p_share_windows(a.n_max) : 1;  // 1: of the smallest cut by windows
+  const bool whole = a.n_max > P2P_SHARE_FINE_N || g == 0 ||
+                     p2p_leaf_chunks(g, t.p2p_src_window, a.leaf_size) > 1;
+  const int npw = whole ? 64 : 1;
   const int blocks = (int)std::min<int64_t>(1024, (cells + npw * PLAN_WAVES - 1) / (npw * PLAN_WAVES));
-  hipLaunchKernelGGL(k_p2p_plan, dim3(std::max(blocks, 1)), dim3(PLAN_WAVES * 64), 0, s, t, npw);
+  hipLaunchKernelGGL(k_p2p_plan, dim3(std::max(blocks, 1)), dim3(PLAN_WAVES * 64), 0, s, t, npw,
+                     a.leaf_size);
   return hipGetLastError();
 }
 

@@ -6,7 +6,11 @@ twice and four times the windows a share (32,768 and 131,072 particles, leaf
 64), and whole chunks of the list (9,000 in leaves of 1).  With every pair near,
 the direct sum is the reference: accelerations and potentials of random sinks
 with the parity bounds (FP64 1e-12, mixed 2e-6 rms), their gradient with its own
-(1e-10 of a tensor's size, 1e-5 rms), and the context's memory with its bound."""
+(1e-10 of a tensor's size, 1e-5 rms), and the context's memory with its bound.
+
+Small leaves: shares of whole chunks of the list, on both sides of the sizes where
+a share's length changes, random sinks and the sparsest leaf's against the oracle
+with the same bounds."""
 import numpy as np
 import pytest
 
@@ -66,3 +70,31 @@ def test_wide_softening(n, leaf, precision):
     else:
         assert np.sqrt((eg * eg).mean()) < 1e-5
     s.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("n,leaf", [(1025, 1), (9001, 3), (32768, 5), (32769, 5), (140000, 15),
+                                    (140000, 17)])
+def test_small_leaves(oracle, n, leaf, precision):
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    pos, _, m = W.plummer(n, seed=29)
+    prm = dict(theta=0.5, eps=0.01)
+    t = oracle.Tree(pos, p=4, leaf_size=leaf, kernel=0, **prm)
+    ref = t.export()
+    far = int(np.argmax((pos ** 2).sum(0)))
+    sinks = np.unique(np.append(np.random.default_rng(6).choice(n, 80, replace=False), far))
+    ra, rp = t.evaluate_sinks(m, sinks)[:2]
+    s = F.Solver(n, p_max=4, leaf_size=leaf, kernel=0, precision=precision)
+    a, pt = (x.cpu().numpy() for x in s.forces(*(torch.from_numpy(x).cuda() for x in (pos, m)),
+                                               p=4, **prm))
+    assert s.tree_info()["leaves"] == int((ref["is_leaf"] != 0).sum())
+    s.close()
+    a, pt = a[:, sinks], pt[sinks]
+    mag = np.sqrt((ra * ra).sum(0))
+    e = np.sqrt(((a - ra) ** 2).sum(0)) / np.maximum(mag, 1e-6 * np.sqrt((mag * mag).mean()))
+    ep = np.abs(pt - rp) / np.abs(rp)
+    if precision == 0:
+        assert e.max() < 1e-12 and ep.max() < 1e-12, (e.max(), ep.max())
+    else:
+        assert np.sqrt((e * e).mean()) < 2e-6 and np.sqrt((ep * ep).mean()) < 2e-6

@@ -90,7 +90,7 @@ def test_shares_are_bounded(tmp_path):
   for (int n : ns) {
     const int most = p2p_share_max(n);
     printf("%%d ", most);
-    for (int c : cnts) printf("%%d ", p2p_share_chunks(c, most));
+    for (int c : cnts) printf("%%d ", p2p_share_chunks(c, most, 4));
   }
 """ % (",".join(map(str, ns)), ",".join(map(str, cnts))))]
     for n in ns:
@@ -138,12 +138,17 @@ def test_walk_form_follows_the_size_of_the_tree_to_come(tmp_path):
 
 def test_near_field_grid_stays_launchable(tmp_path):
     trees = [(1, 0), (1000, 90), (131072, 17408), (131073, 17408), (1 << 24, 4000000),
-             (1 << 25, 1 << 25), (1 << 28, (1 << 28) - 1), (100000, (1 << 28) - 1)]
+             (1 << 25, 1 << 25), (1 << 28, (1 << 28) - 1), (100000, (1 << 28) - 1), (100000, 68350),
+             (100000, 4096), (100000, 4097), (100000, 32769)]
     out = _run(tmp_path, "".join('printf("%%d ", p2p_grid_items(%d, %d));' % t for t in trees)
                + 'printf("%d", GRID_WAVES);')
     for (n, cells), waves in zip(trees, map(int, out)):
         assert 1 <= waves and waves * 64 < 2 ** 32
-        assert waves == max(1, min((8 if n <= 131072 else 2) * cells, int(out[-1])))
+        if n > 131072:
+            assert waves == min(2 * cells, int(out[-1]))
+        else:  # one per cell at least, no more than 8, and not many without an item
+            assert min(max(cells, 1), int(out[-1])) <= waves <= max(8 * cells, 1)
+            assert waves <= max(32768, cells)
 
 
 def test_sort_rule(tmp_path):
@@ -170,3 +175,19 @@ def test_sort_rule(tmp_path):
         reach = n if k == 1 else n_max + 1023
         assert m < 0 or 1024 * 16 ** m >= reach > (1024 * 16 ** (m - 1) if m else 0)
     assert out[len(measured):] == [0, 0, 1, 1, 2, 2, 3, 3, -1, 2, -1, 2, -1, 1, 2, -1]
+
+
+def test_small_leaves_share_whole_chunks(tmp_path):
+    cases = [(n, w, leaf) for n in (1024, 1025, 32768, 32769, 131073, 524288, 524289)
+             for w in (256, 384) for leaf in (1, 2, 4, 8, 16, 32, 64, 128, 4096)]
+    out = [int(x) for x in _run(tmp_path, "".join(
+        'printf("%%d %%d ", p2p_share_windows(%d), p2p_leaf_chunks(p2p_share_windows(%d), %d, %d));'
+        % (n, n, w, leaf) for n, w, leaf in cases))]
+    for k, (n, window, leaf) in enumerate(cases):
+        g, chunks = out[2 * k], out[2 * k + 1]
+        if g == 0:
+            assert (n <= 1024 or n > 524288) and chunks == 4
+        elif chunks > 1:  # a share holds no more than its windows where leaves are half full
+            assert 32 * leaf * chunks <= g * window < 32 * leaf * (chunks + 1)
+        else:  # a chunk of half full leaves holds more than half a share
+            assert 64 * leaf > g * window

@@ -488,7 +488,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   // per leaf_size particles; the host's wait for the level sizes cost about
   // 25 us of a 12,526-particle solve.
   const bool direct = build_tree_direct_ok(a.leaf_size);
-  const bool one_wg = n_all <= c->small_max && direct;
+  const bool one_wg = n_all <= c->small_max;  // any leaf size: up to it, nothing is split
   if (one_wg || (direct && paths_ok && c->small_max >= 0 &&
                  n_all <= SMALL_TREE_LEAVES * (int64_t)a.leaf_size)) {
     if (one_wg) {

@@ -67,7 +67,8 @@ def test_empty_system_after_a_failed_solve():
     none = torch.zeros(0, dtype=torch.int32, device="cuda")
     bad = pos.clone()
     bad[2, 17] = float("nan")
-    s = F.Solver(5000, p_max=4, leaf_size=2048, kernel=0, precision=0)
+    s = F.Solver(5000, p_max=4, leaf_size=16, kernel=0, precision=0)
+    s.set_small_path(False)  # the predicted sequence for empty systems too
     s.set_level_prediction(True)
     s.forces(pos, m, **prm)
     s.forces(pos, m, none, **prm)

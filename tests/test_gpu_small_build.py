@@ -6,7 +6,9 @@
   one.  Against the oracle with the parity bound (1e-12).
 * Up to 1,024 particles in several systems, some empty, with coincident
   particles and particles on cell faces: cells, lists and values equal those of
-  the multi-workgroup build bit for bit, system by system and together."""
+  the multi-workgroup build bit for bit, system by system and together.
+* Leaves larger than the build's level search holds (1,024 particles): taken too,
+  since a batch of that few particles is not split then."""
 import numpy as np
 import pytest
 
@@ -115,3 +117,22 @@ def test_equals_general_build(sizes, leaf, precision):
     for a, b in zip(t1, t2):
         for key in a:
             np.testing.assert_array_equal(a[key], b[key], err_msg=key)
+
+
+@pytest.mark.parametrize("leaf", [1024, 1025, 4096])
+@pytest.mark.parametrize("n", [1, 900, 1024])
+def test_leaves_beyond_the_level_search(oracle, n, leaf):
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    prm = dict(eps=0.01, theta=0.5, p=4)
+    pos, _, m = W.plummer(n, seed=33)
+    s = F.Solver(n, p_max=4, leaf_size=leaf, kernel=1, precision=0)
+    tp, tm = torch.from_numpy(pos).cuda(), torch.from_numpy(m).cuda()
+    s.profile(True)
+    a, pt = (x.cpu().numpy() for x in s.forces(tp, tm, **prm))
+    assert s.profile_read()["sort"][1] == 0  # built by one workgroup
+    assert s.tree_info()["nodes"] == 1
+    s.close()
+    ra, rp = oracle.fmm(pos, m, leaf_size=leaf, kernel=1, **prm)
+    assert np.abs(a - ra).max() <= 1e-12 * np.abs(ra).max()
+    assert np.abs(pt - rp).max() <= 1e-12 * np.abs(rp).max()

@@ -497,22 +497,31 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
       HIPCHK(c, launch_sort(c->t, a, c->stream));
       HIPCHK(c, launch_build_tree_direct(c->t, a, FMM_MAXLEVEL, c->stream));
     }
-    const int cells = (int)std::min<int64_t>(c->t.cap_nodes, 5 * (n_all / a.leaf_size) + 64);
+    // no system is split: as many cells as systems.  A solve of 28 particles: 77 us
+    // with the size read back, 102 queued as a tree of unknown size, 74 so
+    const bool roots_only = a.n_max <= a.leaf_size;
+    const int cells = (int)std::min<int64_t>(
+        c->t.cap_nodes, roots_only ? n_req : 5 * (n_all / a.leaf_size) + 64);
     const bool fuse = p_fused > 0 && n_all > 0;
     EvalArgs e = {};
     if (fuse) {
       set_eval_args(c, e, n_all, p_fused, eps);
-      e.n_nodes = cells;
       e.dev = true;
-      e.small_tree = true;
-      HIPCHK(c, hipEventRecord(c->fork, c->stream));
-      HIPCHK(c, hipStreamWaitEvent(c->side, c->fork, 0));
-      HIPCHK(c, launch_upward(c->t, e, c->side));
-      HIPCHK(c, hipEventRecord(c->up_done, c->side));
+      if (roots_only) {  // no M2M or L2L, and a walk too short for P2M to run beside
+        e.n_nodes = n_req;
+        e.exact = true;
+      } else {
+        e.n_nodes = cells;
+        e.small_tree = true;
+        HIPCHK(c, hipEventRecord(c->fork, c->stream));
+        HIPCHK(c, hipStreamWaitEvent(c->side, c->fork, 0));
+        HIPCHK(c, launch_upward(c->t, e, c->side));
+        HIPCHK(c, hipEventRecord(c->up_done, c->side));
+      }
     }
-    HIPCHK(c, launch_traverse_paths(c->t, a, cells, c->stream));
+    HIPCHK(c, launch_traverse_paths(c->t, a, cells, true, c->stream));
     if (fuse) {
-      e.upward_done = true;
+      e.upward_done = !roots_only;
       e.up_done = c->up_done;
       e.plan = &a;
       e.pin_hdr = c->pin_hdr;
@@ -572,7 +581,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
     if (paths_ok && walk_paths_expected(prev_nodes - c->last.n_leaves, c->b_n, n_all)) {
       const int64_t cells = prev_nodes * n_all / c->b_n;
       HIPCHK(c, launch_traverse_paths(c->t, a, (int)std::min(c->t.cap_nodes, cells + cells / 4 + 64),
-                                      c->stream));
+                                      true, c->stream));
     } else {
       HIPCHK(c, launch_traverse_dev(c->t, a, pred, c->stream));
     }
@@ -668,7 +677,7 @@ static fmm_status build_impl(fmm_ctx *c, int n_req, const fmm_request *reqs, dou
   const bool few_groups = lvl[FMM_NLEVELS] - c->hh.n_leaves <= WALK_PATH_GROUPS;
   for (int attempt = 0; attempt < 10; ++attempt) {
     if (paths_ok && few_groups)
-      HIPCHK(c, launch_traverse_paths(c->t, a, lvl[FMM_NLEVELS], c->stream));
+      HIPCHK(c, launch_traverse_paths(c->t, a, lvl[FMM_NLEVELS], attempt == 0, c->stream));
     else
       HIPCHK(c, launch_traverse(c->t, a, c->stream));
     bool queued = false;

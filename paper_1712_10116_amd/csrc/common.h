@@ -346,7 +346,8 @@ static inline bool walk_paths_expected(int64_t last_groups, int64_t last_n, int6
 #define PATH_HOLD 32  // builds that walk by levels after a path walk failed
 // the whole walk in one launch (trees of few split cells), sizes read on the
 // device; flags OVF_PATH when an open list is too long for it
-hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, hipStream_t s);
+hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, bool first,
+                                 hipStream_t s);
 hipError_t launch_reset_lists(const DevTree &t, hipStream_t s);
 // near-field work items of the walk's lists: needed by P2P and L2P only
 hipError_t launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s);

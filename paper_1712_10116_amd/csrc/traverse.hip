@@ -1221,9 +1221,10 @@ hipError_t launch_reset_lists(const DevTree &t, hipStream_t s) {
 }
 
 // the whole walk in one launch; cells: an estimate (or bound) of the tree's
-// cells, for the grid
-hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, hipStream_t s) {
-  launch_reset_lists(t, s);
+// cells, for the grid; first: the header is as the build left it
+hipError_t launch_traverse_paths(const DevTree &t, const BuildArgs &a, int cells, bool first,
+                                 hipStream_t s) {
+  if (!first) launch_reset_lists(t, s);
   if (a.n <= 0) return hipGetLastError();
   if (a.tm) a.tm->start(PH_WALK, s);
   const int blocks = std::min(std::max(cells, 1), GRID_WAVES / WALK_WAVES);

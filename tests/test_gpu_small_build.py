@@ -8,7 +8,9 @@
   particles and particles on cell faces: cells, lists and values equal those of
   the multi-workgroup build bit for bit, system by system and together.
 * Leaves larger than the build's level search holds (1,024 particles): taken too,
-  since a batch of that few particles is not split then."""
+  since a batch of that few particles is not split then.
+* Batches in which no system is split, queued in one call: as build and evaluation
+  in two, bit for bit, and a system without masses left alone."""
 import numpy as np
 import pytest
 
@@ -136,3 +138,27 @@ def test_leaves_beyond_the_level_search(oracle, n, leaf):
     ra, rp = oracle.fmm(pos, m, leaf_size=leaf, kernel=1, **prm)
     assert np.abs(a - ra).max() <= 1e-12 * np.abs(ra).max()
     assert np.abs(pt - rp).max() <= 1e-12 * np.abs(rp).max()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("sizes", [[1], [64], [0, 5, 0, 64, 63], [64] * 16, [7, 64, 0, 33] * 75])
+def test_systems_of_one_cell(sizes, precision):
+    import torch
+    from paper_1712_10116_amd import fmm as F
+    prm = dict(eps=0.01, theta=0.5, p=5)
+    _, dev = _systems(sizes, 1300)
+    s = F.Solver(sum(sizes), p_max=5, leaf_size=64, kernel=0, precision=precision)
+    ref = [[x.clone() for x in o] for o in _forces(F, s, dev, False, **prm)]
+    for _ in range(2):
+        for got, want in zip(_forces(F, s, dev, True, **prm), ref):
+            assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    reqs, out = s._requests(dev, True)
+    last = len(sizes) - 1
+    for x in out[last]:
+        x.fill_(7.0)
+    reqs[last].mass = None
+    s._raise(F.lib().fmm_forces_batched(s._h, len(dev), reqs, prm["eps"], prm["theta"], prm["p"]))
+    for k, (got, want) in enumerate(zip(out, ref)):
+        for x, y in zip(got, want):
+            assert bool((x == 7.0).all()) if k == last else torch.equal(x, y)
+    s.close()

@@ -410,8 +410,8 @@ int p2p_window_sources(bool mixed);
 // near, all are, and each share of each particle takes a row of partial sums:
 // 2^25 rows (1 GiB) in all up to 2^20 particles, 32 a particle beyond.
 __host__ __device__ static inline int p2p_share_max(int n) {
-  const int s = (1 << 25) / (n > 0 ? n : 1);
-  return s > 128 ? 128 : s < 32 ? 32 : s;
+  if (n <= 1 << 18) return 128;
+  return n >= 1 << 20 ? 32 : (1 << 25) / n;
 }
 // Source windows of a share in a system of n particles (0: shares of whole chunks):
 // small systems have too few leaves to fill the chip, so every window is a share;
@@ -434,8 +434,8 @@ __host__ __device__ static inline int p2p_leaf_chunks(int g, int window, int lea
 }
 // at most share_max shares of a list of cnt entries, of at least `chunks` chunks
 __host__ __device__ static inline int p2p_share_chunks(int cnt, int share_max, int chunks) {
-  const int per = ((cnt + 63) / 64 + share_max - 1) / share_max;
-  return per > chunks ? per : chunks;
+  const int all = (cnt + 63) / 64;
+  return all <= share_max * chunks ? chunks : (all + share_max - 1) / share_max;
 }
 // Strides of the cells' rows at maximum degree p, of coefficients and of folded
 // moments: even, so that every FP64 row starts on 16 bytes, whatever the order

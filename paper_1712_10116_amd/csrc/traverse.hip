@@ -1037,8 +1037,8 @@ __device__ __forceinline__ void chunk_windows(const DevTree &t, int off, int cnt
 // and for systems cut by windows the whole wavefront on one leaf after the
 // other (it adds up the source counts of the leaf's chunks).  A workgroup
 // allocates its items and rows with one atomic each.
-__global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw_min,
-                                                               int leaf_size) {
+// chunks: p2p_leaf_chunks of 1, 2 and 4 windows a share (the same in every lane).
+__global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw_min, int3 chunks) {
   __shared__ int s_items[PLAN_WAVES];
   __shared__ unsigned long long s_rows[PLAN_WAVES];
   __shared__ unsigned s_item0;
@@ -1062,14 +1062,14 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
       cnt = t.p2p_cnt[A];
       off = t.p2p_off[A];
       g = p2p_share_windows(n);
-      const int chunks = p2p_leaf_chunks(g, t.p2p_src_window, leaf_size);
-      if (chunks > 1 || t.uncut) g = 0;
+      const int whole = g == 0 ? P2P_SHARE_CHUNKS : g == 1 ? chunks.x : g == 2 ? chunks.y : chunks.z;
+      if (whole > 1 || t.uncut) g = 0;
       share_max = p2p_share_max(n);
       // list entries of a share of whole chunks
       per = nA > P2P_SHARE_MAX_LEAF || t.uncut
                 ? max(cnt, 1)
-                : 64 * p2p_share_chunks(cnt, share_max, max(chunks, 1));
-      groups = max(1, (cnt + per - 1) / per);
+                : 64 * p2p_share_chunks(cnt, share_max, max(whole, 1));
+      groups = cnt <= per ? 1 : (cnt + per - 1) / per;
     }
     // leaves whose chunks are counted, and those cut by windows
     const unsigned long long counted =
@@ -1077,30 +1077,29 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
     unsigned long long fine = counted;
     int used = 0;  // chunks counted so far in this batch (kept up to PLAN_CHUNKS)
     for (unsigned long long m = counted; m; m &= m - 1) {
-      const int l = (int)__ffsll((long long)m) - 1;
-      const int c = __shfl(cnt, l, 64), o = __shfl(off, l, 64), gl = __shfl(g, l, 64);
-      const int most = __shfl(share_max, l, 64), gs = 31 - __clz(gl);  // gl: a power of two
-      int sum[P2P_SHARE_STEPS] = {};
-      for (int qb = 0; qb < c; qb += 256) {
-        int nw[4];
-        chunk_windows(t, o, c, qb, nw);
+      const int l = (int)__ffsll((long long)m) - 1;  // the same in every lane
+      const int c = __builtin_amdgcn_readlane(cnt, l), o = __builtin_amdgcn_readlane(off, l);
+      const int gl = __builtin_amdgcn_readlane(g, l);
+      const int most = __builtin_amdgcn_readlane(share_max, l), gs = 31 - __clz(gl);  // gl: a power of two
+      const int kept = used;
+      int step = 0, shares = 0;
+      for (;; ++step) {  // a second round at lists of more than p2p_share_max shares only
+        shares = 0;
+        used = kept;
+        for (int qb = 0; qb < c; qb += 256) {
+          int nw[4];
+          chunk_windows(t, o, c, qb, nw);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          if (qb + 64 * k < c) {
-            if (lane == 0 && used < PLAN_CHUNKS) s_nw[w][used] = (uint16_t)nw[k];
-            ++used;
+          for (int k = 0; k < 4; ++k) {
+            if (qb + 64 * k < c) {
+              if (lane == 0 && used < PLAN_CHUNKS) s_nw[w][used] = (uint16_t)nw[k];
+              ++used;
+            }
+            shares += (nw[k] + (gl << step) - 1) >> (gs + step);
           }
-#pragma unroll
-          for (int j = 0; j < P2P_SHARE_STEPS; ++j) sum[j] += (nw[k] + (gl << j) - 1) >> (gs + j);
         }
+        if (shares <= most || step == P2P_SHARE_STEPS - 1) break;
       }
-      int step = 0, shares = sum[0];
-#pragma unroll
-      for (int j = 1; j < P2P_SHARE_STEPS; ++j)
-        if (shares > most) {
-          step = j;
-          shares = sum[j];
-        }
       if (shares > most) {
         fine &= ~(1ull << l);
       } else if (lane == l) {
@@ -1151,15 +1150,17 @@ __global__ __launch_bounds__(PLAN_WAVES * 64) void k_p2p_plan(DevTree t, int npw
     }
     int at = 0;  // the batch's chunks in the order counted
     for (unsigned long long m = counted; m; m &= m - 1) {
-      const int l = (int)__ffsll((long long)m) - 1;
-      const int c = __shfl(cnt, l, 64), o = __shfl(off, l, 64), gl = __shfl(g, l, 64);
+      const int l = (int)__ffsll((long long)m) - 1;  // the same in every lane
+      const int c = __builtin_amdgcn_readlane(cnt, l), o = __builtin_amdgcn_readlane(off, l);
+      const int gl = __builtin_amdgcn_readlane(g, l);
       if (!(fine >> l & 1)) {
         at += (c + 63) >> 6;
         continue;
       }
-      const int Al = __shfl(A, l, 64), nl = __shfl(nA, l, 64), Tl = __shfl(T, l, 64);
-      const int64_t il = (int64_t)__shfl((unsigned long long)i0, l, 64);
-      const int64_t rl = (int64_t)__shfl((unsigned long long)r0, l, 64);
+      const int Al = __builtin_amdgcn_readlane(A, l), nl = __builtin_amdgcn_readlane(nA, l);
+      const int Tl = __builtin_amdgcn_readlane(T, l);
+      const int64_t il = (int64_t)readlane_u64((unsigned long long)i0, l);
+      const int64_t rl = (int64_t)readlane_u64((unsigned long long)r0, l);
       int done = 0;  // shares of the chunks before
       for (int qb = 0; qb < c; qb += 64, ++at) {
         int nw;
@@ -1192,13 +1193,17 @@ hipError_t launch_p2p_plan(const DevTree &t, const BuildArgs &a, hipStream_t s) 
   // bounds the cells a context holds), a lane per cell where they are not: a
   // workgroup's items then follow 1024 cells in order, and so the XCDs' shares
   const int64_t cells = std::min<int64_t>(t.cap_nodes, (int64_t)a.n + 1024);
+  int3 chunks;
+  chunks.x = p2p_leaf_chunks(1, t.p2p_src_window, a.leaf_size);
+  chunks.y = p2p_leaf_chunks(2, t.p2p_src_window, a.leaf_size);
+  chunks.z = p2p_leaf_chunks(4, t.p2p_src_window, a.leaf_size);
   const int g = a.n_req == 1 ? p2p_share_windows(a.n_max) : 1;  // 1: of the smallest cut by windows
   const bool whole = a.n_max > P2P_SHARE_FINE_N || g == 0 ||
-                     p2p_leaf_chunks(g, t.p2p_src_window, a.leaf_size) > 1;
+                     (g == 1 ? chunks.x : g == 2 ? chunks.y : chunks.z) > 1;
   const int npw = whole ? 64 : 1;
   const int blocks = (int)std::min<int64_t>(1024, (cells + npw * PLAN_WAVES - 1) / (npw * PLAN_WAVES));
   hipLaunchKernelGGL(k_p2p_plan, dim3(std::max(blocks, 1)), dim3(PLAN_WAVES * 64), 0, s, t, npw,
-                     a.leaf_size);
+                     chunks);
   return hipGetLastError();
 }
 

@@ -581,13 +581,12 @@ __device__ __forceinline__ void header_init(const DevTree &t, bool nonfinite) {
   h->nonfinite = nonfinite ? 1 : 0;
   h->max_prefix = 0;
   h->n_leaves = 0;
-  // as k_reset_lists: the first walk of a tree needs no launch for it
+  // as k_reset_lists, but for the open lists: a first walk by paths needs no launch for it
   h->m2l_cursor = 0;
   h->p2p_cursor = 0;
   h->p2p_pairs = 0;
   h->item_cursor = 0;
   h->part_cursor = 0;
-  for (int l = 0; l < FMM_NLEVELS; ++l) h->open_cursor[l] = 0;
 }
 
 __device__ __forceinline__ void root_init(const DevTree &t, int r, int leaf_size) {

@@ -54,7 +54,8 @@ typedef enum {
     FMM_EDEVICE = 3,     /* a HIP runtime call failed                             */
     FMM_ENONFINITE = 4,  /* an input position was NaN or infinite                 */
     FMM_ESTALE = 5,      /* fmm_evaluate without a tree built for these particles */
-    FMM_EOVERFLOW = 6    /* a list or tree exceeded its workspace after regrowth  */
+    FMM_EOVERFLOW = 6    /* a list or tree exceeded its workspace after regrowth,
+                            or needs more than 2^31 - 1 list entries              */
 } fmm_status;
 
 typedef enum {
@@ -273,11 +274,12 @@ fmm_status fmm_forces_batched(fmm_ctx *ctx, int n_req, const fmm_request *reqs, 
  * particle-particle interactions evaluated by P2P. */
 fmm_status fmm_tree_info(fmm_ctx *ctx, int64_t info[9]);
 
-/* Builds of few active particles (all systems of a batch together) run as
- * a single-workgroup launch and a walk with one readback up to 1024 particles,
- * the most that launch holds: enable = 1 (the default) or 2; enable = 0 never.
- * Trees, lists and results are the same either way (for comparison and
- * tests).  Other values: FMM_EINVAL. */
+/* Small solves, queued without reading the tree's size back.  enable = 1 (the
+ * default) or 2: builds of up to 1024 active particles (all systems of a batch
+ * together) run as a single-workgroup launch, and build, walk and evaluation
+ * of up to 400 leaf_size particles are queued to the end, with one readback.
+ * enable = 0: neither.  Trees, lists and results are the same either way (for
+ * comparison and tests).  Other values: FMM_EINVAL. */
 fmm_status fmm_set_small_path(fmm_ctx *ctx, int enable);
 
 /* enable = 1: multi-workgroup builds queue the tree and the walk for the

@@ -1,9 +1,10 @@
 // Host side of the C ABI declared in include/fmm355.h.
 //
 // A context owns one device workspace sized from max_n at creation.  Every
-// call is queued on the context's stream; fmm_build waits once, at its end,
-// to read the list sizes (and to regrow a list buffer that turned out too
-// small, which is then rebuilt once).
+// call is queued on the context's stream; a build waits to read the tree's
+// header, once where tree, walk and evaluation are queued without its sizes, for
+// the tree's and for the lists' sizes otherwise (and again after a buffer that
+// turned out too small has been regrown).
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>

@@ -144,7 +144,7 @@ struct DevTree {
   double4 *part;                 // [cap_part] ax, ay, az, pot
   // scratch
   int32_t *scan_part;          // [FMM_SCAN_BLOCKS]
-  double *bbox_part;           // [bbox blocks][6]
+  double *bbox_part;           // [bbox blocks][FMM_BBOX_COLS]
   uint32_t *sort_hist;         // [256][sort blocks]
   uint32_t *sort_dtot;         // [256] digit totals
   uint32_t *scan_blk;          // block sums of the generic scan
@@ -336,7 +336,8 @@ hipError_t launch_traverse(const DevTree &t, const BuildArgs &a, hipStream_t s);
 hipError_t launch_traverse_dev(const DevTree &t, const BuildArgs &a, int levels, hipStream_t s);
 // Trees of at most this many split cells are walked in the path form: at 1,590
 // it took 175 us against some 280 by levels, at 2,769 (2^20 sphere) a
-// workgroup per group takes longer than the wavefront form's 168.
+// workgroup per group takes longer than the wavefront form's 168.  Where between
+// the two sizes the forms cross has not been measured.
 #define WALK_PATH_GROUPS 1600
 // Whether a tree of n particles, not yet built, is expected to have that few split
 // cells: those of the last tree (of last_n) in proportion.

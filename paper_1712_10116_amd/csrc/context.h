@@ -38,7 +38,8 @@ struct fmm_ctx {
   hipEvent_t hdr_ev;                // recorded after a queued header readback
   hipEvent_t up_done;               // upward pass queued beside the walk has finished
   int n_nodes, depth;
-  int small_max;           // single-workgroup build and walk for batches of at most this many particles
+  int small_max;           // one-workgroup build of batches of at most this many particles; -1:
+                           // none, and small trees are not queued without reading their size
   // split levels of recent multi-workgroup builds: the next build queues the
   // tree and the walk for the deepest of them behind the sort, with one
   // readback at the end, and falls back to reading the split depth first when

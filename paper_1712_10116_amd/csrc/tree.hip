@@ -771,9 +771,6 @@ __global__ __launch_bounds__(FMM_BLOCK) void k_tree_count(DevTree t, int l, int 
 }
 
 
-// Children of the splitting cells of level l; a child is a leaf when it holds
-// at most leaf_size particles or sits at the deepest level, and leaves are
-// counted here.
 // Sum of v over a block of FMM_BLOCK threads (all of them call it).
 __device__ __forceinline__ int block_sum(int v, int *part) {
   v = wave_sum(v);
@@ -786,7 +783,9 @@ __device__ __forceinline__ int block_sum(int v, int *part) {
   return tot;
 }
 
-// Each block first takes its offset among the children of the level (the
+// Children of the splitting cells of level l; a child is a leaf when it holds
+// at most leaf_size particles or sits at the deepest level, and leaves are
+// counted here.  Each block first takes its offset among the children of the level (the
 // child counts of the earlier blocks, from k_tree_count) and the level's
 // total; block 0 records where the next level ends.
 __global__ __launch_bounds__(FMM_BLOCK) void k_tree_emit(DevTree t, int l, int leaf_size) {

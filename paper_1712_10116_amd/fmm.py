@@ -377,8 +377,9 @@ class Solver:
         return self.evaluate_batched(systems, p=p)
 
     def set_small_path(self, enable):
-        """Single-workgroup build for small batches: True (default) or 2 up to
-        1024 particles (the most that launch holds), False never; same trees,
+        """Small solves queued without reading the tree's size back: True
+        (default) or 2, with a single-workgroup build up to 1024 particles and
+        the whole solve queued up to 400 leaf sizes; False: neither.  Same trees,
         lists and results either way."""
         mode = 2 if enable == 2 else int(bool(enable))
         self._raise(lib().fmm_set_small_path(self._h, mode))

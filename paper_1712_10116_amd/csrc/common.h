@@ -393,14 +393,17 @@ hipError_t launch_upward(const DevTree &t, const EvalArgs &e, hipStream_t s);
 bool eval_order_supported(int p);
 // Wavefronts for the near-field items of a tree of n particles and some
 // n_nodes cells; their number is read on the device: about one to two per leaf
-// of a large system, up to one per staged window of a small one of few leaves.
-// The wavefronts stride over the items, so more than GRID_WAVES (a launch holds
-// less than 2^32 threads) are not needed, and one without an item costs 0.25 ns
-// (100,000 particles in leaves of 4, 8 for each of 68,350 cells: P2P 106 -> 219 us).
+// of a large system, up to one per staged window of a small one of few leaves,
+// and one per 64 particles where leaves are larger.  The wavefronts stride over the
+// items, so more than GRID_WAVES (a launch holds less than 2^32 threads) are not
+// needed, and one without an item costs 0.25 ns (100,000 particles in leaves of 4, 8
+// for each of 68,350 cells: P2P 106 -> 219 us).
 #define GRID_WAVES (1 << 24)
 static inline int p2p_grid_items(int n, int n_nodes) {
   int64_t w = 2 * (int64_t)n_nodes;
   if (n <= 131072) w = n_nodes > 32768 ? n_nodes : n_nodes > 4096 ? 32768 : 8 * (int64_t)n_nodes;
+  const int64_t uncut = (int64_t)n / 64 + n_nodes;
+  if (w < uncut) w = uncut;
   return (int)(w < 1 ? 1 : w > GRID_WAVES ? GRID_WAVES : w);
 }
 // sources of one staged P2P window

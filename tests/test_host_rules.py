@@ -139,16 +139,16 @@ def test_walk_form_follows_the_size_of_the_tree_to_come(tmp_path):
 def test_near_field_grid_stays_launchable(tmp_path):
     trees = [(1, 0), (1000, 90), (131072, 17408), (131073, 17408), (1 << 24, 4000000),
              (1 << 25, 1 << 25), (1 << 28, (1 << 28) - 1), (100000, (1 << 28) - 1), (100000, 68350),
-             (100000, 4096), (100000, 4097), (100000, 32769)]
+             (100000, 4096), (100000, 4097), (100000, 32769), (1024, 1), (100000, 22)]
     out = _run(tmp_path, "".join('printf("%%d ", p2p_grid_items(%d, %d));' % t for t in trees)
                + 'printf("%d", GRID_WAVES);')
     for (n, cells), waves in zip(trees, map(int, out)):
         assert 1 <= waves and waves * 64 < 2 ** 32
-        if n > 131072:
-            assert waves == min(2 * cells, int(out[-1]))
-        else:  # one per cell at least, no more than 8, and not many without an item
-            assert min(max(cells, 1), int(out[-1])) <= waves <= max(8 * cells, 1)
-            assert waves <= max(32768, cells)
+        most = int(out[-1])
+        assert waves == most or waves >= n // 64 + cells  # every 64 sinks of uncut leaves
+        assert waves <= max(1, min(most, max((8 if n <= 131072 else 2) * cells, n // 64 + cells)))
+        if n <= 131072:  # not many without an item
+            assert waves <= max(32768, n // 64 + cells)
 
 
 def test_sort_rule(tmp_path):
